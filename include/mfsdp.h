@@ -251,8 +251,8 @@ typedef struct {
  *   beta >= 0, weight >= 0: S <- beta S + weight G G^T (L) and G^T G (R); 1, 1 = accumulation
  *   eps > 0, eps_rel >= 0: the root is taken of S + rho I, rho = eps + eps_rel ||S||_F
  *   refresh 0/1: recompute PL, PR from the updated statistics (1) or use the stored ones (0)
- *   root_iters 1 .. 100: iterations of the coupled Newton inverse-root iteration (20 reaches fp32
- *   accuracy for rho >= 1e-6 ||S||_F on the tested spectra; see mfsdp_inverse_root). */
+ *   root_iters 1 .. 100: at most this many iterations of the coupled inverse-root iteration (it ends
+ *   by itself; 20 is enough for rho >= 1e-6 ||S||_F on the tested spectra; see mfsdp_inverse_root). */
 typedef struct {
   double lr;
   double weight_decay;
@@ -288,9 +288,9 @@ int mfsdp_shampoo_step(const mfsdp_shampoo_entry* entries, int64_t count,
 size_t mfsdp_inverse_root_workspace_size(int64_t d, int32_t p, int32_t iters);
 
 /* out = (a + rho I)^(-1/p), rho = eps + eps_rel ||a||_F, for a symmetric positive semidefinite
- * d x d fp32 matrix `a` (row-major, device; read only; not checked for symmetry), by `iters`
- * steps of the coupled Newton iteration (Guo and Higham 2006), the iteration the Shampoo step
- * uses (products as there). p in {1, 2, 4}; 1 <= d <= 65536; eps > 0; eps_rel >= 0;
+ * d x d fp32 matrix `a` (row-major, device; read only; not checked for symmetry), by at most `iters`
+ * steps of a coupled iteration (p = 1, 2: Newton's, Guo and Higham 2006; p = 4: the same coupling with
+ * a quadratic factor, the iteration the Shampoo step uses; products as there). p in {1, 2, 4}; 1 <= d <= 65536; eps > 0; eps_rel >= 0;
  * 1 <= iters <= 100.
  * `out` (d x d fp32, device) must not overlap `a`. In fp32 the iteration is stable while rho is
  * at least about 1e-6 ||a||_F; a smaller ridge can diverge. Same stream, workspace and error

@@ -17,10 +17,32 @@ namespace mfsdp {
 
 constexpr int kShTile = 128;     // GEMM output tile and padding granularity
 constexpr int kShCopyTile = 64;  // copy / init / apply tile
-// Convergence of the inverse-root iteration: once max |M_k - I| over the real block is below this,
-// the remaining change of X is below 2.5e-6 relative (T_k = I - (M_k - I)/p, then quadratic), and
-// the side's remaining products are skipped.
+// Convergence of the Newton inverse-root iteration (p = 1, 2): once max |M_k - I| over the real block
+// is below this, the remaining change of X is below 5e-6 relative (T_k = I - (M_k - I)/p, then
+// quadratic), and the side's remaining products are skipped.
 constexpr float kShConvTol = 1e-5f;
+
+// The fourth-root iteration (p = 4): X <- X T, M <- T^4 M with T = a I + b M + c M^2, M_0 = z (S + rho I),
+// z = 1 / ||S + rho I||_F, so that the spectrum of every M stays in (0, 1] (rounding aside).
+// While max |M - I| >= kRootSwitch the coefficients are the aggressive row: the quadratic q for which
+// f(x) = x q(x)^4 has its inner maximum and f(1) equal to 1 and its inner minimum equal to 0.7. Small
+// eigenvalues grow by a^4 = 11.9 per iteration (Newton: (5/4)^4 = 2.44), and [0.0863, 1] maps into
+// [0.7, 1], so no eigenvalue already near 1 is pushed far down again (which would cost it its relative
+// accuracy: the unconstrained minimax quadratic grows 37-fold but loses a digit or two). Below
+// kRootSwitch the row is the expansion of x^(-1/4) about 1 (third-order convergence). Below
+// kRootFinalTol one last X update follows (its cubic error is negligible), nothing else.
+constexpr float kRootAggressive[3] = {1.85835485f, -2.08442379f, 1.22606893f};
+constexpr float kRootFinal[3] = {45.0f / 32.0f, -18.0f / 32.0f, 5.0f / 32.0f};
+constexpr float kRootSwitch = 0.31f;
+constexpr float kRootFinalTol = 1e-4f;
+constexpr float kRootDone = -1.0f;  // residual slot of a side whose last X update is done
+// Products of one iteration (ShGemmDesc::root_op); a is the current row's a.
+constexpr int kRootFirst = 1;  // T_0 = c M M + b M + a I (becomes X_1 / z^(1/4))
+constexpr int kRootU = 2;      // U = T - a I = c M M + b M
+constexpr int kRootX = 3;      // X' = X U + a X (small while M is: keeps X's rounding errors down)
+constexpr int kRootT2 = 4;     // T^2 = U U + 2 a U + a^2 I (T_0 T_0 in the first iteration)
+constexpr int kRootT4 = 5;     // T^4 = T^2 T^2
+constexpr int kRootM = 6;      // M' = T^4 M
 
 // C = alpha * P Q^T + beta * E + diag * I over one padded problem (P: M x K, Q: N x K, all
 // row-major with the given row strides; M, N and K multiples of kShTile). sym: only tiles bi <= bj are computed; each is stored at
@@ -37,10 +59,21 @@ struct ShGemmDesc {
   int32_t sym;
   int32_t tile_begin;  // prefix over the problems of one launch
   float alpha, beta, diag;
+  // p = 4 root iteration: the product of the iteration this is (0: none). Its alpha, beta and diag
+  // come from the row that the side's residual selects, times *scale if set.
+  int32_t root_op;
+  int32_t out_idx;       // kRootX, kRootFirst: index of the X buffer written ...
+  int32_t* xsel;         // ... stored here by the problem's first block
+  const float* scale;
+  // operand buffers selected on the device: P (Q) is P1 (Q1) when *psel (*qsel) is 1
+  const float* P1;
+  const float* Q1;
+  const int32_t* psel;
+  const int32_t* qsel;
   // inverse-root iteration only (null otherwise). Each side has two residual slots; iteration k
   // (parity q) reads slot q^1 (written by iteration k-1) and writes slot q:
-  const float* conv_in;  // skip the product when this residual is below kShConvTol (and, with
-                         // copy_on_skip, copy the tile of E into C instead)
+  const float* conv_in;  // p < 4: skip the product when this residual is below kShConvTol (and, with
+                         // copy_on_skip, copy the tile of E into C instead); p = 4: see root_op
   float* clear;          // set to 0 by the problem's first block before anything else
   float* resid_out;      // max |C - I| over the real block (rows, cols < valid), atomic max
   int32_t copy_on_skip;
@@ -66,6 +99,8 @@ struct ShCopyDesc {
   int32_t tiles_n;     // column tiles of the domain
   int32_t tile_begin;
   int32_t dst_bf16;    // dir 0: dst and dstT hold bf16
+  const void* src1;    // dir 1: the source when *sel is 1 (sel may be null)
+  const int32_t* sel;
 };
 
 // Sum of squares and trace of a padded d_pad x d_pad statistic, in row chunks (fp64 partials).
@@ -80,7 +115,8 @@ struct ShNormDesc {
 };
 
 // Root scalars of one problem from its partials: rho = eps + eps_rel ||S||_F,
-// z = (1 + p) / (2 ||S + rho I||_F) over the real dimension d; out = {rho, z, z^(1/p)}.
+// z over the real dimension d (p = 4: 1 / ||S + rho I||_F; else (1 + p) / (2 ||S + rho I||_F));
+// out = {rho, z, z^(1/p)}.
 struct ShScalarDesc {
   const double* partials;
   int32_t nchunks;
@@ -88,7 +124,8 @@ struct ShScalarDesc {
   float* out;
 };
 
-// M = z (S + rho I), X = z^(1/p) I over the padded domain (the padded diagonal is rho as well).
+// M = z (S + rho I) and, if X is set, X = z^(1/p) I over the padded domain (the padded diagonal is
+// rho as well).
 struct ShInitDesc {
   const float* S;
   float* M;

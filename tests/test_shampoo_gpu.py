@@ -97,6 +97,35 @@ def test_inverse_root_matches_oracle(native, d, p):
     np.testing.assert_array_equal(from_dev(ad), a)
 
 
+@pytest.mark.parametrize("d", [1, 2, 128, 129, 384])
+@pytest.mark.parametrize("spectrum", ["identity", "flat", "falling", "rank_deficient", "zero"])
+def test_inverse_fourth_root_spectra(native, d, spectrum):
+    """The fourth-root iteration on spectra that take few and many steps, with the cap at the step count
+    that the ridge needs and far above it. Bound: an absolute error of 8 roundings (2^-24 each) of ||A||_F
+    moves A^(-1/4) by at most a quarter of their ratio to the smallest eigenvalue; 2e-6 covers the
+    final factor and the sums."""
+    import torch
+    _say(f"fourth root d={d} {spectrum}")
+    rng = np.random.default_rng(40 + d)
+    q, _ = np.linalg.qr(rng.standard_normal((d, d)))
+    i = np.arange(d)
+    w = {"identity": np.ones(d), "flat": rng.uniform(0.5, 1.5, d), "falling": 1.0 / (1.0 + i),
+         "rank_deficient": np.where(i < (d + 3) // 4, 1.0, 0.0), "zero": np.zeros(d)}[spectrum]
+    a = ((q * w) @ q.T).astype(np.float32)
+    a = (a + a.T) * np.float32(0.5)
+    ref = OS.inverse_root(a.astype(np.float64), 4, 1e-6, 1e-6)
+    norm = np.linalg.norm(a.astype(np.float64) + (1e-6 + 1e-6 * np.linalg.norm(a.astype(np.float64))) * np.eye(d))
+    tol = 2e-6 + 0.25 * 8 * 2.0 ** -24 * norm * np.linalg.norm(ref, 2) ** 4
+    for iters in (11, 100):
+        out = torch.empty((d, d), dtype=torch.float32, device="cuda")
+        native.inverse_root_t(to_dev(a, synth.F32), out, p=4, eps=1e-6, eps_rel=1e-6, iters=iters)
+        _sync()
+        got = from_dev(out)
+        err = rel_fro(got, ref)
+        assert err <= tol, (iters, err, tol)
+        np.testing.assert_array_equal(got, got.T)
+
+
 def test_inverse_root_input_read_in_place_or_copied(native):
     """A tile-multiple d whose input is 16-byte aligned is read where it lies; the same values at a
     4-byte offset take the copy path. Same bits either way."""
