@@ -82,8 +82,8 @@ constexpr int kShStage = 6 * kShPlane;  // both operands of one K step, three pl
 // earlier) are split into LDS. Few products per step (one-part operands) take several steps per
 // stage, so that a barrier and the load latency are spread over more MFMAs.
 template <bool ABF, bool BBF>
-__device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, const float* dP, const float* dQ, int bi,
-                                                 int bj, uint8_t* lds_raw, f32x16 (&acc)[2][2]) {
+__device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, int bj, uint8_t* lds_raw,
+                                                 f32x16 (&acc)[2][2]) {
   constexpr int PA = ABF ? 1 : 3, PB = BBF ? 1 : 3;  // parts per operand
   constexpr int KS = ABF && BBF ? 2 : 1;             // K steps per stage
   static_assert(KS * (PA + PB) <= 6, "a stage holds at most six planes");
@@ -94,8 +94,8 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, const floa
   using TB = typename std::conditional<BBF, u32x2, f32x4>::type;
   // tile rows of both operands (uniform) and this thread's byte offsets into them (32-bit: a tile
   // spans at most 128 rows with a row stride of at most 2 x 65536 elements, under 2^27 bytes)
-  g_cu8* P = (g_cu8*)(dP) + int64_t(bi) * kShTile * d.ldp * ea;
-  g_cu8* Q = (g_cu8*)(dQ) + int64_t(bj) * kShTile * d.ldq * eb;
+  g_cu8* P = (g_cu8*)(d.P) + int64_t(bi) * kShTile * d.ldp * ea;
+  g_cu8* Q = (g_cu8*)(d.Q) + int64_t(bj) * kShTile * d.ldq * eb;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int wr = w >> 1, wc = w & 1;
   const int fr = lane & 31, fh = lane >> 5;
@@ -232,36 +232,7 @@ __global__ __launch_bounds__(256, 3) void sh_gemm_kernel(const ShGemmDesc* __res
   const int e = find_desc(descs, count, blockIdx.x);
   const ShGemmDesc& d = descs[e];
   int lt = blockIdx.x - d.tile_begin;
-  float alpha = d.alpha, beta = d.beta, diag = d.diag;
-  if (d.root_op) {
-    const float r = *d.conv_in;
-    const bool done = r == kRootDone, fin = r < kRootFinalTol;
-    if (lt == 0 && threadIdx.x == 0) {
-      if (d.clear) *d.clear = fin ? kRootDone : 0.0f;
-      if (d.xsel && !done) *d.xsel = d.out_idx;
-    }
-    if (done || (fin && d.root_op >= kRootT2)) return;
-    const bool agg = !(r < kRootSwitch);
-    const float a = agg ? kRootAggressive[0] : kRootFinal[0];
-    if (d.root_op <= kRootU) {
-      alpha = agg ? kRootAggressive[2] : kRootFinal[2];
-      beta = agg ? kRootAggressive[1] : kRootFinal[1];
-      if (d.root_op == kRootFirst) diag = a;
-    } else if (d.root_op == kRootX) {
-      beta = a;
-    } else if (d.root_op == kRootT2 && d.E) {
-      beta = 2.0f * a;
-      diag = a * a;
-    }
-    if (d.scale) {
-      const float sc = *d.scale;
-      alpha *= sc;
-      beta *= sc;
-      diag *= sc;
-    }
-  } else if (d.clear && lt == 0 && threadIdx.x == 0) {
-    *d.clear = 0.0f;
-  }
+  if (d.clear && lt == 0 && threadIdx.x == 0) *d.clear = 0.0f;
   int bi, bj;
   if (d.sym) {
     bi = 0;
@@ -279,7 +250,7 @@ __global__ __launch_bounds__(256, 3) void sh_gemm_kernel(const ShGemmDesc* __res
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int wr = w >> 1, wc = w & 1;
   const int fr = lane & 31, fh = lane >> 5;
-  if (!d.root_op && d.conv_in && *d.conv_in < kShConvTol) {  // converged side: the iterate no longer changes
+  if (d.conv_in && *d.conv_in < kShConvTol) {  // converged side: the iterate no longer changes
     if (d.copy_on_skip) {
       const g_cf32* src = (const g_cf32*)(d.E);
       g_f32* dst = (g_f32*)(d.C);
@@ -300,14 +271,12 @@ __global__ __launch_bounds__(256, 3) void sh_gemm_kernel(const ShGemmDesc* __res
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
-  const float* dP = d.psel && *d.psel ? d.P1 : d.P;
-  const float* dQ = d.qsel && *d.qsel ? d.Q1 : d.Q;
   if (d.q_bf16 && d.p_bf16)
-    sh_tile_products<true, true>(d, dP, dQ, bi, bj, lds_raw, acc);
+    sh_tile_products<true, true>(d, bi, bj, lds_raw, acc);
   else if (d.q_bf16)
-    sh_tile_products<false, true>(d, dP, dQ, bi, bj, lds_raw, acc);
+    sh_tile_products<false, true>(d, bi, bj, lds_raw, acc);
   else
-    sh_tile_products<false, false>(d, dP, dQ, bi, bj, lds_raw, acc);
+    sh_tile_products<false, false>(d, bi, bj, lds_raw, acc);
 
   // Epilogue, in two passes over the tile's row halves (the waves with wr = h hold rows
   // 64 h .. 64 h + 63). Accumulator element v of block (i, j) is row 32 i + 8 (v / 4) + 4 (lane / 32)
@@ -355,9 +324,9 @@ __global__ __launch_bounds__(256, 3) void sh_gemm_kernel(const ShGemmDesc* __res
             const int r = 64 * h + rl, c = wc * 64 + j * 32 + fr;
             if (diag_tile && r > c) continue;  // filled from the upper triangle below
             const int64_t gr = r0 + r, gc = c0 + c;
-            float x = alpha * acc[i][j][v];
-            if (E) x += beta * tl[rl * kShTile + c];
-            if (gr == gc) x += diag;
+            float x = d.alpha * acc[i][j][v];
+            if (E) x += d.beta * tl[rl * kShTile + c];
+            if (gr == gc) x += d.diag;
             C[gr * d.ldc + gc] = x;
             acc[i][j][v] = x;
             if (gr < d.valid && gc < d.valid) {
@@ -439,7 +408,7 @@ __global__ __launch_bounds__(256) void sh_copy_out_kernel(const ShCopyDesc* __re
   const int lt = blockIdx.x - d.tile_begin;
   const int ti = lt / d.tiles_n, tj = lt - ti * d.tiles_n;
   const int t = threadIdx.x, c = t & 63, rr = t >> 6;
-  const g_cf32* src = (const g_cf32*)(d.sel && *d.sel ? d.src1 : d.src);
+  const g_cf32* src = (const g_cf32*)(d.src);
   g_f32* dst = (g_f32*)(d.dst);
   const int64_t gc = int64_t(tj) * kShCopyTile + c;
   if (gc >= d.cols) return;
@@ -499,9 +468,14 @@ __global__ void sh_scalars_kernel(const ShScalarDesc* __restrict__ descs, int co
   d.out[0] = float(rho);
   d.out[1] = float(z);
   d.out[2] = float(pow(z, 1.0 / double(p)));
+  if (p == 4) {
+    // X's scale: every eigenvalue x of M_0 is at least z rho, and X^4 M_0 <= 1
+    const double b = fmin(fmax(log2(kRootBound) + 0.25 * log2(z * rho), -100.0), 100.0);
+    d.out[3] = float(exp2(floor(b)));
+  }
 }
 
-// M = z (S + rho I) and, if X is set, X = z^(1/p) I (M may alias S).
+// M = z (S + rho I), X = z^(1/p) I (M may alias S).
 __global__ __launch_bounds__(256) void sh_init_kernel(const ShInitDesc* __restrict__ descs, int count) {
   const int e = find_desc(descs, count, blockIdx.x);
   const ShInitDesc& d = descs[e];
@@ -517,7 +491,7 @@ __global__ __launch_bounds__(256) void sh_init_kernel(const ShInitDesc* __restri
     const int64_t o = gr * d.ld + gc;
     const bool dg = gr == gc;
     d.M[o] = z * (d.S[o] + (dg ? rho : 0.0f));
-    if (d.X) d.X[o] = dg ? zp : 0.0f;
+    d.X[o] = dg ? zp : 0.0f;
   }
 }
 

@@ -47,6 +47,7 @@ struct Arena {
 
 enum OpKind {
   kOpCopyIn, kOpCopyOut, kOpGemm, kOpNorm, kOpScalars, kOpInit, kOpApply,
+  kOpRoot, kOpRootIn, kOpRootOut,
   kOpSoapPrep, kOpSoapAdam, kOpEye, kOpQrPanel, kOpQrCol, kOpQrT,
   kOpFork,  // the auxiliary stream waits for everything enqueued so far on the caller's stream
   kOpJoin   // the caller's stream waits for everything enqueued so far on the auxiliary stream
@@ -57,6 +58,7 @@ struct Op {
   int count;
   int total;  // grid blocks
   int aux;    // 1: launched on the auxiliary stream
+  size_t tiles_off = 0;  // kOpRoot: the launch's tile list
 };
 
 // Per-call scalars the kernels take by value.
@@ -168,6 +170,12 @@ inline int run(Build& b, char* ws, size_t desc_at, hipStream_t main_st, const Ru
       case kOpCopyIn: e = launch_sh_copy(reinterpret_cast<ShCopyDesc*>(dp), o.count, o.total, 0, st); break;
       case kOpCopyOut: e = launch_sh_copy(reinterpret_cast<ShCopyDesc*>(dp), o.count, o.total, 1, st); break;
       case kOpGemm: e = launch_sh_gemm(reinterpret_cast<ShGemmDesc*>(dp), o.count, o.total, st); break;
+      case kOpRoot:
+        e = launch_root(reinterpret_cast<RootDesc*>(dp), reinterpret_cast<TileRef*>(ws + desc_at + o.tiles_off),
+                        o.total, st);
+        break;
+      case kOpRootIn: e = launch_root_conv(reinterpret_cast<RootConvDesc*>(dp), o.count, o.total, 0, st); break;
+      case kOpRootOut: e = launch_root_conv(reinterpret_cast<RootConvDesc*>(dp), o.count, o.total, 1, st); break;
       case kOpNorm: e = launch_sh_norm(reinterpret_cast<ShNormDesc*>(dp), o.count, o.total, st); break;
       case kOpScalars:
         e = launch_sh_scalars(reinterpret_cast<ShScalarDesc*>(dp), o.count, s.eps, s.eps_rel, s.p, st);

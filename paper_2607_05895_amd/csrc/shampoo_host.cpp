@@ -13,9 +13,10 @@
 //
 // p = 4 (Shampoo): X <- X T, M <- T^4 M, M_0 = A / ||A||_F, T = a I + b M + c M^2: a quadratic T makes
 // one iteration of five products raise the small eigenvalues 11.9-fold where Newton's four raise them
-// 2.44-fold (shampoo_internal.h has the rows of coefficients and the reason for them). Two layers of
-// width 768 / 3072 (24 sides, spectra 1 / (1 + i)): the whole step 35.96 -> 21.74 ms; one 768-wide root of
-// a rank-deficient statistic 2.99 -> 1.84 ms; errors against 64 bits no larger.
+// 2.44-fold (shampoo_internal.h has the rows of coefficients and the reason for them). The iterates are
+// held as split fp16 and multiplied by h2_root_kernel. Two layers of width 768 / 3072 (24 sides, spectra
+// 1 / (1 + i)), the whole step: Newton on three-way bf16 splits 35.96 ms, the quadratic T on them 21.74 ms,
+// on split fp16 14.3 ms; one 768-wide root of a rank-deficient statistic 2.99, 1.84, 0.76 ms.
 // p = 1, 2: the coupled Newton iteration (Guo and Higham, SIAM J. Matrix Anal. Appl. 2006): with
 // z = (1 + p) / (2 ||A||_F),
 //   X_0 = z^(1/p) I,  M_0 = z A,  T_k = ((p + 1) I - M_k) / p,  X_{k+1} = X_k T_k,  M_{k+1} = T_k^p M_k,
@@ -51,6 +52,8 @@ struct Side {
   float* out = nullptr;  // caller destination of the root (d x d, row stride d)
   bool has_out = false;  // copy the root out (decided by the call, not by the pointer value,
                          // so that the size query, which sees no pointers, builds the same ops)
+  // the fourth root in the padded fp32 layout: the caller's buffer when the side works in place
+  float* root(const Build& b) const { return S ? out : b.ptr<float>(M); }
 };
 
 void plan_side(Side& s, int64_t d, Arena& a) {
@@ -154,45 +157,71 @@ int root4_iters(double eps_rel, int64_t d, int iters) {
   return std::min(iters, k + 6);
 }
 
+// The upper 128 x 128 tiles of a launch in the order in which its workgroups take them: bands of 8 block
+// rows, column by column; runs of 64 (two workgroups on each CU of an XCD) go to one XCD, so that the
+// tiles running side by side share operand panels in its L2 (workgroup b runs on XCD b mod 8). The last,
+// partial round keeps the plain order, which spreads it over all XCDs.
+std::vector<TileRef> root_tiles(const std::vector<int64_t>& dps) {
+  std::vector<TileRef> flat;
+  for (size_t e = 0; e < dps.size(); ++e) {
+    const int tn = int(dps[e] / kShTile);
+    for (int r0 = 0; r0 < tn; r0 += 8)
+      for (int c = r0; c < tn; ++c)
+        for (int r = r0; r < std::min(r0 + 8, c + 1); ++r) flat.push_back(TileRef{int32_t(e), int16_t(r), int16_t(c), 0, 0});
+  }
+  constexpr size_t run = 2 * kGemmSlots, round = run * kGemmXcds;
+  std::vector<TileRef> out = flat;
+  for (size_t b = 0; b < flat.size() / round * round; ++b) {
+    const size_t in = b % round;
+    out[b] = flat[b / round * round + (in % kGemmXcds) * run + in / kGemmXcds];
+  }
+  return out;
+}
+
 // The products of the fourth-root iteration (five per side and iteration in four launches; the
-// coefficients are chosen on the device). X_1 is T_0 without its factor z^(1/4), which the second
-// iteration's X product brings in. Buffers: M and T2 alternate as M and its successor, T4 holds U and
-// then T^4, X[0] and X[1] alternate. The X buffer a side ends in is stored at side.xsel.
+// coefficients are chosen on the device). Buffers: T2 and M alternate as M and its successor (M may hold
+// the fp32 statistic until it is converted into T2), T4 holds U and then T^4, X[0] and X[1] alternate. The
+// index of the X buffer a side ends in is stored at side.xsel.
 void add_root4_products(Build& b, const std::vector<Side*>& sides, int iters) {
   struct Launch {
-    std::vector<ShGemmDesc> d;
+    std::vector<RootDesc> d;
+    std::vector<int64_t> dps;
     int tiles = 0;
-    size_t off = 0;
+    size_t off = 0, toff = 0;
   };
-  // launches of iterations 0, 1 (with the scale), and of even and odd later ones
+  // launches of iterations 0 and 1, and of even and odd later ones
   Launch L[4][4];
   for (int v = 0; v < 4; ++v) {
     const int q = v & 1;  // parity of the iteration
     for (Side* s : sides) {
-      const int64_t dp = s->dp;
-      float* A = b.ptr<float>(q == 0 ? s->M : s->T2);
-      float* B = b.ptr<float>(q == 0 ? s->T2 : s->M);
-      float* W = b.ptr<float>(s->T4);
-      float* X1 = b.ptr<float>(s->X[1]);
-      float* xin = b.ptr<float>(s->X[q]);
-      float* xout = b.ptr<float>(s->X[q ^ 1]);
-      auto add = [&](int l, const float* P, const float* Q, const float* E, float* C, int op) {
-        ShGemmDesc g = gemm_desc(P, Q, E, C, dp, dp, E ? dp : 0, dp, dp, dp, dp, 1, 1.0f, 0.0f, 0.0f, L[v][l].tiles);
-        g.root_op = op;
+      const uint16_t* A = b.ptr<uint16_t>(q == 0 ? s->T2 : s->M);
+      uint16_t* B = b.ptr<uint16_t>(q == 0 ? s->M : s->T2);
+      uint16_t* W = b.ptr<uint16_t>(s->T4);
+      uint16_t* xin = b.ptr<uint16_t>(s->X[q]);
+      uint16_t* xout = b.ptr<uint16_t>(s->X[q ^ 1]);
+      auto add = [&](int l, const uint16_t* P, const uint16_t* Q, const uint16_t* E, uint16_t* C, int op) {
+        RootDesc g{};
+        g.P = P;
+        g.Q = Q;
+        g.E = E;
+        g.C = C;
+        g.sc = b.ptr<float>(s->sc);
         g.conv_in = b.ptr<float>(s->resid + sizeof(float) * (q ^ 1));
-        g.valid = int32_t(s->d);
         if (op == kRootX || op == kRootFirst) {
           g.out_idx = q ^ 1;
           g.xsel = b.ptr<int32_t>(s->xsel);
           g.clear = b.ptr<float>(s->resid + sizeof(float) * q);
         }
-        if ((op == kRootX && v == 1) || (op == kRootFirst && iters == 1)) g.scale = b.ptr<float>(s->sc + 2 * sizeof(float));
         if (op == kRootM) g.resid_out = b.ptr<float>(s->resid + sizeof(float) * q);
+        g.K = int32_t(s->dp);
+        g.valid = int32_t(s->d);
+        g.op = op;
         L[v][l].d.push_back(g);
+        L[v][l].dps.push_back(s->dp);
       };
       if (v == 0) {
-        add(0, A, A, A, X1, kRootFirst);
-        add(1, X1, X1, nullptr, B, kRootT2);
+        add(0, A, A, A, xout, kRootFirst);
+        add(1, xout, xout, nullptr, B, kRootT2);
       } else {
         add(0, A, A, A, W, kRootU);
         add(1, xin, W, xin, xout, kRootX);
@@ -202,12 +231,25 @@ void add_root4_products(Build& b, const std::vector<Side*>& sides, int iters) {
       add(3, W, A, nullptr, B, kRootM);
     }
   }
+  // two tile lists: one product per side, and two
+  size_t toff[2] = {0, 0};
+  int total[2] = {0, 0};
+  for (int two = 0; two < (iters > 1 ? 2 : 1); ++two) {
+    const std::vector<TileRef> t = root_tiles(two ? L[1][1].dps : L[0][0].dps);
+    toff[two] = b.put(t);
+    total[two] = int(t.size());
+  }
   for (int v = 0; v < std::min(iters, 4); ++v)
-    for (Launch& l : L[v]) l.off = b.put(l.d);
+    for (Launch& l : L[v]) {
+      const int two = l.d.size() > sides.size() ? 1 : 0;
+      l.off = b.put(l.d);
+      l.toff = toff[two];
+      l.tiles = total[two];
+    }
   for (int k = 0; k < iters; ++k) {
     Launch* l = L[k < 2 ? k : 2 + (k & 1)];
     for (int i = 0; i < (k == iters - 1 ? (k == 0 ? 1 : 2) : 4); ++i)
-      b.ops.push_back(Op{kOpGemm, l[i].off, int(l[i].d.size()), l[i].tiles});
+      b.ops.push_back(Op{kOpRoot, l[i].off, int(l[i].d.size()), l[i].tiles, 0, l[i].toff});
   }
 }
 
@@ -220,6 +262,7 @@ void add_root_ops(Build& b, std::vector<Side*> sides, int p, int iters, double e
   std::vector<ShNormDesc> nd;
   std::vector<ShScalarDesc> sd;
   std::vector<ShInitDesc> idesc;
+  std::vector<RootConvDesc> conv;
   int nblocks = 0, itiles = 0;
   for (Side* s : sides) {
     ShNormDesc n{};
@@ -238,39 +281,54 @@ void add_root_ops(Build& b, std::vector<Side*> sides, int p, int iters, double e
     c.d = int32_t(s->d);
     c.out = b.ptr<float>(s->sc);
     sd.push_back(c);
+    const int tn = int(s->dp / kShCopyTile);
+    if (p == 4) {
+      RootConvDesc r{};
+      r.S = n.S;
+      r.M = b.ptr<uint16_t>(s->T2);
+      r.X0 = b.ptr<uint16_t>(s->X[0]);
+      r.X1 = b.ptr<uint16_t>(s->X[1]);
+      r.out = s->root(b);
+      r.sc = c.out;
+      r.resid = b.ptr<float>(s->resid);
+      r.xsel = b.ptr<int32_t>(s->xsel);
+      r.dp = int32_t(s->dp);
+      r.tile_begin = itiles;
+      itiles += tn * tn;
+      conv.push_back(r);
+      continue;
+    }
     ShInitDesc in{};
     in.S = n.S;
     in.M = b.ptr<float>(s->M);
-    in.X = p == 4 ? nullptr : b.ptr<float>(s->X[0]);
+    in.X = b.ptr<float>(s->X[0]);
     in.resid = b.ptr<float>(s->resid);
     in.ld = s->dp;
     in.sc = c.out;
-    in.tiles_n = int32_t(s->dp / kShCopyTile);
+    in.tiles_n = tn;
     in.tile_begin = itiles;
-    itiles += int((s->dp / kShCopyTile) * (s->dp / kShCopyTile));
+    itiles += tn * tn;
     idesc.push_back(in);
   }
   b.op(kOpNorm, nd, nblocks);
   b.op(kOpScalars, sd, int(sd.size()));
   b.op(kOpInit, idesc, itiles);
+  b.op(kOpRootIn, conv, itiles);
 
   if (p == 4) {
     int64_t dmax = 1;
     for (Side* s : sides) dmax = std::max(dmax, s->dp);
     add_root4_products(b, sides, root4_iters(eps_rel, dmax, iters));
+    b.op(kOpRootOut, conv, itiles);
   } else {
     newton_x = add_newton_products(b, sides, p, iters);
   }
   std::vector<ShCopyDesc> co;
   int ct = 0;
   for (Side* s : sides) {
-    if (!s->has_out) continue;
-    co.push_back(copy_desc(b.ptr<float>(s->X[p == 4 ? 0 : newton_x]), kDtF32, s->out, nullptr, s->d, s->d, s->dp,
-                           s->d, 0, s->d, s->d, ct));
-    if (p == 4) {
-      co.back().src1 = b.ptr<float>(s->X[1]);
-      co.back().sel = b.ptr<int32_t>(s->xsel);
-    }
+    if (!s->has_out || (p == 4 && s->S)) continue;  // (written where it belongs)
+    co.push_back(copy_desc(p == 4 ? s->root(b) : b.ptr<float>(s->X[newton_x]), kDtF32, s->out, nullptr, s->d, s->d,
+                           s->dp, s->d, 0, s->d, s->d, ct));
   }
   b.op(kOpCopyOut, co, ct);
 }
@@ -423,18 +481,8 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
     EntryPlan& e = *ep;
     const size_t i = size_t(ep - P.data());
     // the preconditioners: this step's roots, or the stored ones (read where they lie, or copied)
-    const float* pl = (!refresh && e.L.S) ? en[i].PL : b.ptr<float>(e.L.X[0]);
-    const float* pr = (!refresh && e.R.S) ? en[i].PR : b.ptr<float>(e.R.X[0]);
-    auto sel_p = [&](ShGemmDesc& g, const Side& s) {  // this step's root lies in X[0] or X[1]
-      if (!refresh) return;
-      g.P1 = b.ptr<float>(s.X[1]);
-      g.psel = b.ptr<int32_t>(s.xsel);
-    };
-    auto sel_q = [&](ShGemmDesc& g, const Side& s) {
-      if (!refresh) return;
-      g.Q1 = b.ptr<float>(s.X[1]);
-      g.qsel = b.ptr<int32_t>(s.xsel);
-    };
+    const float* pl = refresh ? e.L.root(b) : e.L.S ? en[i].PL : b.ptr<float>(e.L.X[0]);
+    const float* pr = refresh ? e.R.root(b) : e.R.S ? en[i].PR : b.ptr<float>(e.R.X[0]);
     // U = P_L G P_R^T. Both association orders take the same fp32 flop, but with a bf16 G the product
     // that reads G takes three bf16 MFMAs per step and the other six, so the larger of the two
     // products should be the one with G: a wide G (n > m) forms Y^T = P_R G^T (n x m) first and then
@@ -443,18 +491,14 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
       gy.push_back(gemm_desc(pr, b.ptr<float>(e.g()), nullptr, b.ptr<float>(e.Y), e.np, e.np, 0, e.mp, e.np,
                              e.mp, e.np, 0, 1.0f, 0.0f, 0.0f, ty));
       gy.back().q_bf16 = 1;
-      sel_p(gy.back(), e.R);
       gu.push_back(gemm_desc(pl, b.ptr<float>(e.Y), nullptr, b.ptr<float>(e.u()), e.mp, e.mp, 0, e.np, e.mp,
                              e.np, e.mp, 0, 1.0f, 0.0f, 0.0f, tu));
-      sel_p(gu.back(), e.L);
     } else {
       gy.push_back(gemm_desc(pl, b.ptr<float>(e.gt()), nullptr, b.ptr<float>(e.Y), e.mp, e.mp, 0, e.np, e.mp,
                              e.np, e.mp, 0, 1.0f, 0.0f, 0.0f, ty));
       gy.back().q_bf16 = e.grad_bf16 ? 1 : 0;
-      sel_p(gy.back(), e.L);
       gu.push_back(gemm_desc(b.ptr<float>(e.Y), pr, nullptr, b.ptr<float>(e.u()), e.np, e.np, 0, e.np, e.mp,
                              e.np, e.np, 0, 1.0f, 0.0f, 0.0f, tu));
-      sel_q(gu.back(), e.R);
     }
   }
   b.op(kOpGemm, gy, ty);
@@ -491,7 +535,7 @@ size_t build_root(int64_t d, int p, int iters, double eps_rel, const float* a, f
   s.out = out;
   s.has_out = true;
   desc_at = ar.off;
-  if (!sizing && d == s.dp && aligned(a, 16)) {
+  if (!sizing && d == s.dp && aligned(a, 16) && (p != 4 || aligned(out, 16))) {
     s.S = a;  // read where it lies
   } else {
     std::vector<ShCopyDesc> cin;

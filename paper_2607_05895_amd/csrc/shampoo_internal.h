@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_schedule.h"
+
 namespace mfsdp {
 
 constexpr int kShTile = 128;     // GEMM output tile and padding granularity
@@ -36,8 +38,14 @@ constexpr float kRootFinal[3] = {45.0f / 32.0f, -18.0f / 32.0f, 5.0f / 32.0f};
 constexpr float kRootSwitch = 0.31f;
 constexpr float kRootFinalTol = 1e-4f;
 constexpr float kRootDone = -1.0f;  // residual slot of a side whose last X update is done
-// Products of one iteration (ShGemmDesc::root_op); a is the current row's a.
-constexpr int kRootFirst = 1;  // T_0 = c M M + b M + a I (becomes X_1 / z^(1/4))
+// Every iterate is held as split fp16 (h2_core.h) under a power-of-two scale from a bound on its
+// eigenvalues, which bound its elements: M <= 1, |U| <= 0.9, T^2 <= 3.46, T^4 <= 11.93 (each times its scale at
+// most 2^14, a factor of four inside fp16's range) and X <= (z rho)^(-1/4), whose scale the scalar
+// kernel forms. X lacks the factor z^(1/4) until it is converted back.
+constexpr double kRootBound = 16384.0;
+constexpr float kScM = 16384.0f, kScU = 16384.0f, kScT2 = 4096.0f, kScT4 = 1024.0f;
+// Products of one iteration (RootDesc::op); a is the current row's a.
+constexpr int kRootFirst = 1;  // T_0 = c M M + b M + a I (is X_1)
 constexpr int kRootU = 2;      // U = T - a I = c M M + b M
 constexpr int kRootX = 3;      // X' = X U + a X (small while M is: keeps X's rounding errors down)
 constexpr int kRootT2 = 4;     // T^2 = U U + 2 a U + a^2 I (T_0 T_0 in the first iteration)
@@ -59,21 +67,10 @@ struct ShGemmDesc {
   int32_t sym;
   int32_t tile_begin;  // prefix over the problems of one launch
   float alpha, beta, diag;
-  // p = 4 root iteration: the product of the iteration this is (0: none). Its alpha, beta and diag
-  // come from the row that the side's residual selects, times *scale if set.
-  int32_t root_op;
-  int32_t out_idx;       // kRootX, kRootFirst: index of the X buffer written ...
-  int32_t* xsel;         // ... stored here by the problem's first block
-  const float* scale;
-  // operand buffers selected on the device: P (Q) is P1 (Q1) when *psel (*qsel) is 1
-  const float* P1;
-  const float* Q1;
-  const int32_t* psel;
-  const int32_t* qsel;
-  // inverse-root iteration only (null otherwise). Each side has two residual slots; iteration k
+  // Newton inverse-root iteration only (null otherwise). Each side has two residual slots; iteration k
   // (parity q) reads slot q^1 (written by iteration k-1) and writes slot q:
-  const float* conv_in;  // p < 4: skip the product when this residual is below kShConvTol (and, with
-                         // copy_on_skip, copy the tile of E into C instead); p = 4: see root_op
+  const float* conv_in;  // skip the product when this residual is below kShConvTol (and, with
+                         // copy_on_skip, copy the tile of E into C instead)
   float* clear;          // set to 0 by the problem's first block before anything else
   float* resid_out;      // max |C - I| over the real block (rows, cols < valid), atomic max
   int32_t copy_on_skip;
@@ -99,8 +96,6 @@ struct ShCopyDesc {
   int32_t tiles_n;     // column tiles of the domain
   int32_t tile_begin;
   int32_t dst_bf16;    // dir 0: dst and dstT hold bf16
-  const void* src1;    // dir 1: the source when *sel is 1 (sel may be null)
-  const int32_t* sel;
 };
 
 // Sum of squares and trace of a padded d_pad x d_pad statistic, in row chunks (fp64 partials).
@@ -116,7 +111,7 @@ struct ShNormDesc {
 
 // Root scalars of one problem from its partials: rho = eps + eps_rel ||S||_F,
 // z over the real dimension d (p = 4: 1 / ||S + rho I||_F; else (1 + p) / (2 ||S + rho I||_F));
-// out = {rho, z, z^(1/p)}.
+// out = {rho, z, z^(1/p)} and for p = 4 X's scale.
 struct ShScalarDesc {
   const double* partials;
   int32_t nchunks;
@@ -124,8 +119,7 @@ struct ShScalarDesc {
   float* out;
 };
 
-// M = z (S + rho I) and, if X is set, X = z^(1/p) I over the padded domain (the padded diagonal is
-// rho as well).
+// M = z (S + rho I), X = z^(1/p) I over the padded domain (the padded diagonal is rho as well).
 struct ShInitDesc {
   const float* S;
   float* M;
@@ -135,6 +129,40 @@ struct ShInitDesc {
   const float* sc;     // {rho, z, z^(1/p)}
   int32_t tiles_n;
   int32_t tile_begin;
+};
+
+// One product of the fourth-root iteration: C = alpha P Q + beta E + diag I on dp x dp symmetric h2
+// operands (K = dp, a multiple of 128), alpha, beta and diag from op and the side's residual.
+struct RootDesc {
+  const uint16_t* P;
+  const uint16_t* Q;
+  const uint16_t* E;     // may be null
+  uint16_t* C;
+  const float* sc;       // {rho, z, z^(1/4), X's scale}
+  // two residual slots per side; iteration k (parity q) reads slot q^1 and writes slot q
+  const float* conv_in;
+  float* clear;          // (tile (0, 0)) set to 0, or to kRootDone in the side's last iteration
+  float* resid_out;      // max |C - I| over the real block, atomic max
+  int32_t* xsel;         // (tile (0, 0)) receives out_idx, the index of the X buffer written
+  int32_t out_idx;
+  int32_t K;
+  int32_t valid;
+  int32_t op;
+};
+
+// Conversions over the padded domain: in, M = z (S + rho I) in h2 from fp32; out, z^(1/4) X in fp32 from
+// the X buffer that xsel names.
+struct RootConvDesc {
+  const float* S;
+  uint16_t* M;
+  const uint16_t* X0;
+  const uint16_t* X1;
+  float* out;
+  const float* sc;
+  float* resid;          // the two residual slots: {0, not converged}
+  const int32_t* xsel;
+  int32_t dp;
+  int32_t tile_begin;    // 64 x 64 tiles
 };
 
 // p <- p (1 - lr wd) - lr U (U padded fp32), and optionally update_out = U.
@@ -155,6 +183,9 @@ hipError_t launch_sh_norm(const ShNormDesc* d, int count, int total_blocks, hipS
 hipError_t launch_sh_scalars(const ShScalarDesc* d, int count, double eps, double eps_rel, int p,
                              hipStream_t st);
 hipError_t launch_sh_init(const ShInitDesc* d, int count, int total_tiles, hipStream_t st);
+// tiles: one upper 128 x 128 tile per workgroup, in launch order
+hipError_t launch_root(const RootDesc* d, const TileRef* tiles, int total_tiles, hipStream_t st);
+hipError_t launch_root_conv(const RootConvDesc* d, int count, int total_tiles, int dir, hipStream_t st);
 hipError_t launch_sh_apply(const ShApplyDesc* d, int count, int total_tiles, float decay, float step,
                            hipStream_t st);
 
