@@ -727,7 +727,7 @@ def main() -> int:
                    "weight_decay": hp.weight_decay, "lr_adjust": hp.lr_adjust,
                    "nominal_ns_flop_per_step": flops},
         "roofline": {
-            "kernel": GEMM_KERNEL if bf16_ns else "gemm_f32_kernel",
+            "kernel": GEMM_KERNEL if bf16_ns else "ns_h2_kernel",
             "bound": "mfma",
             "achieved": round(ns_tflops, 2),
             "peak": peak,

@@ -19,7 +19,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libmfsdp.so")
 SOURCES = ["mfsdp_host.cpp", "planner.cpp", "shampoo_host.cpp", "soap_host.cpp", "kernels_elementwise.hip",
-           "kernels_gemm.hip", "kernels_shampoo.hip", "kernels_root.hip", "kernels_soap.hip"]
+           "kernels_gemm.hip", "kernels_ns_h2.hip", "kernels_shampoo.hip", "kernels_root.hip", "kernels_soap.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

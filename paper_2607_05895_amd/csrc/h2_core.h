@@ -76,7 +76,7 @@ struct H2Core {
   static constexpr int DLOADS = PL + QL;
   static constexpr int STAGE = (PP + QP) * 1024;
   static constexpr int NMF = MI * NI, NRD = MI + NI;
-  static_assert(PP % NW == 0 && QP % NW == 0 && NMF >= NRD && 2 * NMF >= DLOADS, "schedule of a step");
+  static_assert(PP % NW == 0 && QP % NW == 0 && PL >= 1 && QL >= 1, "whole blocks per wave");
 
   // psrc[i] / qsrc[i]: this wave's i-th panel of P / Q (panel i NW + w) at k = 0, in 16-bit units, already
   // holding the lane's offset lane * 8.
@@ -125,8 +125,8 @@ struct H2Core {
       rd(smem + cs * STAGE, 1, pl, ql);
       mm(ph, qh);
 #pragma unroll
-      for (int i = 0; i < NMF; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      for (int i = 0; i < (NMF > NRD ? NMF : NRD); ++i) {
+        if (i < NMF) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         if (i < NRD) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
       // step kt + 1 has landed (later ones may be in flight); every wave is done with step kt - 1
@@ -138,8 +138,8 @@ struct H2Core {
       mm(pl, qh);
       mm(ph, ql);
 #pragma unroll
-      for (int i = 0; i < 2 * NMF; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      for (int i = 0; i < (2 * NMF > DLOADS ? 2 * NMF : DLOADS); ++i) {
+        if (i < 2 * NMF) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         if (i < DLOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         if (i < NRD) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
@@ -155,6 +155,39 @@ struct H2Core {
     // the clamped tail loads have landed and every wave is done reading: the LDS is free
     H2_WAIT_VMCNT(0);
     __builtin_amdgcn_s_barrier();
+  }
+};
+
+// Lane addressing of one 16 x 16 block's image (1 KiB) when a wave stores it with 16 bytes per lane: lane =
+// 32 plane + 16 chunk + row. off: the lane's 16 bytes of the image. t0, t1: the LDS addresses of the two 4 x 16
+// transposing reads whose results are the lane's 16 bytes of the transposed block (8 consecutive rows of
+// column `row`); lane 4 r + c of each 16 addresses row r (+ 4), columns 4 c .. 4 c + 3.
+struct H2BlockLane {
+  int row, ch, off, t0, t1;
+  __device__ __forceinline__ explicit H2BlockLane(int lane) {
+    const int plane = lane >> 5;
+    row = lane & 15;
+    ch = (lane >> 4) & 1;
+    off = plane * 512 + row * 32 + ((ch ^ h2_swz(row)) << 4);
+    const int c = lane & 3, r0 = 8 * ch + ((lane >> 2) & 3), r1 = r0 + 4;
+    t0 = plane * 512 + r0 * 32 + (((c >> 1) ^ h2_swz(r0)) << 4) + (c & 1) * 8;
+    t1 = plane * 512 + r1 * 32 + (((c >> 1) ^ h2_swz(r1)) << 4) + (c & 1) * 8;
+  }
+  __device__ __forceinline__ h2_u32x4 read(const h2_lds* blk) const { return *(const h2_lu4*)(blk + off); }
+  __device__ __forceinline__ h2_u32x4 read_t(h2_lds* blk) const {
+    const h2_s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((h2_ls4*)(blk + t0));
+    const h2_s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((h2_ls4*)(blk + t1));
+    return __builtin_bit_cast(h2_u32x4, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
+  // v with the elements below the block's diagonal taken from the transposed block's bytes tv
+  __device__ __forceinline__ h2_u32x4 mirror(h2_u32x4 v, h2_u32x4 tv) const {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int c = ch * 8 + 2 * k;
+      const uint32_t m = (c < row ? 0xffffu : 0u) | (c + 1 < row ? 0xffff0000u : 0u);
+      v[k] = (v[k] & ~m) | (tv[k] & m);
+    }
+    return v;
   }
 };
 

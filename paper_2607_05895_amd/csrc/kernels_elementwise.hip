@@ -112,7 +112,8 @@ __device__ __forceinline__ void store8(void* base, int64_t idx, const V8& x) {
 // gathers 8 consecutive tile rows 8 (t % 8) .. +7 of tile column t / 8 + 32 q and writes them as one
 // 16-B (bf16) vector, so 8 lanes cover 128 contiguous bytes of a transposed row. In LDS, element
 // (i, j) sits at column j ^ 8 ((i >> 3) & 7): the 16-B row writes stay contiguous and the 8-row
-// column gathers of a wave hit distinct banks.
+// column gathers of a wave hit distinct banks. The fp32 path writes u in the stored orientation only (the
+// split pass that follows the norm forms both layouts of X_0).
 // Non-temporal stores of the NS input u and u^T (they are read back from HBM by the first NS
 // products anyway: the iterate does not fit the caches at the sizes that matter).
 constexpr bool kPrepNtU = true;
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const PrepDesc* __restrict__ 
   constexpr int TW = PrepTraits<NSDT>::TW;
   constexpr int CPR = TW / 8;          // 8-column chunks per tile row
   constexpr int RPP = 256 / CPR;       // tile rows covered per pass
-  __shared__ __attribute__((aligned(16))) T tile[64 * TW];
+  __shared__ __attribute__((aligned(16))) T tile[NSDT == kDtBF16 ? 64 * TW : 1];
   __shared__ float red[4];
   const int e = find_entry(descs, count, blockIdx.x);
   const PrepDesc& d = descs[e];
@@ -152,18 +153,14 @@ __global__ __launch_bounds__(256) void prep_kernel(const PrepDesc* __restrict__ 
 #pragma unroll
     for (int k = 0; k < 8; ++k) ss += u.v[k] * u.v[k];
     store8<NSDT, kPrepNtU>(d.d_out, blk_index(i, j0, d.ld_d), u);
-    // LDS copy (rounded to the NS dtype exactly as the global one)
-    T* trow = tile + ti * TW + (c8 ^ (8 * ((ti >> 3) & 7)));
-    if constexpr (NSDT == kDtBF16) {
+    if constexpr (NSDT == kDtBF16) {  // LDS copy (rounded exactly as the global one)
+      T* trow = tile + ti * TW + (c8 ^ (8 * ((ti >> 3) & 7)));
       uint4 w;
       w.x = pack_bf16x2(u.v[0], u.v[1]);
       w.y = pack_bf16x2(u.v[2], u.v[3]);
       w.z = pack_bf16x2(u.v[4], u.v[5]);
       w.w = pack_bf16x2(u.v[6], u.v[7]);
       *reinterpret_cast<uint4*>(trow) = w;
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) trow[k] = u.v[k];
     }
   };
   if (vec && row0 + 64 <= m && col0 + TW <= n) {
@@ -284,35 +281,23 @@ __global__ __launch_bounds__(256) void prep_kernel(const PrepDesc* __restrict__ 
       emit(q, u);
     }
   }
-  __syncthreads();
-  // transposed copy: buffer row col0 + jj, columns row0 + 8 mm .. +7
-  {
+  if constexpr (NSDT == kDtBF16) {
+    // transposed copy: buffer row col0 + jj, columns row0 + 8 mm .. +7
+    __syncthreads();
     const int mm = t & 7;
 #pragma unroll
     for (int q = 0; q < TW / 32; ++q) {
       const int jj = (t >> 3) + 32 * q;
       T* dst = static_cast<T*>(d.t_out) + blk_index(col0 + jj, row0 + 8 * mm, d.ld_t);
-      if constexpr (NSDT == kDtBF16) {
-        uint32_t h[8];
+      uint32_t h[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int ti = 8 * mm + k;
-          h[k] = tile[ti * TW + (jj ^ (8 * ((ti >> 3) & 7)))];
-        }
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        st_stream<kPrepNtU>(reinterpret_cast<u32x4*>(dst),
-                            u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)});
-      } else {
-        float v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int ti = 8 * mm + k;
-          v[k] = tile[ti * TW + (jj ^ (8 * ((ti >> 3) & 7)))];
-        }
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        st_stream<kPrepNtU>(reinterpret_cast<f32x4*>(dst), f32x4{v[0], v[1], v[2], v[3]});
-        st_stream<kPrepNtU>(reinterpret_cast<f32x4*>(dst + 4), f32x4{v[4], v[5], v[6], v[7]});
+      for (int k = 0; k < 8; ++k) {
+        const int ti = 8 * mm + k;
+        h[k] = tile[ti * TW + (jj ^ (8 * ((ti >> 3) & 7)))];
       }
+      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+      st_stream<kPrepNtU>(reinterpret_cast<u32x4*>(dst),
+                          u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)});
     }
   }
   ss = wave_sum(ss);

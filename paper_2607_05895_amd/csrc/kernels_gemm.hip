@@ -1,4 +1,4 @@
-// Newton-Schulz products on gfx950.
+// Newton-Schulz products of the bf16 path on gfx950 (the fp32 path's are in kernels_ns_h2.hip).
 //
 // Every product of the quintic step is computed as one grouped "NT" GEMM
 //     C = alpha * P Q^T + beta * E        (P: M x K, Q: N x K, both K-contiguous, panel blocked)
@@ -6,13 +6,12 @@
 // (A = X X^T and B' = c A A + b A + a I) compute only the tiles on and above the diagonal and
 // store each off-diagonal tile twice (as is and transposed).
 //
-// bf16 path: a persistent grid of one workgroup per CU (8 waves) walks a host-built tile schedule
+// A persistent grid of one workgroup per CU (8 waves) walks a host-built tile schedule
 // (TileRef); each 256 x 256 output tile is 2 x 4 waves of 128 x 64, as 4 x 2 blocks of
 // v_mfma_f32_32x32x16_bf16 with fp32 accumulation. K advances 32 elements per step through a
 // five-stage LDS ring filled by direct global->LDS loads; the next tile's first loads overlap the
 // current tile's epilogue. The Gram and square products of a small share run the same kernel on
 // 128 x 128 tiles (2 x 2 waves of 64 x 64, two workgroups per CU), four times the tiles.
-// fp32 path: 64 x 64 tiles on the fp32 MFMA (v_mfma_f32_32x32x2f32).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -51,31 +50,6 @@ __device__ __forceinline__ float dpp_quad_xor1(float v) {
 }
 __device__ __forceinline__ float dpp_quad_xor2(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));
-}
-
-template <typename D>
-__device__ __forceinline__ int find_entry(const D* descs, int count, int key) {
-  int lo = 0, hi = count - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (descs[mid].tile_begin <= key) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
-// Map a problem-local tile index to (bi, bj): row-major over the full grid, or over the upper
-// triangle (bi <= bj) for symmetric products.
-__device__ __forceinline__ void tile_coords(const GemmDesc& d, int lt, int& bi, int& bj) {
-  if (d.sym) {
-    const int T = d.tiles_m;
-    int r = 0, rem = lt;
-    while (rem >= T - r) { rem -= T - r; ++r; }
-    bi = r;
-    bj = r + rem;
-  } else {
-    bi = lt / d.tiles_n;
-    bj = lt % d.tiles_n;
-  }
 }
 
 __device__ __forceinline__ float scale_pow(const float* s, int pw) {
@@ -826,117 +800,6 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const GemmDesc* __restric
   for (int k = 0; k < kSumSlab / 8; ++k) dst[k] = u32x4{w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]};
 }
 
-// fp32 NS products on fp32 MFMA. One 64 x 64 output tile per 256-thread workgroup: 4 waves of
-// 32 x 32 (v_mfma_f32_32x32x2f32), K steps of 32 double-buffered in LDS with the next step's 16-byte
-// global loads held in registers. The K index inside a step is permuted identically on both
-// operands (lane half h of MFMA q in group g takes k = 8 g + 4 h + q), so each lane reads its
-// fragments as 16-byte vectors; rows' eight 16-byte chunks are XOR-permuted by
-// (r & 7) ^ ((r >> 3) & 1) in LDS (conflict-free for 32 and 64 banks). The epilogue follows the
-// problem description: C = alpha P Q^T + beta E (+ the square's diagonal term), upper tiles of
-// symmetric products with mirrored stores, the transposed output CT; transposed stores go through
-// an LDS tile so that they are row-contiguous.
-__device__ __forceinline__ int f32_slot(int r, int chunk) {
-  return r * 8 + (chunk ^ ((r & 7) ^ ((r >> 3) & 1)));
-}
-
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmDesc* __restrict__ descs, int count,
-                                                       int parity, int first, int last, float ca,
-                                                       float cb, float cc) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  typedef float f32x16 __attribute__((ext_vector_type(16)));
-  typedef __attribute__((address_space(1))) float gf32;
-  typedef __attribute__((address_space(1))) const f32x4 gcf4;
-  __shared__ f32x4 lds[2][2][64 * 8];  // [stage][P, Q][slot]: 32 KiB
-  __shared__ float tt[64][65];          // transposition tile
-  const int e = find_entry(descs, count, blockIdx.x);
-  const GemmDesc& dd = descs[e];
-  const int lt = blockIdx.x - dd.tile_begin;
-  int bi, bj;
-  tile_coords(dd, lt, bi, bj);
-  const gf32* P = (const gf32*)dd.P[parity];
-  const gf32* Q = (const gf32*)dd.Q[parity];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int wr = w >> 1, wc = w & 1;
-  const int fr = lane & 31, fh = lane >> 5;
-  // global loads of one K step: the 64 x 32 slice of a panel-blocked operand is four 16 x 32 blocks
-  // (2 KiB each); float4 f = t + 256 j covers block f >> 7, row (f >> 3) & 15, chunk f & 7
-  const int64_t prow0 = int64_t(bi) * 64, qrow0 = int64_t(bj) * 64;
-  f32x4 ra[2], rb[2];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int f = t + 256 * j;
-      const int r = (f >> 7) * 16 + ((f >> 3) & 15), c = f & 7;
-      ra[j] = *(gcf4*)(P + blk_index(prow0 + r, k0 + 4 * c, dd.ldp));
-      rb[j] = *(gcf4*)(Q + blk_index(qrow0 + r, k0 + 4 * c, dd.ldq));
-    }
-  };
-  auto lstore = [&](int s) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int f = t + 256 * j;
-      const int slot = f32_slot((f >> 7) * 16 + ((f >> 3) & 15), f & 7);
-      lds[s][0][slot] = ra[j];
-      lds[s][1][slot] = rb[j];
-    }
-  };
-  f32x16 acc = f32x16{};
-  const int nk = dd.K / 32;
-  gload(0);
-  lstore(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int s = kt & 1;
-    if (kt + 1 < nk) gload((kt + 1) * 32);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x4 a = lds[s][0][f32_slot(wr * 32 + fr, 2 * g + fh)];
-      const f32x4 b = lds[s][1][f32_slot(wc * 32 + fr, 2 * g + fh)];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], acc, 0, 0, 0);
-    }
-    if (kt + 1 < nk) lstore(s ^ 1);
-    __syncthreads();
-  }
-  // the square product (the only one with an addend) takes this step's coefficients
-  const bool square = dd.E[parity] != nullptr;
-  const float alpha = square ? cc : dd.alpha * (first ? scale_pow(dd.scale, dd.alpha_scale_pow) : 1.0f);
-  const float beta = square ? cb : dd.beta * (first ? scale_pow(dd.scale, dd.beta_scale_pow) : 1.0f);
-  const float diag = (square && dd.sym && bi == bj) ? ca : 0.0f;
-  const gf32* E = (const gf32*)dd.E[parity];
-  gf32* C = (gf32*)dd.C[parity];
-  gf32* CT = (gf32*)dd.CT[parity];
-  if (last) {
-    if (!dd.last_c) C = nullptr;
-    if (!dd.last_ct) CT = nullptr;
-  }
-  const bool mirror = dd.sym && bi != bj && C;
-  // accumulator element v is tile row wr*32 + 8 (v / 4) + 4 h + v % 4, column wc*32 + lane % 32
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int i = wr * 32 + 8 * (v >> 2) + 4 * fh + (v & 3);
-    const int j = wc * 32 + fr;
-    const int64_t gi = prow0 + i, gj = qrow0 + j;
-    float x = alpha * acc[v];
-    if (E) x += beta * E[blk_index(gi, gj, dd.lde)];
-    if (gi == gj) x += diag;
-    if (C) C[blk_index(gi, gj, dd.ldc)] = x;
-    tt[i][j] = x;
-  }
-  if (mirror || CT) {
-    __syncthreads();
-    // transposed tile: row qrow0 + j, columns prow0 + i (i across lanes)
-    const int i = t & 63;
-#pragma unroll 4
-    for (int it = 0; it < 16; ++it) {
-      const int j = (t >> 6) + 4 * it;
-      const float x = tt[i][j];
-      if (mirror) C[blk_index(qrow0 + j, prow0 + i, dd.ldc)] = x;
-      if (CT) CT[blk_index(qrow0 + j, prow0 + i, dd.ldct)] = x;
-    }
-  }
-}
-
 }  // namespace
 
 template <int NW, int TB, int PK>
@@ -947,31 +810,27 @@ void launch_bf16(const GemmDesc* d_descs, const TileRef* d_sched, int ngroups, i
                      cb, cc);
 }
 
-hipError_t launch_gemm(const GemmDesc* d_descs, int count, int total_tiles, const TileRef* d_sched,
-                       int ngroups, int ns_dtype, int product, int parity, int first_step,
-                       int last_step, float ca, float cb, float cc, int tile, hipStream_t st) {
+hipError_t launch_gemm(const GemmDesc* d_descs, int total_tiles, const TileRef* d_sched, int ngroups, int product,
+                       int parity, int first_step, int last_step, float ca, float cb, float cc, int tile,
+                       hipStream_t st) {
   if (total_tiles <= 0) return hipSuccess;
-  if (ns_dtype == kDtBF16) {
-    constexpr int W = kGemmWaves;
-    constexpr int WS = kGemmWavesSmall, TS = kTileBF16Small;
-    if (tile == TS) {
-      if (product == kProdGram)
-        launch_bf16<WS, TS, kProdGram>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
-      else if (product == kProdSquare)
-        launch_bf16<WS, TS, kProdSquare>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
-      else
-        return hipErrorInvalidValue;
-    } else if (product == kProdGram)
-      launch_bf16<W, BT, kProdGram>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
+  constexpr int W = kGemmWaves;
+  constexpr int WS = kGemmWavesSmall, TS = kTileBF16Small;
+  if (tile == TS) {
+    if (product == kProdGram)
+      launch_bf16<WS, TS, kProdGram>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
     else if (product == kProdSquare)
-      launch_bf16<W, BT, kProdSquare>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
-    else if (product == kProdUpdate)
-      launch_bf16<W, BT, kProdUpdate>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
+      launch_bf16<WS, TS, kProdSquare>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
     else
-      launch_bf16<W, BT, kProdApply>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
-  } else
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3(total_tiles), dim3(256), 0, st, d_descs, count,
-                       parity, first_step, last_step, ca, cb, cc);
+      return hipErrorInvalidValue;
+  } else if (product == kProdGram)
+    launch_bf16<W, BT, kProdGram>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
+  else if (product == kProdSquare)
+    launch_bf16<W, BT, kProdSquare>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
+  else if (product == kProdUpdate)
+    launch_bf16<W, BT, kProdUpdate>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
+  else
+    launch_bf16<W, BT, kProdApply>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
   return hipGetLastError();
 }
 

@@ -105,14 +105,7 @@ __global__ __launch_bounds__(256, 2) void h2_root_kernel(const RootDesc* __restr
   const int wm = w / Core::WN, wn = w % Core::WN;
   const int fr = lane & 31, fh = lane >> 5;
   const int sw = h2_swz(fr & 15);
-  // Block stores: lane = 32 plane + 16 chunk + row holds 16 bytes of the block's image. The transposed
-  // block's same 16 bytes (8 consecutive tile rows of tile column `row`) come from two 4 x 16 transposing
-  // reads, whose lane 4 r + c of each 16 addresses row r, columns 4 c .. 4 c + 3.
-  const int row = lane & 15, ch = (lane >> 4) & 1, plane = lane >> 5;
-  const int doff = plane * 512 + row * 32 + ((ch ^ h2_swz(row)) << 4);
-  const int tr_r = (lane >> 2) & 3, tr_c = lane & 3;
-  auto toff = [&](int rr) { return plane * 512 + rr * 32 + (((tr_c >> 1) ^ h2_swz(rr)) << 4) + (tr_c & 1) * 8; };
-  const int t0 = toff(8 * ch + tr_r), t1 = toff(8 * ch + tr_r + 4);
+  const H2BlockLane bl(lane);
   float res = 0.0f;
   if (E) {
 #pragma unroll
@@ -173,20 +166,11 @@ __global__ __launch_bounds__(256, 2) void h2_root_kernel(const RootDesc* __restr
     const int b = i * 4 + w;
     const int rp = r0 + (b >> 3), cb = c0 + (b & 7);  // (uniform over the wave)
     if (rp > cb) continue;
-    h2_u32x4 v = *(h2_lu4*)(img + b * 1024 + doff);
-    const h2_s16x4 a0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((h2_ls4*)(img + b * 1024 + t0));
-    const h2_s16x4 a1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((h2_ls4*)(img + b * 1024 + t1));
-    const h2_u32x4 tv = __builtin_bit_cast(h2_u32x4, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
-    if (rp == cb) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int c = ch * 8 + 2 * k;
-        const uint32_t m = (c < row ? 0xffffu : 0u) | (c + 1 < row ? 0xffff0000u : 0u);
-        v[k] = (v[k] & ~m) | (tv[k] & m);
-      }
-    }
-    *(h2_gu4*)(C + rp * panel + int64_t(cb) * 512 + doff / 2) = v;
-    if (rp != cb) *(h2_gu4*)(C + cb * panel + int64_t(rp) * 512 + doff / 2) = tv;
+    h2_u32x4 v = bl.read(img + b * 1024);
+    const h2_u32x4 tv = bl.read_t(img + b * 1024);
+    if (rp == cb) v = bl.mirror(v, tv);
+    *(h2_gu4*)(C + rp * panel + int64_t(cb) * 512 + bl.off / 2) = v;
+    if (rp != cb) *(h2_gu4*)(C + cb * panel + int64_t(rp) * 512 + bl.off / 2) = tv;
   }
   if (d.resid_out) {
     // NaN propagates as the largest bit pattern, so a diverged side never counts as converged

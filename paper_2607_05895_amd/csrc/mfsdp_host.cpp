@@ -275,6 +275,44 @@ struct Plan {
   size_t bytes = 0;
 };
 
+// Output tile of a product of the fp32 path: 64 x 64 where 128 x 128 tiles would leave more than half of the
+// CUs without one.
+int h2_tile(const std::vector<NsPlan>& shapes, int phase) {
+  int64_t n = 0;
+  for (const NsPlan& p : shapes) {
+    const int64_t tr = (p.r_pad + 127) / 128, ts = (p.s_pad + 127) / 128;
+    n += phase == 2 ? tr * ts : tr * (tr + 1) / 2;
+  }
+  return n <= 128 ? 64 : 128;
+}
+
+// K ranges of the fp32 path's Gram tiles (in launch order): while the launch has fewer tiles than the chip
+// holds workgroups, the most ranges (at most 8, of whole pairs of K steps) that keep a range at least
+// 256 long and at least the launch's work per workgroup, and whose partial tiles fit the iterate's free
+// buffer (r_pad x s_pad fp32).
+std::vector<int> h2_splits(const std::vector<NsPlan>& shapes, const std::vector<int>& order, int tile) {
+  std::vector<int> f(order.size(), 1);
+  const int64_t slots = 512;
+  int64_t T = 0, W = 0;
+  auto tiles = [&](const NsPlan& p) {
+    const int64_t t = (p.r_pad + tile - 1) / tile;
+    return t * (t + 1) / 2;
+  };
+  for (const NsPlan& p : shapes) {
+    T += tiles(p);
+    W += tiles(p) * p.s_pad;
+  }
+  if (T >= slots) return f;
+  const int64_t target = std::max<int64_t>(256, W / slots);
+  for (size_t k = 0; k < order.size(); ++k) {
+    const NsPlan& p = shapes[size_t(order[k])];
+    for (int c = 2; c <= 8; ++c)
+      if ((p.s_pad / 32) % c == 0 && p.s_pad / c >= target && tiles(p) * c * tile * tile <= p.r_pad * p.s_pad)
+        f[k] = c;
+  }
+  return f;
+}
+
 // On the bf16 path a Gram launch with fewer tiles than the persistent grid has workgroups may split
 // long contractions (gram_splits); the split problems' partial tiles follow the per-matrix buffers
 // and take at most a quarter of their bytes. When the r x r products' 128 x 128 tiles fit one round
@@ -299,7 +337,7 @@ Plan make_plan(int64_t count, int ns_dtype, ShapeAt shape_at) {
   size_t sched_bytes[3] = {0, 0, 0};
   for (int ph = 0; ph < 3; ++ph) {
     const bool small = bf && ph < 2 && small_tiles <= small_slots;
-    const int tile = !bf ? kTileF32 : small ? kTileBF16Small : kTileBF16;
+    const int tile = !bf ? h2_tile(shapes, ph) : small ? kTileBF16Small : kTileBF16;
     P.tile[ph] = tile;
     P.order[ph] = phase_order(shapes, ph);
     std::vector<TileGrid> grids;
@@ -307,7 +345,7 @@ Plan make_plan(int64_t count, int ns_dtype, ShapeAt shape_at) {
     std::vector<int64_t> cost;
     for (int k = 0; k < int(count); ++k) {
       const NsPlan& p = shapes[P.order[ph][k]];
-      const int tr = int(p.r_pad / tile), ts = int(p.s_pad / tile);
+      const int tr = int((p.r_pad + tile - 1) / tile), ts = int((p.s_pad + tile - 1) / tile);
       const TileGrid g = ph == 2 ? TileGrid{tr, ts, false} : TileGrid{tr, tr, true};
       grids.push_back(g);
       pos.push_back(k);
@@ -326,7 +364,13 @@ Plan make_plan(int64_t count, int ns_dtype, ShapeAt shape_at) {
         P.split = gram_splits(tl, kl, int64_t(base / 4 / part_bytes),
                               small ? small_slots : int64_t(kGemmXcds) * kGemmSlots);
       }
-      for (int k = 0; k < int(count); ++k)
+      if (!bf) {
+        P.split = h2_splits(shapes, P.order[0], tile);
+        P.tiles[0] = 0;
+        for (size_t k = 0; k < grids.size(); ++k)
+          P.tiles[0] += grids[k].tm * (grids[k].tm + 1) / 2 * P.split[k];
+      }
+      for (int k = 0; bf && k < int(count); ++k)
         if (P.split[size_t(k)] > 1)
           for (int bi = 0; bi < grids[size_t(k)].tm; ++bi)
             for (int bj = bi; bj < grids[size_t(k)].tm; ++bj)
@@ -355,7 +399,7 @@ Plan make_plan(int64_t count, int ns_dtype, ShapeAt shape_at) {
   P.part.assign(size_t(count), 0);
   for (int k = 0; k < int(count); ++k) {
     const int f = P.split[size_t(k)];
-    if (f <= 1) continue;
+    if (f <= 1 || !bf) continue;
     const int64_t tr = shapes[size_t(P.order[0][size_t(k)])].r_pad / P.tile[0];
     P.part[size_t(k)] = o;
     o += align_up(size_t(tr * (tr + 1) / 2) * size_t(f) * P.tile[0] * P.tile[0] * sizeof(float));
@@ -375,9 +419,54 @@ std::vector<double> step_coeffs(double a, double b, double c, int steps, const d
   return v;
 }
 
-// On the bf16 path with at least one NS step the last update product applies the parameter update
-// in its epilogue (from the fp32 accumulators); otherwise a separate apply pass reads the iterate.
-bool apply_fused(int ns_dtype, int steps) { return ns_dtype == MFSDP_BF16 && steps >= 1; }
+// With at least one NS step the last update product applies the parameter update in its epilogue (from
+// the fp32 accumulators); otherwise a separate apply pass reads the iterate.
+bool apply_fused(int steps) { return steps >= 1; }
+
+// Scales of the fp32 path's split-fp16 buffers, step by step. Every buffer's elements are bounded by a bound
+// on its singular values: sigma of X (1 at first: the Frobenius norm), sigma^2 of A, max |a + b y + c y^2| over
+// [0, sigma^2] of B', max |x (a + b x^2 + c x^4)| over [0, sigma] of the next X (with 1 % for rounding). A
+// buffer's scale is the power of two that takes its bound to at most 2^14 (2^15 for X_0), a factor of
+// four (two) inside fp16's range.
+struct H2Scales {
+  double x, a, b, xn;
+};
+constexpr double kH2First = 32768.0;
+std::vector<H2Scales> h2_scales(const double* coeffs, int steps) {
+  auto pow2 = [](double bound) {
+    if (!(bound > 0.0) || !std::isfinite(bound)) return 1.0;
+    return std::exp2(std::min(100.0, std::max(-100.0, std::floor(14.0 - std::log2(bound)))));
+  };
+  std::vector<H2Scales> s;
+  double sigma = 1.0, sx = kH2First;
+  for (int k = 0; k < steps; ++k) {
+    const double a = coeffs[3 * k], b = coeffs[3 * k + 1], c = coeffs[3 * k + 2];
+    auto q = [&](double y) { return std::fabs(a + b * y + c * y * y); };
+    auto p = [&](double y) { return std::sqrt(y) * q(y); };
+    const double y1 = sigma * sigma;
+    double bb = std::max(q(0.0), q(y1)), bx = p(y1);
+    auto at = [&](double y) {
+      if (!(y > 0.0 && y < y1)) return;
+      bb = std::max(bb, q(y));
+      bx = std::max(bx, p(y));
+    };
+    if (c != 0.0) {
+      at(-b / (2.0 * c));
+      const double disc = 9.0 * b * b - 20.0 * a * c;  // a + 3 b y + 5 c y^2 = 0
+      if (disc >= 0.0) {
+        at((-3.0 * b + std::sqrt(disc)) / (10.0 * c));
+        at((-3.0 * b - std::sqrt(disc)) / (10.0 * c));
+      }
+    } else if (b != 0.0) {
+      at(-a / (3.0 * b));
+    }
+    sigma = 1.01 * bx;
+    H2Scales h{sx, pow2(y1), pow2(bb), pow2(sigma)};
+    sx = h.xn;
+    s.push_back(h);
+  }
+  return s;
+}
 
 // Descriptors of the three products, stored in the phase's problem order; the schedules refer
 // to problems by that position.
@@ -387,11 +476,12 @@ void fill_gemm_descs(const Plan& P, uint8_t* ws, const mfsdp_muon_hparams& hp, u
     const int tile = P.tile[phase];
     GemmDesc* out = reinterpret_cast<GemmDesc*>(h + P.dl.off_gemm[phase]);
     const std::vector<int>& ord = P.order[phase];
-    int begin = 0;
+    int begin = 0, sum_begin = 0;
     for (int k = 0; k < n; ++k) {
       const NsPlan& p = P.ns[ord[k]];
       GemmDesc d{};
-      const int tr = int(p.r_pad / tile), ts = int(p.s_pad / tile);
+      const int tr = int((p.r_pad + tile - 1) / tile), ts = int((p.s_pad + tile - 1) / tile);
+      const bool h2 = hp.ns_dtype == MFSDP_F32;
       for (int par = 0; par < 2; ++par) {
         uint8_t* xin = ws + p.off_x[par];
         uint8_t* xtin = ws + p.off_xt[par];
@@ -399,7 +489,7 @@ void fill_gemm_descs(const Plan& P, uint8_t* ws, const mfsdp_muon_hparams& hp, u
         uint8_t* xtout = ws + p.off_xt[par ^ 1];
         if (phase == 0) {         // A = X X^T
           d.P[par] = xin; d.Q[par] = xin; d.E[par] = nullptr;
-          d.C[par] = ws + p.off_g; d.CT[par] = nullptr;
+          d.C[par] = ws + p.off_g; d.CT[par] = h2 ? ws + p.off_x[par ^ 1] : nullptr;
         } else if (phase == 1) {  // B' = c A A + b A + a I
           d.P[par] = ws + p.off_g; d.Q[par] = ws + p.off_g; d.E[par] = ws + p.off_g;
           d.C[par] = ws + p.off_h; d.CT[par] = nullptr;
@@ -417,7 +507,12 @@ void fill_gemm_descs(const Plan& P, uint8_t* ws, const mfsdp_muon_hparams& hp, u
         d.tile_count = tr * (tr + 1) / 2;
         d.last_c = 1; d.last_ct = 0;
         d.nks = P.split[size_t(k)];
-        d.part = d.nks > 1 ? reinterpret_cast<float*>(ws + P.part[size_t(k)]) : nullptr;
+        d.part = d.nks > 1 && !h2 ? reinterpret_cast<float*>(ws + P.part[size_t(k)]) : nullptr;
+        if (h2) {
+          d.ldct = sum_begin;
+          sum_begin += d.tile_count * (tile / 16);
+          d.tile_count *= d.nks;
+        }
       } else if (phase == 1) {
         d.ldp = d.ldq = d.lde = d.ldc = p.r_pad; d.ldct = 0;
         d.M = d.N = d.K = int(p.r_pad);
@@ -435,7 +530,7 @@ void fill_gemm_descs(const Plan& P, uint8_t* ws, const mfsdp_muon_hparams& hp, u
         // the final iterate is read in the parameter's orientation only
         d.last_c = p.tall ? 0 : 1;
         d.last_ct = p.tall ? 1 : 0;
-        if (apply_fused(hp.ns_dtype, hp.ns_steps))
+        if (apply_fused(hp.ns_steps))
           d.fused = reinterpret_cast<const ApplyDesc*>(ws + P.dl.off_apply) + ord[k];
       }
       d.tile_begin = begin;
@@ -454,12 +549,14 @@ PrepDesc make_prep(const NsPlan& p, uint8_t* ws, const void* grad, int grad_dtyp
   PrepDesc d{};
   d.grad = grad;
   d.momentum = momentum;
-  // u in its stored orientation is X (wide) or X^T (tall); its transpose goes to the other one
+  // u in its stored orientation is X (wide) or X^T (tall); its transpose goes to the other one. On the fp32
+  // path u goes to the second buffer of the pair, from where the split pass forms X_0 in both layouts.
+  const int u = p.es == 4 ? 1 : 0;
   if (p.tall) {
-    d.d_out = ws + p.off_xt[0]; d.ld_d = p.r_pad;
+    d.d_out = ws + p.off_xt[u]; d.ld_d = p.r_pad;
     d.t_out = ws + p.off_x[0];  d.ld_t = p.s_pad;
   } else {
-    d.d_out = ws + p.off_x[0];  d.ld_d = p.s_pad;
+    d.d_out = ws + p.off_x[u];  d.ld_d = p.s_pad;
     d.t_out = ws + p.off_xt[0]; d.ld_t = p.r_pad;
   }
   d.partials = reinterpret_cast<float*>(ws + p.off_partials);
@@ -475,7 +572,8 @@ PrepDesc make_prep(const NsPlan& p, uint8_t* ws, const void* grad, int grad_dtyp
 ApplyDesc make_apply(const NsPlan& p, uint8_t* ws, int steps, void* param, int param_dtype,
                      float* update_out, int mode, float decay, float step, int tile_begin) {
   ApplyDesc d{};
-  const int par = steps & 1;  // parity of the buffer holding the final iterate
+  // the buffer holding the final iterate (read by the apply pass when there is no NS step)
+  const int par = p.es == 4 && steps == 0 ? 1 : steps & 1;
   if (p.tall) { d.o = ws + p.off_xt[par]; d.ld_o = p.r_pad; }
   else        { d.o = ws + p.off_x[par];  d.ld_o = p.s_pad; }
   d.param = param;
@@ -522,26 +620,51 @@ int enqueue_pipeline(const Plan& P, uint8_t* ws, int slot, int steps, const doub
   e = launch_norm(reinterpret_cast<const NormDesc*>(ws + dl.off_norm), count, float(eps), st);
   if (e != hipSuccess) return hip_fail(e, "norm launch");
   if ((rc = record(events, 1, st))) return rc;
-  for (int k = 0; k < steps; ++k) {
+  auto descs = [&](int ph) { return reinterpret_cast<const GemmDesc*>(ws + dl.off_gemm[ph]); };
+  if (ns_dtype == MFSDP_F32 && steps > 0) {
+    e = launch_ns_h2_split(reinterpret_cast<const PrepDesc*>(ws + dl.off_prep), count, prep_tiles, float(kH2First), st);
+    if (e != hipSuccess) return hip_fail(e, "split launch");
+    const std::vector<H2Scales> sc = h2_scales(coeffs, steps);
+    const bool split = std::any_of(P.split.begin(), P.split.end(), [](int f) { return f > 1; });
+    int sum_blocks = 0;
+    for (const NsPlan& p : P.ns) {
+      const int tr = int((p.r_pad + P.tile[0] - 1) / P.tile[0]);
+      sum_blocks += tr * (tr + 1) / 2 * (P.tile[0] / 16);
+    }
+    for (int k = 0; k < steps; ++k) {
+      const H2Scales& s = sc[size_t(k)];
+      const double* c = coeffs + 3 * k;
+      const int par = k & 1;
+      const bool last = k == steps - 1;
+      const float ga = float(s.a / (s.x * s.x));
+      e = launch_ns_h2(descs(0), count, P.tiles[0], 0, par, ga, 0.0f, 0.0f, P.tile[0], st);
+      if (e == hipSuccess && split) e = launch_ns_h2_sum(descs(0), count, sum_blocks, par, ga, P.tile[0], st);
+      if (e == hipSuccess)
+        e = launch_ns_h2(descs(1), count, P.tiles[1], 1, par, float(c[2] * s.b / (s.a * s.a)), float(c[1] * s.b / s.a),
+                         float(c[0] * s.b), P.tile[1], st);
+      if (e == hipSuccess)
+        e = launch_ns_h2(descs(2), count, P.tiles[2], last ? 3 : 2, par, float((last ? 1.0 : s.xn) / (s.b * s.x)), 0.0f,
+                         0.0f, P.tile[2], st);
+      if (e != hipSuccess) return hip_fail(e, "NS GEMM launch");
+    }
+  }
+  for (int k = 0; ns_dtype == MFSDP_BF16 && k < steps; ++k) {
     for (int ph = 0; ph < 3; ++ph) {
-      // the last update of the bf16 path applies the parameter update in its epilogue (kind 3)
-      const int kind = (ph == 2 && k == steps - 1 && apply_fused(ns_dtype, steps)) ? 3 : ph;
-      e = launch_gemm(reinterpret_cast<const GemmDesc*>(ws + dl.off_gemm[ph]), count, P.tiles[ph],
-                      reinterpret_cast<const TileRef*>(ws + dl.off_sched[ph]), dl.ngroups[ph],
-                      ns_dtype, kind, k & 1, k == 0 ? 1 : 0, k == steps - 1 ? 1 : 0,
-                      float(coeffs[3 * k]), float(coeffs[3 * k + 1]), float(coeffs[3 * k + 2]), P.tile[ph],
-                      st);
+      // the last update applies the parameter update in its epilogue (kind 3)
+      const int kind = ph == 2 && k == steps - 1 ? 3 : ph;
+      e = launch_gemm(descs(ph), P.tiles[ph], reinterpret_cast<const TileRef*>(ws + dl.off_sched[ph]), dl.ngroups[ph],
+                      kind, k & 1, k == 0 ? 1 : 0, k == steps - 1 ? 1 : 0, float(coeffs[3 * k]),
+                      float(coeffs[3 * k + 1]), float(coeffs[3 * k + 2]), P.tile[ph], st);
       if (e != hipSuccess) return hip_fail(e, "NS GEMM launch");
       if (ph == 0 && dl.njobs > 0) {
-        e = launch_gram_sum(reinterpret_cast<const GemmDesc*>(ws + dl.off_gemm[0]),
-                            reinterpret_cast<const TileRef*>(ws + dl.off_jobs), dl.njobs, k & 1,
+        e = launch_gram_sum(descs(0), reinterpret_cast<const TileRef*>(ws + dl.off_jobs), dl.njobs, k & 1,
                             k == 0 ? 1 : 0, P.tile[0], st);
         if (e != hipSuccess) return hip_fail(e, "split Gram sum launch");
       }
     }
   }
   if ((rc = record(events, 2, st))) return rc;
-  if (!apply_fused(ns_dtype, steps)) {
+  if (!apply_fused(steps)) {
     e = launch_apply(reinterpret_cast<const ApplyDesc*>(ws + dl.off_apply), count, apply_tiles,
                      ns_dtype, st);
     if (e != hipSuccess) return hip_fail(e, "apply launch");

@@ -56,7 +56,8 @@ struct PrepDesc {
   const void* grad;      // m x n, grad_dtype (the NS input for standalone NS); unused if nparts > 0
   float* momentum;       // m x n fp32, or null for standalone NS
   void* d_out;           // u in stored orientation, padded, panel blocked with ld_d columns
-  void* t_out;           // u^T, panel blocked with ld_t columns (ns dtype)
+  void* t_out;           // u^T, panel blocked with ld_t columns (fp32 path: X_0's other layout, which
+                         // the split pass writes)
   float* partials;       // one Sum u^2 per tile
   int64_t m, n;          // stored shape
   int64_t ld_d, ld_t;
@@ -113,13 +114,14 @@ struct GemmDesc {
   int32_t tile_begin;    // prefix over the problems of one launch
   int32_t tile_count;
   int32_t last_c, last_ct;  // on the last step: write C / CT (1) or skip (0)
-  // bf16 update product only: on the last step, apply the parameter update (or write the
-  // standalone NS output) from the fp32 accumulators instead of storing the final iterate
+  // update product: on the last step, apply the parameter update (or write the standalone NS
+  // output) from the fp32 accumulators instead of storing the final iterate
   const ApplyDesc* fused;
   // bf16 Gram product with a split contraction (nks > 1): tile (bi, bj, range ks) stores its fp32
   // partial product in part (one 256 x 256 row-major tile per upper tile and range, at
   // ((upper index of (bi, bj)) * nks + ks) * 65536 floats) and a second pass adds the ranges in
-  // order and stores A; 0 or 1: not split
+  // order and stores A; 0 or 1: not split. (On the fp32 path the partials go to CT, the iterate's
+  // other buffer, which is free then, and ldct is the problem's first block in the second pass.)
   float* part;
   int32_t nks;
 };
@@ -154,14 +156,23 @@ constexpr int kAdamWBlockElems = 2048;
 hipError_t launch_prep(const PrepDesc* d_descs, int count, int total_tiles, int ns_dtype,
                        int reduce, float beta, float one_minus_beta, int nesterov, hipStream_t st);
 hipError_t launch_norm(const NormDesc* d_descs, int count, float eps, hipStream_t st);
-// product: 0 Gram, 1 square, 2 update (the order of the products in one NS step); 3 the last update
-// of the bf16 path with the fused parameter update (its descriptors carry `fused`)
+// product: 0 Gram, 1 square, 2 update (the order of the products in one NS step); 3 the last update with
+// the fused parameter update (its descriptors carry `fused`)
 // (ca, cb, cc): the NS step's coefficients (a_k, b_k, c_k), used by the square product.
-// tile: the bf16 path's output tile, kTileBF16 or (Gram and square products only) kTileBF16Small;
-// the descriptors' tile grids and the schedule are in that tile.
-hipError_t launch_gemm(const GemmDesc* d_descs, int count, int total_tiles, const TileRef* d_sched,
-                       int ngroups, int ns_dtype, int product, int parity, int first_step,
-                       int last_step, float ca, float cb, float cc, int tile, hipStream_t st);
+// tile: the output tile, kTileBF16 or (Gram and square products only) kTileBF16Small; the descriptors'
+// tile grids and the schedule are in that tile.
+hipError_t launch_gemm(const GemmDesc* d_descs, int total_tiles, const TileRef* d_sched, int ngroups, int product,
+                       int parity, int first_step, int last_step, float ca, float cb, float cc, int tile,
+                       hipStream_t st);
+// The fp32 path's products (on split fp16): one workgroup per tile (and K range) in the order of the
+// descriptors; alpha, beta and diag take in the operands' scales. tile: 128 or 64.
+hipError_t launch_ns_h2(const GemmDesc* d, int count, int total_tiles, int product, int parity, float alpha,
+                        float beta, float diag, int tile, hipStream_t st);
+// Second pass of a split Gram product there (blocks: tile / 16 per upper tile of every problem).
+hipError_t launch_ns_h2_sum(const GemmDesc* d, int count, int blocks, int parity, float alpha, int tile,
+                            hipStream_t st);
+// X_0 = s0 scale u in both layouts from the momentum pass's u.
+hipError_t launch_ns_h2_split(const PrepDesc* d, int count, int total_tiles, float s0, hipStream_t st);
 hipError_t launch_apply(const ApplyDesc* d_descs, int count, int total_tiles, int ns_dtype,
                         hipStream_t st);
 // The second pass of a split Gram product: for each job (problem e in the Gram launch's order,
@@ -176,6 +187,7 @@ constexpr int kTileBF16 = 256;
 // The bf16 Gram and square products of a launch with few 256 x 256 tiles run on 128 x 128 tiles,
 // two workgroups per CU (the padding stays 256).
 constexpr int kTileBF16Small = 128;
+// The fp32 path pads to 64; its products run on 128 x 128 or 64 x 64 tiles, which may reach past the padding.
 constexpr int kTileF32 = 64;
 constexpr int kPrepRows = 64;                    // prep tile rows
 constexpr int kPrepColsBF16 = 256;              // prep tile columns on the bf16 path (divides 256)

@@ -84,6 +84,28 @@ def test_ns_f32_matches_oracle(native, shape, steps):
     assert err <= 1e-4, err
 
 
+@pytest.mark.parametrize("shape", [(64, 64), (63, 2111), (2111, 65), (128, 640), (192, 4100), (1300, 1411), (1411, 1300)])
+@pytest.mark.parametrize("coeffs", ["quintic", "cubic", "wide"])
+def test_ns_f32_tile_edges(native, shape, coeffs):
+    """The fp32 path on both its tile sizes, with and without K ranges, past the last panel, with rows that
+    are not whole 16-byte slots, and under coefficients with other bounds on the buffers (zero c; singular
+    values up to 2.6). Bound: each of the 3 products of a step sums K / 16 times 3 roundings of 2^-25, random
+    in sign, and a later step multiplies an error by at most its polynomial's slope at 0 (or 3)."""
+    import torch
+    m, n = shape
+    a, b, c = {"quintic": (A, B, C), "cubic": (1.5, -0.5, 0.0), "wide": (2.5, -0.25, 0.01)}[coeffs]
+    steps = 5 if coeffs == "quintic" else 3
+    _say(f"ns f32 {m}x{n} {coeffs}")
+    rng = np.random.default_rng(900 + m + n)
+    x = rng.standard_normal((m, n), dtype=np.float32)
+    out = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    native.newton_schulz_t(to_dev(x, synth.F32), out, a, b, c, steps, 1e-7, "f32")
+    _sync()
+    err = rel_fro(from_dev(out), oracle.newton_schulz(x, a, b, c, steps))
+    tol = 3 * steps * np.sqrt(3 * max(m, n) / 16 + 6) * 2.0 ** -25 * 3.5
+    assert err <= tol, (err, tol)
+
+
 def test_ns_bf16_single_step_exact_products(native):
     # one NS step is a fixed polynomial of X0: checks the MFMA fragment/output layout and the
     # symmetric-tile mirroring on a matrix with several tiles per side
