@@ -1,14 +1,12 @@
 // Split-fp16 operands ("h2") and the MFMA main loop over them: fp32-accurate products at a third of the
 // fp16 matrix rate.
 //
-// An fp32 value x, scaled by a power of two s so that |x s| stays below 2^16, is held as two fp16 numbers,
-// hi = fp16(x s) and lo = fp16(x s - hi): 22 to 23 significant bits down to 2^-17 of the buffer's bound,
-// and an absolute error of at most 2^-40 of that bound below. A product of two such operands takes
-// three fp16 MFMAs per 16 k (lo.hi, hi.lo, hi.hi; lo.lo is below 2^-22 of |x||y|, random in sign). With
-// half as many roundings of the fp32 accumulator as the six products of a three-way bf16 split
-// (v_mfma_f32_32x32x16_bf16) the error against 64 bits is smaller from K = 64 on (normal operands,
-// relative 2-norm: K = 128 1.44e-7 against 1.67e-7, 768 3.0e-7 against 3.9e-7, 4096 6.9e-7 against 1.05e-6;
-// fp32 MFMA: 1.9e-7, 4.9e-7, 1.15e-6).
+// An fp32 value x, scaled by a power of two s so that |x s| stays below 2^15, is held as two fp16 numbers,
+// hi = fp16(x s) and lo = fp16(2^11 (x s - hi)): 22 to 23 significant bits down to 2^-28 of the buffer's
+// bound, and an absolute error of at most 2^-51 of it below. A product of two such operands takes three fp16
+// MFMAs per 16 k: hi.hi into one accumulator, lo.hi and hi.lo into another that is added at the end times
+// 2^-11 (lo.lo is below 2^-22 of |x||y|, random in sign). The main accumulator is rounded a sixth as often as
+// with the six products of a three-way bf16 split, so the error against 64 bits is smaller from K = 64 on.
 //
 // Layout of an R x K operand (K a multiple of 16, rows padded to 16): 16 x 16 blocks of 1 KiB, the blocks
 // of a 16-row panel one after another along K; a block is its 512-byte plane of hi parts and then the
@@ -47,17 +45,19 @@ typedef __attribute__((address_space(3))) h2_u32x2 h2_lu2;
 typedef __attribute__((address_space(3))) h2_u32x4 h2_lu4;
 typedef __attribute__((address_space(3))) h2_s16x4 h2_ls4;
 
+constexpr float kH2LoScale = 2048.0f;
 // The two parts of two scaled values, packed (first value in the low half); round to nearest even.
 __device__ __forceinline__ void h2_split2(float a, float b, uint32_t& hi, uint32_t& lo) {
   const h2_f16x2 h = __builtin_convertvector(h2_f32x2{a, b}, h2_f16x2);
   hi = __builtin_bit_cast(uint32_t, h);
-  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(h2_f32x2{a - float(h.x), b - float(h.y)}, h2_f16x2));
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(h2_f32x2{kH2LoScale * (a - float(h.x)), kH2LoScale * (b - float(h.y))},
+                                                         h2_f16x2));
 }
 // The two (scaled) values of packed parts.
 __device__ __forceinline__ void h2_join2(uint32_t hi, uint32_t lo, float& a, float& b) {
   const h2_f16x2 h = __builtin_bit_cast(h2_f16x2, hi), l = __builtin_bit_cast(h2_f16x2, lo);
-  a = float(h.x) + float(l.x);
-  b = float(h.y) + float(l.y);
+  a = float(h.x) + (1.0f / kH2LoScale) * float(l.x);
+  b = float(h.y) + (1.0f / kH2LoScale) * float(l.y);
 }
 
 // s_waitcnt with only vmcnt constrained; with only lgkmcnt(0)
@@ -91,7 +91,7 @@ struct H2Core {
                                        16, 0, 0);
   }
 
-  // The products of nk steps (even, >= 2) added into acc. One barrier per step, between its hi.hi and its
+  // The products of nk steps (even, >= 2) into acc (zero on entry). One barrier per step, between its hi.hi and its
   // two mixed products: before it a wave waits for its own loads of step kt + 1, after it the loads of step
   // kt + NST - 1 go into the stage of step kt - 1, whose fragments every wave has consumed, and the next
   // step's hi parts are read while the mixed products run.
@@ -113,17 +113,22 @@ struct H2Core {
 #pragma unroll
       for (int i = 0; i < NI; ++i) qf[i] = *reinterpret_cast<const h2_f16x8*>(sb + qbase + i * 2048 + part * 512);
     };
-    auto mm = [&](const h2_f16x8 (&pf)[MI], const h2_f16x8 (&qf)[NI]) {
+    auto mm = [&](h2_f32x16 (&c)[MI][NI], const h2_f16x8 (&pf)[MI], const h2_f16x8 (&qf)[NI]) {
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(qf[j], pf[i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NI; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(qf[j], pf[i], c[i][j], 0, 0, 0);
     };
+    h2_f32x16 mix[MI][NI];  // 2^11 times the mixed products
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) mix[i][j] = h2_f32x16{};
     int cs = 0, ns = 1, fs = NST - 1;
     auto step = [&](int kt, h2_f16x8 (&ph)[MI], h2_f16x8 (&qh)[NI], h2_f16x8 (&phn)[MI], h2_f16x8 (&qhn)[NI]) {
       // the lo parts of this step are read while hi.hi multiplies
       rd(smem + cs * STAGE, 1, pl, ql);
-      mm(ph, qh);
+      mm(acc, ph, qh);
 #pragma unroll
       for (int i = 0; i < (NMF > NRD ? NMF : NRD); ++i) {
         if (i < NMF) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -135,8 +140,8 @@ struct H2Core {
       const int kl = kt + NST - 1;
       issue(psrc, qsrc, kl < nk ? kl : nk - 1, (h2_lds*)(smem + fs * STAGE), w);
       rd(smem + ns * STAGE, 0, phn, qhn);
-      mm(pl, qh);
-      mm(ph, ql);
+      mm(mix, pl, qh);
+      mm(mix, ph, ql);
 #pragma unroll
       for (int i = 0; i < (2 * NMF > DLOADS ? 2 * NMF : DLOADS); ++i) {
         if (i < 2 * NMF) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -152,6 +157,10 @@ struct H2Core {
       step(kt, ph0, qh0, ph1, qh1);
       step(kt + 1, ph1, qh1, ph0, qh0);
     }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[i][j] += (1.0f / kH2LoScale) * mix[i][j];
     // the clamped tail loads have landed and every wave is done reading: the LDS is free
     H2_WAIT_VMCNT(0);
     __builtin_amdgcn_s_barrier();

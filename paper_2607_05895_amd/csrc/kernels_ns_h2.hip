@@ -78,7 +78,7 @@ struct ParamWords {
 // 64 KiB), two workgroups per CU. Bound by the matrix pipe and operand loads at large sizes (2048 x 8192, five
 // steps: 1.95 ms, 318 TFLOP/s of the 3 r^2 s + r^3 fp32 flop; the fp32 MFMA kernel before it 6.18 ms) and by
 // launches and the serial K loop at small ones (256 x 512: 239 -> 112 us; seven 768/3072/1024x4096 matrices
-// 2.20 -> 0.84 ms). Errors against 64 bits after five steps: 768 x 768 2.7e-6 -> 1.8e-6, 2048 x 8192 4.8e-6 -> 2.8e-6.
+// 2.20 -> 0.84 ms). Errors against 64 bits after five steps: 768 x 768 2.7e-6 -> 1.1e-6, 2048 x 8192 4.8e-6 -> 1.5e-6.
 // PK: the product; its epilogue is
 //   Gram, square  C (upper tiles, mirrored; stored exactly symmetric), the square with the addend E = A and a I
 //   Gram, split   the fp32 partial tile of K range ks into CT (the iterate's other buffer, free here)
