@@ -275,9 +275,10 @@ size_t mfsdp_shampoo_workspace_size(const mfsdp_shampoo_entry* entries, int64_t 
 
 /* One Shampoo step on every entry (host array of count entries), enqueued on `stream`
  * (hipStream_t, NULL = default stream); no host synchronisation. Statistics update, inverse
- * fourth roots (on refresh), U = P_L G P_R, every product at fp32 accuracy on the bf16 MFMA
- * (each fp32 operand split exactly into three bf16 parts, fp32 accumulation), then the parameter
- * update. The workspace (device, 256-byte aligned, >= the size query) must not be in use by
+ * fourth roots (on refresh), U = P_L G P_R and the parameter update, every product at fp32 accuracy
+ * on the 16-bit MFMA (each fp32 operand split into two scaled fp16 parts, fp32 accumulation; products
+ * of a bf16 gradient with itself in bf16). With stored preconditioners part of the work may run on the
+ * auxiliary stream that mfsdp_soap_step describes, joined before the call returns. The workspace (device, 256-byte aligned, >= the size query) must not be in use by
  * another call still running. Returns MFSDP_OK, MFSDP_E_INVALID, MFSDP_E_WORKSPACE or
  * MFSDP_E_HIP; on an argument error nothing is enqueued. At most 4096 entries per call. */
 int mfsdp_shampoo_step(const mfsdp_shampoo_entry* entries, int64_t count,
@@ -372,7 +373,8 @@ size_t mfsdp_soap_workspace_size(const mfsdp_soap_entry* entries, int64_t count,
 
 /* One SOAP step on every entry (host array of count entries), enqueued on `stream` (hipStream_t,
  * NULL = default stream); no host synchronisation. Every product runs at fp32 accuracy on the
- * bf16 MFMA as in mfsdp_shampoo_step (grouped over the entries); the refresh QR is a blocked
+ * 16-bit MFMA as in mfsdp_shampoo_step (grouped over the entries; in the refresh QR each fp32 operand is
+ * split into three bf16 parts); the refresh QR is a blocked
  * Householder factorization (16-column panels in 128-column blocks whose updates run on the same
  * GEMM). Part of each block update runs on a library-owned auxiliary stream of the current device
  * (default priority, created on first use, kept until the process ends), forked from `stream` and

@@ -32,48 +32,6 @@ __device__ __forceinline__ int find_entry(const D* descs, int count, int key) {
 
 constexpr int kGram = 0, kSquare = 1, kUpdate = 2, kApply = 3;
 
-// The parameter update p <- p decay - step O (mode 0) or the output p <- O (mode 1), for V = 1 or 4 consecutive
-// elements (4: 8 or 16-byte aligned): the old values' words are loaded first, long before O is there.
-template <int V>
-struct ParamWords {
-  uint32_t w[V];
-  __device__ __forceinline__ void load(const ApplyDesc& a, int64_t i) {
-    if (a.param_dtype == kDtBF16) {
-      if constexpr (V == 4) {
-        const h2_u32x2 x = *(const h2_gu2*)((const h2_gu16*)a.param + i);
-        w[0] = x.x << 16;
-        w[1] = x.x & 0xffff0000u;
-        w[2] = x.y << 16;
-        w[3] = x.y & 0xffff0000u;
-      } else {
-        w[0] = uint32_t(((const h2_gu16*)a.param)[i]) << 16;
-      }
-    } else if constexpr (V == 4) {
-      const h2_u32x4 x = *(const h2_gu4*)((const g_f32*)a.param + i);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) w[k] = x[k];
-    } else {
-      w[0] = ((__attribute__((address_space(1))) const uint32_t*)a.param)[i];
-    }
-  }
-  __device__ __forceinline__ void apply(const ApplyDesc& a, int64_t i, const float (&o)[V]) const {
-    float r[V];
-#pragma unroll
-    for (int k = 0; k < V; ++k) r[k] = a.mode == 0 ? __uint_as_float(w[k]) * a.decay - a.step * o[k] : o[k];
-    if constexpr (V == 4) {
-      if (a.update_out) *(g_f32x4*)((g_f32*)a.update_out + i) = f32x4{o[0], o[1], o[2], o[3]};
-      if (a.param_dtype == kDtBF16)
-        *(h2_gu2*)((h2_gu16*)a.param + i) = h2_u32x2{pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
-      else
-        *(g_f32x4*)((g_f32*)a.param + i) = f32x4{r[0], r[1], r[2], r[3]};
-    } else {
-      if (a.update_out) ((g_f32*)a.update_out)[i] = o[0];
-      if (a.param_dtype == kDtBF16) ((h2_gu16*)a.param)[i] = uint16_t(pack_bf16x2(r[0], 0.0f));
-      else ((g_f32*)a.param)[i] = r[0];
-    }
-  }
-};
-
 // One tile of one product per workgroup, 128 x 128 (4 waves of 64 x 64, 80 KiB of LDS) or 64 x 64 (32 x 32,
 // 64 KiB), two workgroups per CU. Bound by the matrix pipe and operand loads at large sizes (2048 x 8192, five
 // steps: 1.95 ms, 318 TFLOP/s of the 3 r^2 s + r^3 fp32 flop; the fp32 MFMA kernel before it 6.18 ms) and by
@@ -162,6 +120,15 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
     constexpr int SL = T / 4;  // slots per row
     auto at = [&](int r, int c) { return r * (T * 4) + (((c >> 2) ^ (r & (SL - 1))) << 4) + (c & 3) * 4; };
     const int64_t pr0 = int64_t(tall ? bj : bi) * T, pc0 = int64_t(tall ? bi : bj) * T;
+    // (mode 1, the standalone output: p <- O, the words are not used)
+    auto put = [&](const ParamWords<4>& p, int64_t i, const float (&o)[4]) {
+      if (a.mode == 0) p.store(a.param, a.param_dtype, a.update_out, i, a.decay, a.step, o);
+      else ParamWords<4>::write(a.param, a.param_dtype, i, o);
+    };
+    auto put1 = [&](const ParamWords<1>& p, int64_t i, const float (&o)[1]) {
+      if (a.mode == 0) p.store(a.param, a.param_dtype, a.update_out, i, a.decay, a.step, o);
+      else ParamWords<1>::write(a.param, a.param_dtype, i, o);
+    };
     auto exchange = [&] {
 #pragma unroll
       for (int i = 0; i < Core::MI; ++i)
@@ -188,13 +155,13 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
       const bool in = pc0 + c < a.n;
 #pragma unroll
       for (int it = 0; it < NIT; ++it)
-        if (a.mode == 0 && in && pr0 + row(it) < a.m) pw[it].load(a, (pr0 + row(it)) * a.n + pc0 + c);
+        if (a.mode == 0 && in && pr0 + row(it) < a.m) pw[it].load(a.param, a.param_dtype, (pr0 + row(it)) * a.n + pc0 + c);
       exchange();
 #pragma unroll
       for (int it = 0; it < NIT; ++it)
         if (in && pr0 + row(it) < a.m) {
           const f32x4 o = *(l_f32x4*)(img + at(row(it), c));
-          pw[it].apply(a, (pr0 + row(it)) * a.n + pc0 + c, {o[0], o[1], o[2], o[3]});
+          put(pw[it], (pr0 + row(it)) * a.n + pc0 + c, {o[0], o[1], o[2], o[3]});
         }
     } else {
       constexpr int CP = T / 64, NIT = T / 4 * CP;  // column passes, passes
@@ -204,12 +171,12 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
 #pragma unroll
       for (int it = 0; it < NIT; ++it)
         if (a.mode == 0 && pr0 + row(it) < a.m && pc0 + col(it) < a.n)
-          pw[it].load(a, (pr0 + row(it)) * a.n + pc0 + col(it));
+          pw[it].load(a.param, a.param_dtype, (pr0 + row(it)) * a.n + pc0 + col(it));
       exchange();
 #pragma unroll
       for (int it = 0; it < NIT; ++it)
         if (pr0 + row(it) < a.m && pc0 + col(it) < a.n)
-          pw[it].apply(a, (pr0 + row(it)) * a.n + pc0 + col(it), {*(l_f32*)(img + at(row(it), col(it)))});
+          put1(pw[it], (pr0 + row(it)) * a.n + pc0 + col(it), {*(l_f32*)(img + at(row(it), col(it)))});
     }
     return;
   } else {

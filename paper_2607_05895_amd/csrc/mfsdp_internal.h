@@ -47,6 +47,75 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 constexpr int kDtF32 = 0;
 constexpr int kDtBF16 = 1;
 
+// The largest of the workgroup's values (bit patterns of |x|: NaN above infinity) into a slot. Every thread
+// calls it. One atomic per workgroup, and only when it raises the slot (tens of thousands of workgroups of
+// an elementwise pass share one slot).
+__device__ __forceinline__ void slot_max(uint32_t* slot, uint32_t big) {
+  __shared__ uint32_t red[16];
+  for (int o = 32; o > 0; o >>= 1) big = max(big, uint32_t(__shfl_xor(int(big), o)));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = big;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (unsigned w = 1; w < blockDim.x >> 6; ++w) big = max(big, red[w]);
+    if (big > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(slot, big);
+  }
+  __syncthreads();
+}
+
+// A parameter update p <- p decay - step O of V = 1 or 4 consecutive elements (4: 8-byte aligned in bf16, 16 in
+// fp32; update_out, if any, 16), in two halves: the old words are loaded long before O is there.
+template <int V>
+struct ParamWords {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  template <typename T>
+  using gptr = __attribute__((address_space(1))) T*;
+  uint32_t w[V];  // fp32 bits
+  __device__ __forceinline__ void load(const void* param, int dt, int64_t i) {
+    if (dt == kDtBF16) {
+      const gptr<const uint16_t> p = (gptr<const uint16_t>)param + i;
+      if constexpr (V == 4) {
+        const u32x2 x = *(gptr<const u32x2>)p;
+        w[0] = x.x << 16;
+        w[1] = x.x & 0xffff0000u;
+        w[2] = x.y << 16;
+        w[3] = x.y & 0xffff0000u;
+      } else {
+        w[0] = uint32_t(*p) << 16;
+      }
+    } else {
+      const gptr<const uint32_t> p = (gptr<const uint32_t>)param + i;
+      if constexpr (V == 4) {
+        const u32x4 x = *(gptr<const u32x4>)p;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[k] = x[k];
+      } else {
+        w[0] = *p;
+      }
+    }
+  }
+  static __device__ __forceinline__ void write(void* param, int dt, int64_t i, const float (&r)[V]) {
+    if (dt == kDtBF16) {
+      const gptr<uint16_t> p = (gptr<uint16_t>)param + i;
+      if constexpr (V == 4) *(gptr<u32x2>)p = u32x2{pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
+      else *p = uint16_t(pack_bf16x2(r[0], 0.0f));
+    } else {
+      const gptr<uint32_t> p = (gptr<uint32_t>)param + i;
+      if constexpr (V == 4)
+        *(gptr<u32x4>)p = u32x4{__float_as_uint(r[0]), __float_as_uint(r[1]), __float_as_uint(r[2]), __float_as_uint(r[3])};
+      else *p = __float_as_uint(r[0]);
+    }
+  }
+  __device__ __forceinline__ void store(void* param, int dt, float* update_out, int64_t i, float decay, float step,
+                                        const float (&o)[V]) const {
+    float r[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) r[k] = __uint_as_float(w[k]) * decay - step * o[k];
+    if (update_out) write(update_out, kDtF32, i, o);
+    write(param, dt, i, r);
+  }
+};
+
 // ---------------------------------------------------------------------------------------------
 // prep: momentum EMA + Nesterov (or a plain copy for standalone NS), Sum u^2 partials, and the
 // NS input written in both layouts. One 64 x 64 tile of the stored m x n matrix per workgroup.

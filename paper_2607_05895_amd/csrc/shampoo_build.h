@@ -46,7 +46,7 @@ struct Arena {
 };
 
 enum OpKind {
-  kOpCopyIn, kOpCopyOut, kOpGemm, kOpNorm, kOpScalars, kOpInit, kOpApply,
+  kOpCopyIn, kOpCopyOut, kOpGemm, kOpGemmX3, kOpGemmB, kOpGemmP2B, kOpMax, kOpNorm, kOpScalars, kOpInit, kOpApply,
   kOpRoot, kOpRootIn, kOpRootOut,
   kOpSoapPrep, kOpSoapAdam, kOpEye, kOpQrPanel, kOpQrCol, kOpQrT,
   kOpFork,  // the auxiliary stream waits for everything enqueued so far on the caller's stream
@@ -84,6 +84,14 @@ struct Build {
     std::memcpy(h.data() + o, v.data(), v.size() * sizeof(T));
     return o;
   }
+  // Slots for the largest |element| of a buffer (bit patterns), in the descriptor region, so that the
+  // upload clears them. reserve_slots comes first; desc_at: the region's offset in the workspace.
+  size_t desc_at = 0, slots = 0;
+  void reserve_slots(size_t region, size_t n) {
+    desc_at = region;
+    slots = put(std::vector<uint32_t>(n, 0u));
+  }
+  uint32_t* slot(size_t i) const { return ptr<uint32_t>(desc_at + slots) + i; }
   int aux = 0;  // stream of the ops added next
   template <class T>
   void op(OpKind k, const std::vector<T>& v, int total) {
@@ -169,7 +177,15 @@ inline int run(Build& b, char* ws, size_t desc_at, hipStream_t main_st, const Ru
     switch (o.kind) {
       case kOpCopyIn: e = launch_sh_copy(reinterpret_cast<ShCopyDesc*>(dp), o.count, o.total, 0, st); break;
       case kOpCopyOut: e = launch_sh_copy(reinterpret_cast<ShCopyDesc*>(dp), o.count, o.total, 1, st); break;
-      case kOpGemm: e = launch_sh_gemm(reinterpret_cast<ShGemmDesc*>(dp), o.count, o.total, st); break;
+      case kOpGemm:
+      case kOpGemmX3:
+      case kOpGemmB:
+      case kOpGemmP2B:
+        e = launch_sh_gemm(reinterpret_cast<ShGemmDesc*>(dp), o.count, o.total,
+                           o.kind == kOpGemmX3 ? kShX3 : o.kind == kOpGemmB ? kShB : o.kind == kOpGemmP2B ? kShP2B : kShScaled,
+                           s.decay, s.step, st);
+        break;
+      case kOpMax: e = launch_sh_max(reinterpret_cast<ShMaxDesc*>(dp), o.count, o.total, st); break;
       case kOpRoot:
         e = launch_root(reinterpret_cast<RootDesc*>(dp), reinterpret_cast<TileRef*>(ws + desc_at + o.tiles_off),
                         o.total, st);

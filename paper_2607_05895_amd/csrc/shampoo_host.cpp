@@ -50,6 +50,7 @@ struct Side {
   size_t M = 0, T2 = 0, T4 = 0, X[2] = {0, 0}, partials = 0, sc = 0, resid = 0, xsel = 0;
   const float* S = nullptr;
   float* out = nullptr;  // caller destination of the root (d x d, row stride d)
+  uint32_t* amax = nullptr;  // slot that receives the root's largest element
   bool has_out = false;  // copy the root out (decided by the call, not by the pointer value,
                          // so that the size query, which sees no pointers, builds the same ops)
   // the fourth root in the padded fp32 layout: the caller's buffer when the side works in place
@@ -138,9 +139,9 @@ int add_newton_products(Build& b, const std::vector<Side*>& sides, int p, int it
   for (int k = 0; k < iters; ++k) {
     const int q = k & 1;
     const bool last = k == iters - 1;
-    b.ops.push_back(Op{kOpGemm, o1[q], last ? ns : int(l1[q].size()), last ? t1x[q] : t1[q]});
+    b.ops.push_back(Op{kOpGemmX3, o1[q], last ? ns : int(l1[q].size()), last ? t1x[q] : t1[q]});
     if (last) break;
-    if (!l3[q].empty()) b.ops.push_back(Op{kOpGemm, o3[q], int(l3[q].size()), t3[q]});
+    if (!l3[q].empty()) b.ops.push_back(Op{kOpGemmX3, o3[q], int(l3[q].size()), t3[q]});
   }
   return iters & 1;
 }
@@ -292,6 +293,7 @@ void add_root_ops(Build& b, std::vector<Side*> sides, int p, int iters, double e
       r.sc = c.out;
       r.resid = b.ptr<float>(s->resid);
       r.xsel = b.ptr<int32_t>(s->xsel);
+      r.amax = s->amax;
       r.dp = int32_t(s->dp);
       r.tile_begin = itiles;
       itiles += tn * tn;
@@ -404,29 +406,59 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
   desc_at = a.off;
   const bool refresh = hp->refresh != 0;
   const int iters = hp->root_iters;
+  // slots of one entry: the largest |element| of G, P_L, P_R and Y
+  enum { kSG, kSPL, kSPR, kSY, kSlots };
+  b.reserve_slots(desc_at, size_t(count) * kSlots);
+  auto slot = [&](int64_t i, int k) { return b.slot(size_t(i) * kSlots + size_t(k)); };
 
   std::vector<ShCopyDesc> cin;
-  int ct = 0;
+  std::vector<ShMaxDesc> smax;
+  int ct = 0, mt = 0;
   for (int64_t i = 0; i < count; ++i) {
     EntryPlan& e = P[size_t(i)];
     // a bf16 gradient is copied as bf16 (exact): the GEMM reads it as a one-part operand
     cin.push_back(copy_desc(en[i].grad, en[i].grad_dtype, b.ptr<float>(e.g()), b.ptr<float>(e.gt()), e.m, e.n,
                             e.n, e.np, e.mp, e.mp, e.np, ct));
     cin.back().dst_bf16 = e.grad_bf16 ? 1 : 0;
+    cin.back().amax = slot(i, kSG);
+    e.L.amax = slot(i, kSPL);
+    e.R.amax = slot(i, kSPR);
     if (!e.L.S)
       cin.push_back(copy_desc(en[i].L, kDtF32, b.ptr<float>(e.L.M), nullptr, e.m, e.m, e.m, e.mp, 0, e.mp,
                               e.mp, ct));
     if (!e.R.S)
       cin.push_back(copy_desc(en[i].R, kDtF32, b.ptr<float>(e.R.M), nullptr, e.n, e.n, e.n, e.np, 0, e.np,
                               e.np, ct));
-    if (!refresh && !e.L.S)
-      cin.push_back(copy_desc(en[i].PL, kDtF32, b.ptr<float>(e.L.X[0]), nullptr, e.m, e.m, e.m, e.mp, 0,
-                              e.mp, e.mp, ct));
-    if (!refresh && !e.R.S)
-      cin.push_back(copy_desc(en[i].PR, kDtF32, b.ptr<float>(e.R.X[0]), nullptr, e.n, e.n, e.n, e.np, 0,
-                              e.np, e.np, ct));
+    // a stored preconditioner: copied (which takes its largest element), or read where it lies
+    auto stored = [&](const float* p, Side& side) {
+      if (side.S) {
+        ShMaxDesc x{};
+        x.p = p;
+        x.n = side.d * side.d;
+        x.slot = side.amax;
+        x.tile_begin = mt;
+        mt += int((x.n + kShMaxElems - 1) / kShMaxElems);
+        smax.push_back(x);
+        return;
+      }
+      cin.push_back(copy_desc(p, kDtF32, b.ptr<float>(side.X[0]), nullptr, side.d, side.d, side.d, side.dp, 0, side.dp,
+                              side.dp, ct));
+      cin.back().amax = side.amax;
+    };
+    if (!refresh) {
+      stored(en[i].PL, e.L);
+      stored(en[i].PR, e.R);
+    }
   }
   b.op(kOpCopyIn, cin, ct);
+  // the stored preconditioners' largest elements (one read of the buffers) are taken on the auxiliary
+  // stream, beside the statistics, which are not HBM bound
+  if (!smax.empty()) {
+    b.fork();
+    b.aux = 1;
+    b.op(kOpMax, smax, mt);
+    b.aux = 0;
+  }
 
   // grouped products over the entries, largest first (see add_root_ops)
   std::vector<EntryPlan*> order;
@@ -434,24 +466,27 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
   std::stable_sort(order.begin(), order.end(), [](const EntryPlan* x, const EntryPlan* y) {
     return std::max(x->mp, x->np) > std::max(y->mp, y->np);
   });
-  // a bf16 gradient is one bf16 part: the statistics take one product, P_L G three
   auto stat = [&](const Side& s, float* caller) { return s.S ? caller : b.ptr<float>(s.M); };
-  std::vector<ShGemmDesc> gs;
-  int gt = 0;
-  for (EntryPlan* ep : order) {
-    EntryPlan& e = *ep;
-    const mfsdp_shampoo_entry& c = en[ep - P.data()];
-    const int bf = e.grad_bf16 ? 1 : 0;
-    float* Ls = stat(e.L, c.L);
-    float* Rs = stat(e.R, c.R);
-    gs.push_back(gemm_desc(b.ptr<float>(e.g()), b.ptr<float>(e.g()), Ls, Ls, e.np, e.np, e.mp, e.mp, e.mp, e.mp,
-                           e.np, 1, float(hp->weight), float(hp->beta), 0.0f, gt));
-    gs.back().p_bf16 = gs.back().q_bf16 = bf;
-    gs.push_back(gemm_desc(b.ptr<float>(e.gt()), b.ptr<float>(e.gt()), Rs, Rs, e.mp, e.mp, e.np, e.np, e.np, e.np,
-                           e.mp, 1, float(hp->weight), float(hp->beta), 0.0f, gt));
-    gs.back().p_bf16 = gs.back().q_bf16 = bf;
+  // (the statistics of bf16 gradients, one bf16 product per step, in a launch of their own)
+  for (int bf = 1; bf >= 0; --bf) {
+    std::vector<ShGemmDesc> gs;
+    int gt = 0;
+    for (EntryPlan* ep : order) {
+      EntryPlan& e = *ep;
+      if (e.grad_bf16 != (bf == 1)) continue;
+      const mfsdp_shampoo_entry& c = en[ep - P.data()];
+      auto sym = [&](size_t g, float* S, int64_t d, int64_t k) {
+        gs.push_back(gemm_desc(b.ptr<float>(g), b.ptr<float>(g), S, S, k, k, d, d, d, d, k, 1, float(hp->weight),
+                               float(hp->beta), 0.0f, gt));
+        gs.back().p_bf16 = gs.back().q_bf16 = bf;
+        gs.back().pmax = gs.back().qmax = slot(ep - P.data(), kSG);
+      };
+      sym(e.g(), stat(e.L, c.L), e.mp, e.np);
+      sym(e.gt(), stat(e.R, c.R), e.np, e.mp);
+    }
+    b.op(bf ? kOpGemmB : kOpGemm, gs, gt);
   }
-  b.op(kOpGemm, gs, gt);
+  if (!smax.empty()) b.join();
 
   std::vector<ShCopyDesc> cst;
   ct = 0;
@@ -475,54 +510,61 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
     add_root_ops(b, sides, 4, iters, hp->eps_rel);
   }
 
-  std::vector<ShGemmDesc> gy, gu;
-  int ty = 0, tu = 0;
+  // the last product applies the parameter update
+  std::vector<ShApplyDesc> ap;
+  for (int64_t i = 0; i < count; ++i) {
+    ShApplyDesc d{};
+    d.param = en[i].param;
+    d.update_out = en[i].update_out;
+    d.m = en[i].m;
+    d.n = en[i].n;
+    d.param_dtype = en[i].param_dtype == MFSDP_BF16 ? kDtBF16 : kDtF32;
+    ap.push_back(d);
+  }
+  const ShApplyDesc* fused = b.ptr<ShApplyDesc>(desc_at + b.put(ap));
+  // products with G as Q: the bf16 gradients' in a launch of their own
+  std::vector<ShGemmDesc> gyb, gyf, gu;
+  int tyb = 0, tyf = 0, tu = 0;
   for (EntryPlan* ep : order) {
     EntryPlan& e = *ep;
     const size_t i = size_t(ep - P.data());
     // the preconditioners: this step's roots, or the stored ones (read where they lie, or copied)
     const float* pl = refresh ? e.L.root(b) : e.L.S ? en[i].PL : b.ptr<float>(e.L.X[0]);
     const float* pr = refresh ? e.R.root(b) : e.R.S ? en[i].PR : b.ptr<float>(e.R.X[0]);
+    auto max_slots = [&](ShGemmDesc& g, int p, int q, int c) {
+      g.pmax = slot(int64_t(i), p);
+      g.qmax = slot(int64_t(i), q);
+      g.cmax = c < 0 ? nullptr : slot(int64_t(i), c);
+    };
     // U = P_L G P_R^T. Both association orders take the same fp32 flop, but with a bf16 G the product
-    // that reads G takes three bf16 MFMAs per step and the other six, so the larger of the two
+    // that reads G takes two MFMAs per step and the other three, so the larger of the two
     // products should be the one with G: a wide G (n > m) forms Y^T = P_R G^T (n x m) first and then
     // U = P_L Y; otherwise Y = P_L G, then U = Y P_R^T.
+    std::vector<ShGemmDesc>& gy = e.grad_bf16 ? gyb : gyf;
+    int& ty = e.grad_bf16 ? tyb : tyf;
     if (e.grad_bf16 && e.n > e.m) {
       gy.push_back(gemm_desc(pr, b.ptr<float>(e.g()), nullptr, b.ptr<float>(e.Y), e.np, e.np, 0, e.mp, e.np,
                              e.mp, e.np, 0, 1.0f, 0.0f, 0.0f, ty));
       gy.back().q_bf16 = 1;
+      max_slots(gy.back(), kSPR, kSG, kSY);
       gu.push_back(gemm_desc(pl, b.ptr<float>(e.Y), nullptr, b.ptr<float>(e.u()), e.mp, e.mp, 0, e.np, e.mp,
                              e.np, e.mp, 0, 1.0f, 0.0f, 0.0f, tu));
+      max_slots(gu.back(), kSPL, kSY, -1);
     } else {
       gy.push_back(gemm_desc(pl, b.ptr<float>(e.gt()), nullptr, b.ptr<float>(e.Y), e.mp, e.mp, 0, e.np, e.mp,
                              e.np, e.mp, 0, 1.0f, 0.0f, 0.0f, ty));
       gy.back().q_bf16 = e.grad_bf16 ? 1 : 0;
+      max_slots(gy.back(), kSPL, kSG, kSY);
       gu.push_back(gemm_desc(b.ptr<float>(e.Y), pr, nullptr, b.ptr<float>(e.u()), e.np, e.np, 0, e.np, e.mp,
                              e.np, e.np, 0, 1.0f, 0.0f, 0.0f, tu));
+      max_slots(gu.back(), kSY, kSPR, -1);
     }
   }
-  b.op(kOpGemm, gy, ty);
+  for (size_t k = 0; k < gu.size(); ++k) gu[k].fused = fused + (order[k] - P.data());
+  b.op(kOpGemmP2B, gyb, tyb);
+  b.op(kOpGemm, gyf, tyf);
   b.op(kOpGemm, gu, tu);
 
-  std::vector<ShApplyDesc> ap;
-  int at = 0;
-  for (int64_t i = 0; i < count; ++i) {
-    EntryPlan& e = P[size_t(i)];
-    ShApplyDesc d{};
-    d.U = b.ptr<float>(e.u());
-    d.ldu = e.np;
-    d.param = en[i].param;
-    d.update_out = en[i].update_out;
-    d.m = e.m;
-    d.n = e.n;
-    d.param_dtype = en[i].param_dtype == MFSDP_BF16 ? kDtBF16 : kDtF32;
-    const int64_t tn = (e.n + kShCopyTile - 1) / kShCopyTile, tm = (e.m + kShCopyTile - 1) / kShCopyTile;
-    d.tiles_n = int32_t(tn);
-    d.tile_begin = at;
-    at += int(tm * tn);
-    ap.push_back(d);
-  }
-  b.op(kOpApply, ap, at);
   return desc_at + al(b.h.size());
 }
 

@@ -75,10 +75,16 @@ struct ShGemmDesc {
   float* resid_out;      // max |C - I| over the real block (rows, cols < valid), atomic max
   int32_t copy_on_skip;
   int32_t valid;
-  // operand stored as bf16 (a bf16 gradient; row stride in elements): it is one part of the bf16
-  // split, so the products with the zero mid and lo parts of an fp32 split are dropped. Both P and
-  // Q, or Q alone (P alone is not supported). fp32 operands are split into three parts.
+  // operand stored as bf16 (a bf16 gradient; row stride in elements): both P and Q, or Q alone
   int32_t p_bf16, q_bf16;
+  // scaled products: the largest |element| of P and of Q so far, as fp32 bit patterns (null: elements are
+  // at most 1), and a slot that receives C's (atomic max; null: not needed)
+  const uint32_t* pmax;
+  const uint32_t* qmax;
+  uint32_t* cmax;
+  // scaled products: apply the parameter update p <- p decay - step C (and C to update_out) to the real
+  // block instead of storing C; null: store C
+  const struct ShApplyDesc* fused;
 };
 
 // Boundary copies over 64 x 64 tiles of a padded rows_pad x cols_pad domain.
@@ -96,6 +102,16 @@ struct ShCopyDesc {
   int32_t tiles_n;     // column tiles of the domain
   int32_t tile_begin;
   int32_t dst_bf16;    // dir 0: dst and dstT hold bf16
+  uint32_t* amax;      // dir 0: receives the largest |element| (bit pattern, atomic max; may be null)
+};
+
+// The largest |element| of n (a multiple of 4) dense, 16-byte aligned fp32 values, into a slot.
+constexpr int kShMaxElems = 16384;
+struct ShMaxDesc {
+  const float* p;
+  int64_t n;
+  uint32_t* slot;
+  int32_t tile_begin;  // kShMaxElems elements per workgroup
 };
 
 // Sum of squares and trace of a padded d_pad x d_pad statistic, in row chunks (fp64 partials).
@@ -161,6 +177,7 @@ struct RootConvDesc {
   const float* sc;
   float* resid;          // the two residual slots: {0, not converged}
   const int32_t* xsel;
+  uint32_t* amax;        // out: receives the largest |element| (bit pattern, atomic max; may be null)
   int32_t dp;
   int32_t tile_begin;    // 64 x 64 tiles
 };
@@ -177,7 +194,12 @@ struct ShApplyDesc {
   int32_t tile_begin;
 };
 
-hipError_t launch_sh_gemm(const ShGemmDesc* d, int count, int total_tiles, hipStream_t st);
+// kind: three-way bf16 splits (operands of any range), all operands bf16, scaled two-way fp16 splits of a
+// preconditioner P with a bf16 Q, or scaled two-way fp16 splits and one-part operands; decay and step are those of the problems that apply a parameter update
+enum { kShX3, kShB, kShP2B, kShScaled };
+hipError_t launch_sh_gemm(const ShGemmDesc* d, int count, int total_tiles, int kind, float decay, float step,
+                          hipStream_t st);
+hipError_t launch_sh_max(const ShMaxDesc* d, int count, int total_blocks, hipStream_t st);
 hipError_t launch_sh_copy(const ShCopyDesc* d, int count, int total_tiles, int dir, hipStream_t st);
 hipError_t launch_sh_norm(const ShNormDesc* d, int count, int total_blocks, hipStream_t st);
 hipError_t launch_sh_scalars(const ShScalarDesc* d, int count, double eps, double eps_rel, int p,

@@ -347,6 +347,53 @@ def test_shampoo_unaligned_caller_buffers_take_the_copy_path(native, refresh):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("gdt", [synth.BF16, synth.F32])
+@pytest.mark.parametrize("shape", [(129, 300), (300, 129), (256, 384), (5, 3)])
+@pytest.mark.parametrize("k", [-40, 30])
+def test_shampoo_stored_step_is_exact_under_power_of_two_scaling(native, shape, gdt, k):
+    """The products' operands are scaled by powers of two from their largest elements: a gradient and
+    preconditioners 2^k and 2^-k / 2 times as large give exactly 2^k (1/2)^2 2^-2k times the U, and 2^2k times the
+    statistics, in every bit; the parameter, with lr scaled back, is the same. (Parameters at an
+    address that holds no whole 16-byte slots.)"""
+    import torch
+    m, n = shape
+    _say(f"shampoo scaling {m}x{n} {gdt} 2^{k}")
+    outs = []
+    for kk in (0, k):
+        x = _Mat(np.random.default_rng(4300 + m), m, n, synth.F32, gdt).device()
+        f = 2.0 ** kk
+        x.dg.mul_(f)
+        h = 1.0 if kk == 0 else 0.5 / f
+        x.dL.copy_(to_dev((_spd(np.random.default_rng(5), m, 10.0) * 1e-3).astype(np.float32), synth.F32)).mul_(f * f)
+        x.dR.copy_(to_dev((_spd(np.random.default_rng(6), n, 10.0) * 1e-3).astype(np.float32), synth.F32)).mul_(f * f)
+        x.dPL.copy_(to_dev(_spd(np.random.default_rng(7), m, 10.0).astype(np.float32), synth.F32)).mul_(h)
+        x.dPR.copy_(to_dev(_spd(np.random.default_rng(8), n, 10.0).astype(np.float32), synth.F32)).mul_(h)
+        x.dp = _offset_view(x.dp)
+        un = f * h * h
+        hpn, _ = _hp(native, refresh=False, beta=0.5, weight=0.5, lr=2.0 ** -6 / un, weight_decay=0.0)
+        ents = [x.entry(native)]
+        native.shampoo_step_t(ents, hpn, native.shampoo_workspace_t(ents, hpn))
+        _sync()
+        outs.append([x.dU / un, x.dL / (f * f), x.dR / (f * f), x.dp.clone()])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b) and bool(torch.isfinite(a).all())
+
+
+def test_shampoo_stored_step_propagates_non_finite_gradients(native):
+    import torch
+    _say("shampoo non-finite gradient")
+    for bad in (float("inf"), float("nan")):
+        x = _Mat(np.random.default_rng(4400), 130, 70, synth.F32, synth.F32).device()
+        x.dPL.copy_(torch.eye(130, device="cuda"))
+        x.dPR.copy_(torch.eye(70, device="cuda"))
+        x.dg[7, 9] = bad
+        hpn, _ = _hp(native, refresh=False)
+        ents = [x.entry(native)]
+        native.shampoo_step_t(ents, hpn, native.shampoo_workspace_t(ents, hpn))
+        _sync()
+        assert not bool(torch.isfinite(x.dU[7, 9])) and not bool(torch.isfinite(x.dp[7, 9]))
+
+
 @pytest.mark.parametrize("eps_rel", [1e-6, 1e-4])
 @pytest.mark.parametrize("dts", [(synth.BF16, synth.BF16), (synth.F32, synth.F32)])
 def test_shampoo_stale_step_on_new_gradient_after_rank_deficient_refresh(native, eps_rel, dts):

@@ -405,6 +405,36 @@ def test_soap_unaligned_caller_buffers_take_the_copy_path(native, refresh):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("gdt", [synth.BF16, synth.F32])
+@pytest.mark.parametrize("maxd", [4096, 200, 130, 64])
+@pytest.mark.parametrize("k", [-30, 25])
+def test_soap_step_is_exact_under_power_of_two_scaling(native, gdt, maxd, k):
+    """The products' operands are scaled by powers of two from their largest elements: gradients and
+    moments 2^k times as large (second moments and statistics 2^2k) give the same direction and
+    parameter in every bit, with a basis on both sides, one, or none (129 x 300), eps being far below the
+    second moments' roots."""
+    import torch
+    m, n = 129, 300
+    _say(f"soap scaling {gdt} maxd={maxd} 2^{k}")
+    outs = []
+    for kk in (0, k):
+        f = 2.0 ** kk
+        x = _Mat(np.random.default_rng(9950), m, n, synth.F32, gdt, maxd=maxd).device()
+        x.dg.mul_(f)
+        x.dM.mul_(f)
+        x.dV.mul_(f * f)
+        for t in (x.dL, x.dR):
+            if t is not None:
+                t.mul_(f * f)
+        hpn, _, _ = _hp(native, refresh=False, eps=1e-30, max_precond_dim=maxd)
+        ents = [x.entry(native)]
+        native.soap_step_t(ents, hpn, native.soap_workspace_t(ents, hpn))
+        _sync()
+        outs.append([x.dN, x.dp, x.dM / f, x.dV / (f * f)] + [t / (f * f) for t in (x.dL, x.dR) if t is not None])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b) and bool(torch.isfinite(a).all())
+
+
 def test_soap_benchmark_configuration_full_size(native):
     """The configuration bench.py times: the GPT-2-small share's 12 matrices in one call, bf16
     parameters and gradients, full-rank statistics and random orthogonal bases, refresh on; every
