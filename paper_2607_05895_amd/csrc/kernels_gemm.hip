@@ -10,8 +10,9 @@
 // (TileRef); each 256 x 256 output tile is 2 x 4 waves of 128 x 64, as 4 x 2 blocks of
 // v_mfma_f32_32x32x16_bf16 with fp32 accumulation. K advances 32 elements per step through a
 // five-stage LDS ring filled by direct global->LDS loads; the next tile's first loads overlap the
-// current tile's epilogue. The Gram and square products of a small share run the same kernel on
-// 128 x 128 tiles (2 x 2 waves of 64 x 64, two workgroups per CU), four times the tiles.
+// current tile's epilogue. The Gram and square products of a small share, and all products of a yet
+// smaller one, run the same kernel on 128 x 128 tiles (2 x 2 waves of 64 x 64, two workgroups per CU),
+// four times the tiles.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -56,54 +57,6 @@ __device__ __forceinline__ float scale_pow(const float* s, int pw) {
   if (!s || pw == 0) return 1.0f;
   const float v = *s;
   return pw == 1 ? v : v * v;
-}
-
-// Fused parameter update for 4 consecutive elements (pr, pc .. pc + 3) of the stored m x n
-// parameter, pc a multiple of 4: p <- p (1 - lr wd) - lr f O (mode 0, optionally also writing O to
-// update_out), or p <- O (mode 1, standalone NS output). Elements outside m x n are skipped.
-__device__ __forceinline__ void apply4(const ApplyDesc& a, int64_t pr, int64_t pc, float o0,
-                                       float o1, float o2, float o3) {
-  typedef __attribute__((address_space(1))) float gf32;
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  typedef __attribute__((address_space(1))) f32x4 gf4;
-  const int64_t m = a.m, n = a.n;
-  if (pr >= m || pc >= n) return;
-  const int64_t idx = pr * n + pc;
-  const float o[4] = {o0, o1, o2, o3};
-  const bool bf = a.param_dtype == kDtBF16;
-  if ((n & 3) == 0) {  // then pc + 3 < n, and the 4 elements are 8 / 16-byte aligned
-    float r[4] = {o0, o1, o2, o3};
-    if (a.mode == 0) {
-      float p[4];
-      if (bf) {
-        const u32x2 w = *(const gu2*)((const gu16*)a.param + idx);
-        p[0] = __uint_as_float(w.x << 16); p[1] = __uint_as_float(w.x & 0xffff0000u);
-        p[2] = __uint_as_float(w.y << 16); p[3] = __uint_as_float(w.y & 0xffff0000u);
-      } else {
-        const f32x4 w = *(const gf4*)((const gf32*)a.param + idx);
-        p[0] = w.x; p[1] = w.y; p[2] = w.z; p[3] = w.w;
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) r[k] = p[k] * a.decay - a.step * o[k];
-      if (a.update_out) *(gf4*)((gf32*)a.update_out + idx) = f32x4{o0, o1, o2, o3};
-    }
-    if (bf) *(gu2*)((gu16*)a.param + idx) = u32x2{pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
-    else *(gf4*)((gf32*)a.param + idx) = f32x4{r[0], r[1], r[2], r[3]};
-  } else {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (pc + k >= n) break;
-      float r = o[k];
-      if (a.mode == 0) {
-        const float p = bf ? __uint_as_float(uint32_t(((const gu16*)a.param)[idx + k]) << 16)
-                           : ((const gf32*)a.param)[idx + k];
-        r = p * a.decay - a.step * o[k];
-        if (a.update_out) ((gf32*)a.update_out)[idx + k] = o[k];
-      }
-      if (bf) ((gu16*)a.param)[idx + k] = uint16_t(pack_bf16x2(r, 0.0f));
-      else ((gf32*)a.param)[idx + k] = r;
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -715,31 +668,116 @@ __global__ __launch_bounds__(NW * 64, TB == BT ? 1 : 2) void gemm_bf16_kernel(
       continue;
     }
     if constexpr (PK == kProdApply) {
-      // Parameters the staged update does not take (fp32 parameters, or n % 8 != 0): straight from
-      // the accumulators, 4 elements per lane and group; a tall parameter takes the quad-transposed
-      // values. (Compile-time loops: every acc index must be a constant for acc to stay in registers.)
-      static_for<MI>([&](auto mi_c) {
-        constexpr int mi = decltype(mi_c)::value;
-        const int64_t i = int64_t(bi) * TB + wm * (MI * 32) + mi * 32 + frow;
-        const int64_t iq = i - q;  // first row of this lane quad
-        static_for<NI>([&](auto ni_c) {
-          constexpr int ni = decltype(ni_c)::value;
-          static_for<4>([&](auto gg_c) {
-            constexpr int gg = decltype(gg_c)::value;
-            const int64_t j = int64_t(bj) * TB + wn * (NI * 32) + ni * 32 + gg * 8 + fhalf * 4;
-            float v0 = alpha * acc[mi][ni][4 * gg + 0];
-            float v1 = alpha * acc[mi][ni][4 * gg + 1];
-            float v2 = alpha * acc[mi][ni][4 * gg + 2];
-            float v3 = alpha * acc[mi][ni][4 * gg + 3];
-            if (fa_t) {
-              quad_transpose(v0, v1, v2, v3);
-              apply4(*fa, j + q, iq, v0, v1, v2, v3);  // lane q: column j + q at rows iq .. iq + 3
-            } else {
-              apply4(*fa, i, j, v0, v1, v2, v3);
+      // Other parameters (fp32, n % 8 != 0, or 128 x 128 tiles): the same rounds and slab (fp32 rows of TB / 2
+      // tile columns of a wide parameter, or of the 64 tile rows of a tall one; 16-byte slots XOR-permuted by
+      // the row), read back four consecutive elements per lane, so that a wave's accesses cover whole row
+      // segments. Before, each lane went straight from its accumulators, one element at a time where n % 4 != 0,
+      // and a wave touched 32 rows per access: a 4001 x 4003 step of one iteration took 538 us, now 470 us (fp32
+      // 4003 x 4001: 585 and 529 us). Single elements through the slab were no faster than before (540 us): the
+      // count of accesses bounds it, so odd n takes vectors too, at its elements' own alignment.
+      typedef float f32x4 __attribute__((ext_vector_type(4)));
+      typedef __attribute__((address_space(3))) f32x4 lf4;
+      typedef __attribute__((address_space(3))) float lf1;
+      lds_byte* slab = (lds_byte*)(smem + (NSTAGE - 1) * STAGE_BYTES);
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      const int frow = ln & 31, fhalf = ln >> 5, qd = ln & 3;
+      constexpr int WH = WG::WN / 2;                      // waves per column half
+      auto rounds = [&](auto tall_c) {
+        constexpr bool TALL = decltype(tall_c)::value;
+        constexpr int V = 4;
+        constexpr int COLS = TALL ? 64 : TB / 2, ROWS = TALL ? WG::WN * 32 : 64;  // of the slab
+        constexpr int LPR = COLS / V < 64 ? COLS / V : 64, CP = COLS / V / LPR;   // lanes per row, column passes
+        constexpr int RPP = 64 / LPR, NIT = ROWS / NW / RPP * CP;                  // rows per wave and pass, passes
+        static_assert(ROWS * 4 <= NW * 64, "four threads a row for the rows' last elements");
+        auto srow = [&](int it) { return w * (ROWS / NW) + (it / CP) * RPP + ln / LPR; };
+        auto scol = [&](int it) { return ((it % CP) * LPR + ln % LPR) * V; };
+        auto at = [](int r, int c) { return r * (COLS * 4) + (((c >> 2) ^ (r & (COLS / 4 - 1))) << 4) + (c & 3) * 4; };
+        static_for<MI>([&](auto mi_c) {
+          constexpr int mi = decltype(mi_c)::value;
+          static_for<NI>([&](auto h_c) {  // column half of the tile (wide), block column of every wave (tall)
+            constexpr int h = decltype(h_c)::value;
+            static_assert(NI == 2, "two halves");
+            // slab element (r, c) is parameter element (pr0 + dr(r), pc0 + dc(c))
+            const int64_t pr0 = TALL ? int64_t(bj) * TB + h * 32 : int64_t(bi) * TB + mi * 32;
+            const int64_t pc0 = TALL ? int64_t(bi) * TB + mi * 32 : int64_t(bj) * TB + h * (TB / 2);
+            constexpr int RS = TALL ? NI * 32 : MI * 32;  // rows between the 32-row pieces
+            auto dr = [&](int r) { return (r >> 5) * RS + (r & 31); };
+            auto dc = [&](int c) { return TALL ? (c >> 5) * (MI * 32) + (c & 31) : c; };
+            const int64_t base = pr0 * fa->n + pc0;
+            const int nn = int(fa->n), rl = int(fa->m - pr0 < 4096 ? fa->m - pr0 : 4096),
+                      cl = int(fa->n - pc0 < 4096 ? fa->n - pc0 : 4096);  // real rows and columns from there
+            // the parameter words of passes it0 .. it0 + NB - 1
+            constexpr int NB = 16 / V;
+            ParamWords<V> pw[NB];
+            auto load = [&](int it0) {
+#pragma unroll
+              for (int k = 0; k < NB; ++k) {
+                const int r = dr(srow(it0 + k)), c = dc(scol(it0 + k));
+                if (fa->mode == 0 && r < rl && c + V <= cl) pw[k].load(fa->param, fa->param_dtype, base + (r * nn + c));
+              }
+            };
+            load(0);
+            if constexpr (TALL) {
+              static_for<4>([&](auto gg_c) {
+                constexpr int gg = decltype(gg_c)::value;
+                float v0 = alpha * acc[mi][h][4 * gg + 0];
+                float v1 = alpha * acc[mi][h][4 * gg + 1];
+                float v2 = alpha * acc[mi][h][4 * gg + 2];
+                float v3 = alpha * acc[mi][h][4 * gg + 3];
+                quad_transpose(v0, v1, v2, v3);  // lane qd: column + qd at four tile rows
+                *(lf4*)(slab + at(wn * 32 + gg * 8 + fhalf * 4 + qd, wm * 32 + (frow & ~3))) = f32x4{v0, v1, v2, v3};
+              });
+            } else if (wn / WH == h) {
+              static_for<NI>([&](auto ni_c) {
+                constexpr int ni = decltype(ni_c)::value;
+                static_for<4>([&](auto gg_c) {
+                  constexpr int gg = decltype(gg_c)::value;
+                  *(lf4*)(slab + at(wm * 32 + frow, (wn % WH) * 64 + ni * 32 + gg * 8 + fhalf * 4)) =
+                      f32x4{alpha * acc[mi][ni][4 * gg], alpha * acc[mi][ni][4 * gg + 1], alpha * acc[mi][ni][4 * gg + 2],
+                            alpha * acc[mi][ni][4 * gg + 3]};
+                });
+              });
             }
+            MFSDP_WAIT_LGKM0();
+            __builtin_amdgcn_s_barrier();
+#pragma unroll
+            for (int it0 = 0; it0 < NIT; it0 += NB) {
+              if (it0 > 0) load(it0);
+#pragma unroll
+              for (int k = 0; k < NB; ++k) {
+                const int sr = srow(it0 + k), sc = scol(it0 + k), r = dr(sr), c = dc(sc);
+                if (r < rl && c + V <= cl) {
+                  const f32x4 x = *(lf4*)(slab + at(sr, sc));
+                  const float o[V] = {x.x, x.y, x.z, x.w};
+                  const int64_t i = base + (r * nn + c);
+                  if (fa->mode == 0) pw[k].store(fa->param, fa->param_dtype, fa->update_out, i, fa->decay, fa->step, o);
+                  else ParamWords<V>::write(fa->param, fa->param_dtype, i, o);
+                }
+              }
+            }
+            if (nn & 3) {  // the row's last one to three elements, one per lane
+              const int sr = threadIdx.x >> 2, r = dr(sr), c = (cl & ~3) + (threadIdx.x & 3);  // c: from pc0
+              const int sc = TALL ? (c / (MI * 32)) * 32 + c % (MI * 32) : c;
+              const bool here = TALL ? c % (MI * 32) < 32 && c < 2 * MI * 32 : c < TB / 2;
+              if (sr < ROWS && cl > 0 && here && r < rl && c < cl) {
+                const float o[1] = {*(lf1*)(slab + at(sr, sc))};
+                const int64_t i = base + (r * nn + c);
+                ParamWords<1> p1;
+                if (fa->mode == 0) {
+                  p1.load(fa->param, fa->param_dtype, i);
+                  p1.store(fa->param, fa->param_dtype, fa->update_out, i, fa->decay, fa->step, o);
+                } else {
+                  ParamWords<1>::write(fa->param, fa->param_dtype, i, o);
+                }
+              }
+            }
+            __builtin_amdgcn_s_barrier();  // slab reads done before the next round writes
           });
         });
-      });
+      };
+      if (fa_t) rounds(std::true_type{});
+      else rounds(std::false_type{});
     }
     if (!has_next) break;
     cur = nxt;
@@ -821,8 +859,10 @@ hipError_t launch_gemm(const GemmDesc* d_descs, int total_tiles, const TileRef* 
       launch_bf16<WS, TS, kProdGram>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
     else if (product == kProdSquare)
       launch_bf16<WS, TS, kProdSquare>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
+    else if (product == kProdUpdate)
+      launch_bf16<WS, TS, kProdUpdate>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
     else
-      return hipErrorInvalidValue;
+      launch_bf16<WS, TS, kProdApply>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
   } else if (product == kProdGram)
     launch_bf16<W, BT, kProdGram>(d_descs, d_sched, ngroups, parity, first_step, last_step, ca, cb, cc, st);
   else if (product == kProdSquare)

@@ -62,12 +62,13 @@ __device__ __forceinline__ void slot_max(uint32_t* slot, uint32_t big) {
   __syncthreads();
 }
 
-// A parameter update p <- p decay - step O of V = 1 or 4 consecutive elements (4: 8-byte aligned in bf16, 16 in
-// fp32; update_out, if any, 16), in two halves: the old words are loaded long before O is there.
+// A parameter update p <- p decay - step O of V = 1 or 4 consecutive elements, in two halves: the old words are
+// loaded long before O is there. Four elements are one access at any address of their own type's alignment (rows
+// of odd n): global memory takes unaligned vectors, split by the hardware only where they cross a line.
 template <int V>
 struct ParamWords {
-  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(2)));
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
   template <typename T>
   using gptr = __attribute__((address_space(1))) T*;
   uint32_t w[V];  // fp32 bits
@@ -228,8 +229,8 @@ hipError_t launch_norm(const NormDesc* d_descs, int count, float eps, hipStream_
 // product: 0 Gram, 1 square, 2 update (the order of the products in one NS step); 3 the last update with
 // the fused parameter update (its descriptors carry `fused`)
 // (ca, cb, cc): the NS step's coefficients (a_k, b_k, c_k), used by the square product.
-// tile: the output tile, kTileBF16 or (Gram and square products only) kTileBF16Small; the descriptors'
-// tile grids and the schedule are in that tile.
+// tile: the output tile, kTileBF16 or kTileBF16Small; the descriptors' tile grids and the schedule are in
+// that tile.
 hipError_t launch_gemm(const GemmDesc* d_descs, int total_tiles, const TileRef* d_sched, int ngroups, int product,
                        int parity, int first_step, int last_step, float ca, float cb, float cc, int tile,
                        hipStream_t st);
@@ -253,8 +254,8 @@ hipError_t launch_adamw(const AdamWBatch& batch, int total_blocks, hipStream_t s
 
 // NS tile sizes (padding granularity of the workspace buffers).
 constexpr int kTileBF16 = 256;
-// The bf16 Gram and square products of a launch with few 256 x 256 tiles run on 128 x 128 tiles,
-// two workgroups per CU (the padding stays 256).
+// The bf16 products of a launch with few 256 x 256 tiles run on 128 x 128 tiles, two workgroups per CU
+// (the padding stays 256).
 constexpr int kTileBF16Small = 128;
 // The fp32 path pads to 64; its products run on 128 x 128 or 64 x 64 tiles, which may reach past the padding.
 constexpr int kTileF32 = 64;

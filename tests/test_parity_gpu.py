@@ -284,6 +284,34 @@ def test_muon_small_and_full_size_tiles_give_the_same_bits(native):
             assert torch.equal(x, y)
 
 
+# both sides of the 128 and 256 tile edges, tall and wide, n % 8 == 0, n % 4 == 0 and neither
+UPDATE_EDGES = [(129, 513), (513, 129), (260, 772), (772, 260), (127, 255), (255, 1), (264, 520), (520, 264)]
+
+
+@pytest.mark.parametrize("full_size_tiles", [False, True])
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+def test_muon_parameter_update_tile_edges(native, dtype, full_size_tiles):
+    """The last launch's parameter update at tile edges: alone (128 x 128 tiles, staged through LDS by
+    four elements or one) and next to a 4096 x 4096 matrix that takes every launch to 256 x 256 tiles
+    (staged by eight or four, or straight from the accumulators). Matches the oracle; parameters do not
+    depend on whether the update is also written out."""
+    import torch
+    _say(f"muon update at tile edges: dtype={dtype} full_size_tiles={full_size_tiles} {UPDATE_EDGES}")
+    rng = np.random.default_rng(5400)
+    specs = [synth.MuonSpec(m, n, f"e{m}x{n}", dtype, synth.BF16) for (m, n) in UPDATE_EDGES]
+    tensors = [synth.random_muon_tensors(rng, e.m, e.n, e.param_dtype, e.grad_dtype) for e in specs]
+    hp = synth.MuonHParams(lr=0.02, weight_decay=0.05)
+    more, more_t = [], []
+    if full_size_tiles:
+        more = [synth.MuonSpec(4096, 4096, "big")]
+        more_t = [synth.random_muon_tensors(rng, 4096, 4096)]
+    dev = _run_muon(native, tensors + more_t, specs + more, hp)
+    _check_muon(tensors, specs, dev[:len(specs)], hp, 2e-2)
+    plain = _run_muon(native, tensors + more_t, specs + more, hp, with_update=False)
+    for a, b in zip(dev, plain):
+        assert torch.equal(a[0], b[0])
+
+
 MIXED = [(256, 512), (512, 256), (384, 384), (100, 700), (700, 100), (130, 1000), (1, 50),
          (50, 1), (768, 3072), (3072, 768)]
 
