@@ -333,29 +333,23 @@ __global__ __launch_bounds__(kQrPanelThreads) void qr_panel_kernel(const QrPanel
     }
   });
   __syncthreads();
-  // the panel's 16 columns of V and rows of Vt over every block row: rows [0, c - j0) above the
-  // panel are zero, rows [c - j0, vrows) are the registers (zero from d on; vrows - (c - j0) =
-  // dp - c <= kQrMaxDim)
+  // the panel's 16 rows of Vt over every block row: entries [0, c - j0) above the panel are zero,
+  // entries [c - j0, vrows) are the registers (zero from d on; vrows - (c - j0) = dp - c <= kQrMaxDim).
+  // (V itself is formed by qr_t_kernel's launch: 64-byte pieces of its 512-byte rows, stored from here,
+  // took one line per lane and instruction on the one CU that the whole factorization waits for.)
   const int top = d.c - d.j0, s16 = top;  // the panel's first column within the block = c - j0
   {
-    g_f32* V = (g_f32*)(d.V) + s16;
     g_f32* Vt = (g_f32*)(d.Vt) + int64_t(s16) * d.ldvt;
     const int below = d.vrows - top;
 #pragma unroll
     for (int i = 0; i < kQrRowsPerThread; ++i) {
       const int lr = t + kQrPanelThreads * i;
       if (lr < below) {
-        g_f32x4* vrow = (g_f32x4*)(V + int64_t(top + lr) * kQrBlock);
-#pragma unroll
-        for (int q = 0; q < kQrPanel / 4; ++q)
-          vrow[q] = f32x4{a[i][4 * q], a[i][4 * q + 1], a[i][4 * q + 2], a[i][4 * q + 3]};
 #pragma unroll
         for (int k = 0; k < kQrPanel; ++k) Vt[int64_t(k) * d.ldvt + top + lr] = a[i][k];
       }
     }
     for (int r = t; r < top; r += kQrPanelThreads) {
-#pragma unroll
-      for (int q = 0; q < kQrPanel / 4; ++q) ((g_f32x4*)(V + int64_t(r) * kQrBlock))[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int k = 0; k < kQrPanel; ++k) Vt[int64_t(k) * d.ldvt + r] = 0.0f;
     }
@@ -366,103 +360,115 @@ __global__ __launch_bounds__(kQrPanelThreads) void qr_panel_kernel(const QrPanel
 
 // x <- H_16 ... H_1 x = x - V_s y for one column x of A (a row of At, rows [c, d) of A), with
 // y_k = tau_k (w_k - sum_{j<k} (v_j . v_k) y_j) and w = V_s^T x (the reflectors applied one after the
-// other, in the reduced coordinates). Thread t holds entries t + 256 i in registers and forms its
-// part of the 16 sums w (the panel's V rows are 64 contiguous bytes); the workgroup reduces them in
-// a fixed order (DPP reduce-scatter within each row of 16 lanes, then over the wave's four rows, then
-// over the four waves through LDS), one thread runs the 16-step recurrence for y, and every thread
-// subtracts V_s y from its entries. The column is read once and written once.
+// other, in the reduced coordinates). Bound by latency: it runs between two panels that depend on it.
+// (This layout, V out of the panels and the factor below: basis refresh of six 768/3072-sided matrices
+// 14.24 -> 12.16 ms.)
+// Thread t holds entries 4 (t + 256 i) .. + 3 in registers and reads the reflectors from Vt, 16 bytes per
+// lane and 1 KiB per wave (from V's rows, 64 bytes of each 512, a load touched one line per lane).
+// It forms its part of the 16 sums w; the workgroup reduces them in a fixed order (DPP reduce-scatter
+// within each row of 16 lanes, then over the wave's four rows, then over the four waves through LDS);
+// every wave then runs the 16-step recurrence for y itself, lane k holding w_k and column k of
+// the panel's block of T, and subtracts V_s y from its entries. The column is read and written once.
 __global__ __launch_bounds__(kQrColThreads) void qr_col_kernel(const QrColDesc* __restrict__ descs, int count) {
   __shared__ float red[kQrColThreads / 64][kQrPanel];
-  __shared__ float ws[kQrPanel];
-  __shared__ float ys[kQrPanel];
-  __shared__ float Ts[kQrPanel][kQrPanel];
   const int e = find_desc(descs, count, blockIdx.x);
   const QrColDesc& d = descs[e];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  static_assert(kQrColThreads == kQrPanel * kQrPanel, "one thread per entry of the panel's block of T");
-  Ts[t / kQrPanel][t % kQrPanel] = ((const g_cf32*)(d.T))[(t / kQrPanel) * kQrBlock + t % kQrPanel];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = lane & (kQrPanel - 1);
+  float tk[kQrPanel];  // T[j][l16]
+#pragma unroll
+  for (int j = 0; j < kQrPanel; ++j) tk[j] = ((const g_cf32*)(d.T))[j * kQrBlock + l16];
   const int64_t col = int64_t(d.c) + kQrPanel + (blockIdx.x - d.tile_begin);
   g_f32* x = (g_f32*)(d.At) + col * d.ld + d.c;
-  const g_cf32* V = (const g_cf32*)(d.V);
-  const int used = (d.rows + kQrColThreads - 1) / kQrColThreads;  // uniform
-  float xr[kQrColRows];
+  const g_cf32* Vt = (const g_cf32*)(d.Vt);
+  f32x4 xr[kQrColGroups];
   float part[kQrPanel];
 #pragma unroll
   for (int k = 0; k < kQrPanel; ++k) part[k] = 0.0f;
+  // (a group's four entries lie within the padded row: c and the row's length are multiples of 4;
+  // entries from d on count as zero and are not written)
 #pragma unroll
-  for (int i = 0; i < kQrColRows; ++i) {
-    xr[i] = 0.0f;
-    if (i < used) {
-      const int r = t + kQrColThreads * i;
-      if (r < d.rows) {
-        xr[i] = x[r];
-        const g_cf32x4* vr = (const g_cf32x4*)(V + int64_t(r) * kQrBlock);
+  for (int i = 0; i < kQrColGroups; ++i) {
+    xr[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int r = 4 * (t + kQrColThreads * i);
+    if (r < d.rows) {
+      xr[i] = *(const g_cf32x4*)(x + r);
 #pragma unroll
-        for (int q = 0; q < kQrPanel / 4; ++q) {
-          const f32x4 v = vr[q];
+      for (int j = 1; j < 4; ++j)
+        if (r + j >= d.rows) xr[i][j] = 0.0f;
 #pragma unroll
-          for (int j = 0; j < 4; ++j) part[4 * q + j] += v[j] * xr[i];
-        }
+      for (int k = 0; k < kQrPanel; ++k) {
+        const f32x4 v = *(const g_cf32x4*)(Vt + int64_t(k) * d.ldvt + r);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) part[k] += v[j] * xr[i][j];
       }
     }
   }
-  const float rsum = sum_rows4(row_reduce_scatter16(part, lane & 15));
+  const float rsum = sum_rows4(row_reduce_scatter16(part, l16));
   if (lane < kQrPanel) red[w][lane] = rsum;
   __syncthreads();
-  if (t < kQrPanel) ws[t] = ((red[0][t] + red[1][t]) + red[2][t]) + red[3][t];
-  __syncthreads();
-  if (t == 0) {
-    float yk[kQrPanel];
-#pragma unroll
-    for (int k = 0; k < kQrPanel; ++k) {
-      float acc = ws[k];
-#pragma unroll
-      for (int j = 0; j < k; ++j) acc -= Ts[j][k] * yk[j];
-      yk[k] = Ts[k][k] * acc;
-      ys[k] = yk[k];
-    }
-  }
-  __syncthreads();
+  float acc = ((red[0][l16] + red[1][l16]) + red[2][l16]) + red[3][l16];
   float y[kQrPanel];
 #pragma unroll
-  for (int k = 0; k < kQrPanel; ++k) y[k] = ys[k];
+  for (int j = 0; j < kQrPanel; ++j) {
+    y[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tk[j] * acc), j));
+    acc -= tk[j] * y[j];  // (lanes up to j are not read again)
+  }
 #pragma unroll
-  for (int i = 0; i < kQrColRows; ++i) {
-    if (i < used) {
-      const int r = t + kQrColThreads * i;
-      if (r < d.rows) {
-        const g_cf32x4* vr = (const g_cf32x4*)(V + int64_t(r) * kQrBlock);
-        float sub = 0.0f;
+  for (int i = 0; i < kQrColGroups; ++i) {
+    const int r = 4 * (t + kQrColThreads * i);
+    if (r < d.rows) {
+      f32x4 sub = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int q = 0; q < kQrPanel / 4; ++q) {
-          const f32x4 v = vr[q];
+      for (int k = 0; k < kQrPanel; ++k) {
+        const f32x4 v = *(const g_cf32x4*)(Vt + int64_t(k) * d.ldvt + r);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) sub += v[j] * y[4 * q + j];
-        }
-        x[r] = xr[i] - sub;
+        for (int j = 0; j < 4; ++j) sub[j] += v[j] * y[k];
+      }
+      const f32x4 out = xr[i] - sub;
+      if (r + 4 <= d.rows) {
+        *(g_f32x4*)(x + r) = out;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+          if (r + j < d.rows) x[r + j] = out[j];
       }
     }
   }
 }
 
-// The block's compact-WY factor, held in LDS. Each panel's diagonal block first, row by row (one
-// thread per row i; T_kk = tau_k, T_ik = -tau_k sum_{j=i}^{k-1} T_ij (v_j . v_k), from the tau and dot
-// products the panel left in its block); then, with the blocks of G above the diagonal blocks (G
-// summed over its partials in order), for each panel s = 1 .. 7 (first column n0 = 16 s),
-// M = G[0:n0, n0:n0+16] T_s and T[0:n0, n0:n0+16] = -T[0:n0, 0:n0] M over the upper triangle of
-// T[0:n0, 0:n0].
-__global__ __launch_bounds__(256) void qr_t_kernel(const QrTDesc* __restrict__ descs) {
+// The block's compact-WY factor, one workgroup per block, held in LDS. The panels' diagonal blocks
+// first, row by row (one thread per row i; T_kk = tau_k, T_ik = -tau_k sum_{j=i}^{k-1} T_ij (v_j . v_k),
+// from the tau and dot products the panel left in its block); then, with the blocks of G above the
+// diagonal (G summed over its partials in order), neighbouring diagonal blocks T1, T2 of side L = 16, 32,
+// 64 are joined: M = G12 T2, T12 = -T1 M, on the fp32 MFMA (16 x 16 x 4), M held below the diagonal, where T
+// is zero. Three levels of two products: the panel-by-panel form with one output element per thread
+// had seven, on a chain that every block waits for. The launch's other workgroups form V from Vt,
+// 64 x 64 elements each, meanwhile.
+__global__ __launch_bounds__(kQrTThreads) void qr_t_kernel(const QrTDesc* __restrict__ descs, int count) {
   __shared__ float Tl[kQrBlock][kQrBlock + 1];
   __shared__ float Gl[kQrBlock][kQrBlock + 1];
-  __shared__ float M1[kQrBlock - kQrPanel][kQrPanel + 1];
   __shared__ float Dl[kQrBlock][kQrPanel];  // row i: the panel's tau / dot-product row i
-  const QrTDesc& d = descs[blockIdx.x];
   const int t = threadIdx.x;
+  if (int(blockIdx.x) >= count) {
+    const int b = int(blockIdx.x) - count;
+    const QrTDesc& d = descs[find_desc(descs, count, b)];
+    const int lt = b - d.tile_begin, ti = lt >> 1, tj = lt & 1;  // rows 64 ti, columns 64 tj of V
+    const int c = t & 63, rr = t >> 6;
+    const g_cf32* Vt = (const g_cf32*)(d.Vt) + int64_t(64 * tj) * d.ldvt + 64 * ti;
+    g_f32* V = (g_f32*)(d.V) + int64_t(64 * ti) * kQrBlock + 64 * tj;
+#pragma unroll
+    for (int i = 0; i < 64; i += kQrTThreads / 64) Tl[rr + i][c] = Vt[int64_t(rr + i) * d.ldvt + c];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 64; i += kQrTThreads / 64) V[int64_t(rr + i) * kQrBlock + c] = Tl[c][rr + i];
+    return;
+  }
+  const QrTDesc& d = descs[blockIdx.x];
   g_f32* T = (g_f32*)(d.T);
   const g_cf32* G = (const g_cf32*)(d.G);
-  // thread t owns column j = t % 128 and rows i = t / 128 + 2 m (m < 64) of both matrices; the
-  // partials of G are summed with every load of one partial in flight together
-  constexpr int kM = kQrBlock * kQrBlock / 256;
+  // thread t owns column j = t % 128 and every fourth row of both matrices; the partials of G are
+  // summed with every load of one partial in flight together
+  constexpr int kM = kQrBlock * kQrBlock / kQrTThreads, kStep = kQrTThreads / kQrBlock;
   const int tj = t % kQrBlock, ti = t / kQrBlock;
   float g[kM];
 #pragma unroll
@@ -470,15 +476,16 @@ __global__ __launch_bounds__(256) void qr_t_kernel(const QrTDesc* __restrict__ d
   for (int q = 0; q < d.nG; ++q) {
     const g_cf32* Gq = G + int64_t(q) * kQrBlock * kQrBlock;
 #pragma unroll
-    for (int m = 0; m < kM; ++m) g[m] += Gq[(ti + 2 * m) * kQrBlock + tj];  // (every partial is whole)
+    for (int m = 0; m < kM; ++m) g[m] += Gq[(ti + kStep * m) * kQrBlock + tj];  // (every partial is whole)
   }
 #pragma unroll
   for (int m = 0; m < kM; ++m) {
-    const int i = ti + 2 * m;
+    const int i = ti + kStep * m;
     Tl[i][tj] = 0.0f;
     Gl[i][tj] = g[m];
   }
-  for (int idx = t; idx < kQrBlock * kQrPanel; idx += 256) {
+#pragma unroll
+  for (int idx = t; idx < kQrBlock * kQrPanel; idx += kQrTThreads) {
     const int i = idx / kQrPanel, jj = idx % kQrPanel;
     Dl[i][jj] = T[i * kQrBlock + (i / kQrPanel) * kQrPanel + jj];
   }
@@ -503,32 +510,40 @@ __global__ __launch_bounds__(256) void qr_t_kernel(const QrTDesc* __restrict__ d
     }
   }
   __syncthreads();
-  for (int s = 1; s < kQrBlock / kQrPanel; ++s) {
-    const int n0 = kQrPanel * s;
-    for (int idx = t; idx < n0 * kQrPanel; idx += 256) {
-      const int i = idx / kQrPanel, j = idx % kQrPanel;
-      float acc = 0.0f;
+  // one wave per 16 x 16 output tile; a lane's operands are row (column) lane % 16, k = lane / 16, its
+  // outputs rows 4 (lane / 16) .. + 3 of column lane % 16
+  const int lane = t & 63, w = t >> 6, lc = lane & 15, lk = lane >> 4;
+  for (int L = kQrPanel; L < kQrBlock; L *= 2) {
+    const int n = L / 16, per = n * n, tiles = kQrBlock / (2 * L) * per;
+    for (int tile = w; tile < tiles; tile += kQrTThreads / 64) {
+      const int b = tile / per * 2 * L, i0 = tile % per / n * 16, j0 = tile % n * 16;
+      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (int k = 0; k < j0 + 16; k += 4)  // T2 is upper triangular
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Gl[b + i0 + lc][b + L + k + lk], Tl[b + L + k + lk][b + L + j0 + lc],
+                                                   acc, 0, 0, 0);
 #pragma unroll
-      for (int k = 0; k < kQrPanel; ++k) acc += Gl[i][n0 + k] * Tl[n0 + k][n0 + j];
-      M1[i][j] = acc;
+      for (int r = 0; r < 4; ++r) Tl[b + L + i0 + 4 * lk + r][b + j0 + lc] = acc[r];
     }
     __syncthreads();
-    // T[0:n0, 0:n0] is upper triangular with zeros below (whole 16-row groups summed; four
-    // accumulators per group, added in a fixed order)
-    for (int idx = t; idx < n0 * kQrPanel; idx += 256) {
-      const int i = idx / kQrPanel, j = idx % kQrPanel;
-      float acc = 0.0f;
-      for (int k0 = (i / kQrPanel) * kQrPanel; k0 < n0; k0 += kQrPanel) {
-        float p[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int tile = w; tile < tiles; tile += kQrTThreads / 64) {
+      const int b = tile / per * 2 * L, i0 = tile % per / n * 16, j0 = tile % n * 16;
+      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (int k = i0; k < L; k += 4)  // so is T1
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Tl[b + i0 + lc][b + k + lk], Tl[b + L + k + lk][b + j0 + lc], acc, 0,
+                                                   0, 0);
 #pragma unroll
-        for (int k = 0; k < kQrPanel; ++k) p[k & 3] += Tl[i][k0 + k] * M1[k0 + k][j];
-        acc += (p[0] + p[1]) + (p[2] + p[3]);
-      }
-      Tl[i][n0 + j] = -acc;
+      for (int r = 0; r < 4; ++r) Tl[b + i0 + 4 * lk + r][b + L + j0 + lc] = -acc[r];
+    }
+    __syncthreads();
+    // M's place is read as T's zeros by the next level
+    for (int idx = t; idx < 64 * L; idx += kQrTThreads) {
+      const int p = idx / (L * L), i = idx % (L * L) / L, j = idx % L;
+      Tl[2 * L * p + L + i][2 * L * p + j] = 0.0f;
     }
     __syncthreads();
   }
-  for (int idx = t; idx < kQrBlock * kQrBlock; idx += 256) T[idx] = Tl[idx / kQrBlock][idx % kQrBlock];
+#pragma unroll
+  for (int m = 0; m < kM; ++m) T[(ti + kStep * m) * kQrBlock + tj] = Tl[ti + kStep * m][tj];
 }
 
 }  // namespace
@@ -565,9 +580,9 @@ hipError_t launch_qr_col(const QrColDesc* d, int count, int total_blocks, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_qr_t(const QrTDesc* d, int count, hipStream_t st) {
+hipError_t launch_qr_t(const QrTDesc* d, int count, int total_tiles, hipStream_t st) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(qr_t_kernel, dim3(count), dim3(256), 0, st, d);
+  hipLaunchKernelGGL(qr_t_kernel, dim3(count + total_tiles), dim3(kQrTThreads), 0, st, d, count);
   return hipGetLastError();
 }
 

@@ -210,7 +210,7 @@ inline int run(Build& b, char* ws, size_t desc_at, hipStream_t main_st, const Ru
       case kOpEye: e = launch_soap_eye(reinterpret_cast<SoapEyeDesc*>(dp), o.count, o.total, st); break;
       case kOpQrPanel: e = launch_qr_panel(reinterpret_cast<QrPanelDesc*>(dp), o.count, st); break;
       case kOpQrCol: e = launch_qr_col(reinterpret_cast<QrColDesc*>(dp), o.count, o.total, st); break;
-      case kOpQrT: e = launch_qr_t(reinterpret_cast<QrTDesc*>(dp), o.count, st); break;
+      case kOpQrT: e = launch_qr_t(reinterpret_cast<QrTDesc*>(dp), o.count, o.total, st); break;
       case kOpFork:
       case kOpJoin:
         break;

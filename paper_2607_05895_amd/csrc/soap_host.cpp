@@ -175,7 +175,6 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
         QrPanelDesc p{};
         p.At = b.ptr<float>(s->St);
         p.ld = s->dp;
-        p.V = b.ptr<float>(s->V);
         p.Vt = b.ptr<float>(s->Vt);
         p.T = b.ptr<float>(s->T);
         p.ldvt = s->dp;
@@ -190,7 +189,8 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
           QrColDesc q{};
           q.At = b.ptr<float>(s->St);
           q.ld = s->dp;
-          q.V = b.ptr<float>(s->V) + (c - j0) * kQrBlock + (c - j0);
+          q.Vt = b.ptr<float>(s->Vt) + (c - j0) * s->dp + (c - j0);
+          q.ldvt = s->dp;
           q.T = b.ptr<float>(s->T) + (c - j0) * kQrBlock + (c - j0);
           q.c = int32_t(c);
           q.rows = int32_t(s->d - c);
@@ -206,10 +206,11 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
     // (the previous block's update of the trailing columns beyond this block and of Q, on the
     // auxiliary stream, overlapped the panels above; it must end before W reads them)
     if (j0 > 0) b.join();
-    // G = V^T V in K chunks together with W = X V (both read only V), then the block's T
+    // G = V^T V in K chunks together with W = X V (both read only Vt), then the block's T, and V from Vt
     {
       std::vector<Prod> gp;
       std::vector<QrTDesc> td;
+      int tt = 0;
       for (QrSide* s : act) {
         const int64_t vrows = s->dp - j0;
         int32_t ng = 0;
@@ -219,11 +220,12 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
           gp.push_back(Prod{vt, vt, nullptr, g, s->dp, s->dp, 0, kQrBlock, kQrBlock, kQrBlock,
                             std::min<int64_t>(kQrGramChunk, vrows - k0), 1, 1.0f, 0.0f});
         }
-        td.push_back(QrTDesc{b.ptr<float>(s->T), b.ptr<float>(s->G), ng});
+        td.push_back(QrTDesc{b.ptr<float>(s->T), b.ptr<float>(s->G), b.ptr<float>(s->Vt), b.ptr<float>(s->V), s->dp, ng, tt});
+        tt += int(vrows / 64 * (kQrBlock / 64));
       }
       add_wx(b, act, j0, kW, gp);
       add_gemm(b, gp, kOpGemmX3);
-      b.op(kOpQrT, td, int(td.size()));
+      b.op(kOpQrT, td, tt);
     }
     // U = V T^T; X <- X - W U^T for the next block's columns first, then (on the auxiliary stream,
     // while the next block's panels run) for the rest of the trailing columns and for Q

@@ -21,8 +21,12 @@ constexpr int kQrPanelThreads = 512;  // one workgroup per panel (2 waves per SI
 constexpr int kQrRowsPerThread = 8;   // panel rows held in registers per thread
 constexpr int kQrMaxDim = kQrPanelThreads * kQrRowsPerThread;  // 4096
 constexpr int kQrColThreads = 256;    // in-block application: one workgroup per column
-constexpr int kQrColRows = kQrMaxDim / kQrColThreads;          // column entries per thread
-constexpr int kQrGramChunk = 256;     // K chunk of the split V^T V product
+constexpr int kQrColGroups = kQrMaxDim / (4 * kQrColThreads);  // groups of four column entries per thread
+constexpr int kQrTThreads = 512;      // block factor: one workgroup per block
+// K chunk of the split V^T V product: its launch also holds W = X V over the whole K, so chunks of a
+// quarter of the longest side end well before it, and the block factor sums at most 4 partials (12
+// partials of 256 took it 12 rounds of dependent loads on one CU)
+constexpr int kQrGramChunk = 1024;
 static_assert(kQrBlock == kShTile, "the block update runs on the Shampoo GEMM's tiles");
 
 // M <- beta1 M + (1 - beta1) G over the real m x n block, and the padded layouts the products read
@@ -83,14 +87,12 @@ struct SoapEyeDesc {
 // V, zero rows and columns of T).
 
 // Householder factorization of panel s of a block: A's columns [c, c + jb) (c = j0 + 16 s), rows
-// [c, d) (d - c <= kQrMaxDim; jb = min(16, d - c), 0 when c >= d). Writes the panel's 16 columns of V
-// and rows of Vt over all dp - j0 block rows (zero above the pivot rows, 1 on them, zero below d and
-// for columns >= jb) and its 16 x 16 factor into T's diagonal block s. A is only read (R is not
-// needed).
+// [c, d) (d - c <= kQrMaxDim; jb = min(16, d - c), 0 when c >= d). Writes the panel's 16 rows of
+// Vt over all dp - j0 block rows (zero above the pivot rows, 1 on them, zero below d and for columns
+// >= jb) and its 16 x 16 factor into T's diagonal block s. A is only read (R is not needed).
 struct QrPanelDesc {
   const float* At;
   int64_t ld;
-  float* V;
   float* Vt;
   float* T;
   int64_t ldvt;
@@ -103,20 +105,25 @@ struct QrPanelDesc {
 struct QrColDesc {
   float* At;
   int64_t ld;
-  const float* V;  // the panel's first column of V, at row c - j0 (row stride kQrBlock)
+  const float* Vt;  // the panel's first row of Vt, at entry c - j0
+  int64_t ldvt;
   const float* T;  // the panel's diagonal block of T (row stride kQrBlock)
   int32_t c, rows, ncols;
   int32_t tile_begin;  // first workgroup of this problem in the launch
 };
 
 // The block's factor T from its panels' diagonal blocks (already in T) and G = V^T V, given as nG
-// partial sums (consecutive 128 x 128 row-major): for s = 1 .. 7,
-// T[0:16s, 16s:16s+16] = -T[0:16s, 0:16s] G[0:16s, 16s:16s+16] T_s; zero below the diagonal blocks.
-// One workgroup per block.
+// partial sums (consecutive 128 x 128 row-major): for neighbouring diagonal blocks T1, T2 of side 16,
+// 32 and 64 the block between them is -T1 G12 T2; zero below the diagonal blocks.
+// One workgroup per block; then, one per 64 x 64 tile, V from Vt over the block's rows.
 struct QrTDesc {
   float* T;
   const float* G;
+  const float* Vt;
+  float* V;
+  int64_t ldvt;
   int32_t nG;
+  int32_t tile_begin;  // first tile of V of this problem, counted after the launch's `count` blocks
 };
 
 hipError_t launch_soap_prep(const SoapPrepDesc* d, int count, int total_tiles, float beta1,
@@ -126,6 +133,6 @@ hipError_t launch_soap_adam(const SoapAdamDesc* d, int count, int total_tiles, f
 hipError_t launch_soap_eye(const SoapEyeDesc* d, int count, int total_tiles, hipStream_t st);
 hipError_t launch_qr_panel(const QrPanelDesc* d, int count, hipStream_t st);
 hipError_t launch_qr_col(const QrColDesc* d, int count, int total_blocks, hipStream_t st);
-hipError_t launch_qr_t(const QrTDesc* d, int count, hipStream_t st);
+hipError_t launch_qr_t(const QrTDesc* d, int count, int total_tiles, hipStream_t st);
 
 }  // namespace mfsdp

@@ -104,6 +104,22 @@ def test_orthonormal_factor_random_sizes(native, d):
     np.testing.assert_allclose(qg.T @ qg, np.eye(d), atol=2e-5)
 
 
+@pytest.mark.parametrize("d", [1023, 1025, 1037, 2051, 3083])
+def test_orthonormal_factor_around_the_row_groups(native, d):
+    """Sizes around the 1024 rows of one group of the in-block application (each lane holds four
+    neighbouring rows, the last ones in part) and of one partial of V^T V (1 to 4 partials)."""
+    import torch
+    _say(f"orthonormal factor d={d}")
+    rng = np.random.default_rng(300 + d)
+    a = (rng.standard_normal((d, d)) + 0.5 * d ** 0.5 * np.eye(d)).astype(np.float32)
+    q = torch.empty((d, d), dtype=torch.float32, device="cuda")
+    native.orthonormal_factor_t(to_dev(a, synth.F32), q)
+    _sync()
+    qg = from_dev(q)
+    assert _sign_aligned_err(qg, OS.orthonormal_factor(a.astype(np.float64))) <= Q_TOL
+    np.testing.assert_allclose(qg.T @ qg, np.eye(d), atol=2e-5)
+
+
 def test_orthonormal_factor_rank_deficient_and_signs(native):
     """A rank-deficient input still gives an orthogonal factor with Q^T A upper triangular; on a
     full-rank input LAPACK's signs are reproduced (no column flips)."""
