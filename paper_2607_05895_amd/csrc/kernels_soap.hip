@@ -235,6 +235,7 @@ __global__ __launch_bounds__(kQrPanelThreads) void qr_panel_kernel(const QrPanel
   __shared__ float red[2][kQrPanelThreads / 64][kQrPanel];  // by column parity: the waves' sums
   __shared__ float piv[2][kQrPanel];                         // by column parity: the pivot row
   __shared__ float Ds[kQrPanel][kQrPanel];
+  __builtin_amdgcn_s_setprio(3);  // the updates of the auxiliary stream share its CU
   const QrPanelDesc& d = descs[blockIdx.x];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int jb = d.jb;
@@ -371,6 +372,7 @@ __global__ __launch_bounds__(kQrPanelThreads) void qr_panel_kernel(const QrPanel
 // the panel's block of T, and subtracts V_s y from its entries. The column is read and written once.
 __global__ __launch_bounds__(kQrColThreads) void qr_col_kernel(const QrColDesc* __restrict__ descs, int count) {
   __shared__ float red[kQrColThreads / 64][kQrPanel];
+  __builtin_amdgcn_s_setprio(3);
   const int e = find_desc(descs, count, blockIdx.x);
   const QrColDesc& d = descs[e];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = lane & (kQrPanel - 1);
@@ -398,8 +400,8 @@ __global__ __launch_bounds__(kQrColThreads) void qr_col_kernel(const QrColDesc* 
 #pragma unroll
       for (int k = 0; k < kQrPanel; ++k) {
         const f32x4 v = *(const g_cf32x4*)(Vt + int64_t(k) * d.ldvt + r);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) part[k] += v[j] * xr[i][j];
+        // (in pairs: four terms in a row made the factor's error a few per cent larger)
+        part[k] += (v[0] * xr[i][0] + v[1] * xr[i][1]) + (v[2] * xr[i][2] + v[3] * xr[i][3]);
       }
     }
   }
@@ -417,14 +419,14 @@ __global__ __launch_bounds__(kQrColThreads) void qr_col_kernel(const QrColDesc* 
   for (int i = 0; i < kQrColGroups; ++i) {
     const int r = 4 * (t + kQrColThreads * i);
     if (r < d.rows) {
-      f32x4 sub = {0.0f, 0.0f, 0.0f, 0.0f};
+      f32x4 sub[2] = {};
 #pragma unroll
       for (int k = 0; k < kQrPanel; ++k) {
         const f32x4 v = *(const g_cf32x4*)(Vt + int64_t(k) * d.ldvt + r);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) sub[j] += v[j] * y[k];
+        for (int j = 0; j < 4; ++j) sub[k & 1][j] += v[j] * y[k];
       }
-      const f32x4 out = xr[i] - sub;
+      const f32x4 out = xr[i] - (sub[0] + sub[1]);
       if (r + 4 <= d.rows) {
         *(g_f32x4*)(x + r) = out;
       } else {
@@ -449,10 +451,23 @@ __global__ __launch_bounds__(kQrTThreads) void qr_t_kernel(const QrTDesc* __rest
   __shared__ float Gl[kQrBlock][kQrBlock + 1];
   __shared__ float Dl[kQrBlock][kQrPanel];  // row i: the panel's tau / dot-product row i
   const int t = threadIdx.x;
+  __builtin_amdgcn_s_setprio(3);
   if (int(blockIdx.x) >= count) {
     const int b = int(blockIdx.x) - count;
     const QrTDesc& d = descs[find_desc(descs, count, b)];
-    const int lt = b - d.tile_begin, ti = lt >> 1, tj = lt & 1;  // rows 64 ti, columns 64 tj of V
+    int lt = b - d.tile_begin;
+    if (d.W) {
+      if (lt < kQrSumWgs) {
+        static_assert(kQrBlock * kQrBlock == 4 * kQrTThreads * kQrSumWgs, "four elements per thread");
+        const int o = 4 * (lt * kQrTThreads + t);
+        f32x4 s = *(const g_cf32x4*)((const g_cf32*)(d.W) + o);
+        for (int q = 1; q < d.nG; ++q) s += *(const g_cf32x4*)((const g_cf32*)(d.W) + q * kQrBlock * kQrBlock + o);
+        *(g_f32x4*)((g_f32*)(d.Ws) + o) = s;
+        return;
+      }
+      lt -= kQrSumWgs;
+    }
+    const int ti = lt >> 1, tj = lt & 1;  // rows 64 ti, columns 64 tj of V
     const int c = t & 63, rr = t >> 6;
     const g_cf32* Vt = (const g_cf32*)(d.Vt) + int64_t(64 * tj) * d.ldvt + 64 * ti;
     g_f32* V = (g_f32*)(d.V) + int64_t(64 * ti) * kQrBlock + 64 * tj;
@@ -517,22 +532,28 @@ __global__ __launch_bounds__(kQrTThreads) void qr_t_kernel(const QrTDesc* __rest
     const int n = L / 16, per = n * n, tiles = kQrBlock / (2 * L) * per;
     for (int tile = w; tile < tiles; tile += kQrTThreads / 64) {
       const int b = tile / per * 2 * L, i0 = tile % per / n * 16, j0 = tile % n * 16;
-      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-      for (int k = 0; k < j0 + 16; k += 4)  // T2 is upper triangular
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Gl[b + i0 + lc][b + L + k + lk], Tl[b + L + k + lk][b + L + j0 + lc],
-                                                   acc, 0, 0, 0);
+      f32x4 acc[4] = {};
+      for (int k = 0; k < j0 + 16; k += 16)  // T2 is upper triangular
 #pragma unroll
-      for (int r = 0; r < 4; ++r) Tl[b + L + i0 + 4 * lk + r][b + j0 + lc] = acc[r];
+        for (int q = 0; q < 4; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(Gl[b + i0 + lc][b + L + k + 4 * q + lk],
+                                                        Tl[b + L + k + 4 * q + lk][b + L + j0 + lc], acc[q], 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        Tl[b + L + i0 + 4 * lk + r][b + j0 + lc] = (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]);
     }
     __syncthreads();
     for (int tile = w; tile < tiles; tile += kQrTThreads / 64) {
       const int b = tile / per * 2 * L, i0 = tile % per / n * 16, j0 = tile % n * 16;
-      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-      for (int k = i0; k < L; k += 4)  // so is T1
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Tl[b + i0 + lc][b + k + lk], Tl[b + L + k + lk][b + j0 + lc], acc, 0,
-                                                   0, 0);
+      f32x4 acc[4] = {};
+      for (int k = i0; k < L; k += 16)  // so is T1
 #pragma unroll
-      for (int r = 0; r < 4; ++r) Tl[b + i0 + 4 * lk + r][b + L + j0 + lc] = -acc[r];
+        for (int q = 0; q < 4; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(Tl[b + i0 + lc][b + k + 4 * q + lk],
+                                                        Tl[b + L + k + 4 * q + lk][b + j0 + lc], acc[q], 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        Tl[b + i0 + 4 * lk + r][b + L + j0 + lc] = -((acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]));
     }
     __syncthreads();
     // M's place is read as T's zeros by the next level

@@ -50,24 +50,26 @@ using namespace mfsdp::shb;
 namespace {
 
 // One basis refresh problem: St (dp x dp) holds S^T (real block d x d) and is factored in place; Q
-// (dp x dp) accumulates the orthonormal factor (row-major, zero padding). V, Vt, T, G, U, Ws, Wq hold
-// the current block's reflectors, factor and products.
+// (dp x dp) accumulates the orthonormal factor (row-major, zero padding). V, Vt, T, G, Wn, U, Ws, Wq hold
+// the current block's reflectors, factor and products (Vt: even and odd blocks, since a block's panels run
+// beside the update by the one before; G, Wn: partials).
 struct QrSide {
   int64_t d = 0, dp = 0;
-  size_t St = 0, Q = 0, V = 0, Vt = 0, T = 0, G = 0, U = 0, Ws = 0, Wq = 0;
+  size_t St = 0, Q = 0, V = 0, Vt[2] = {}, T = 0, G = 0, Wn = 0, U = 0, Ws = 0, Wq = 0;
 };
 
-constexpr int64_t kQrMaxGram = (kQrMaxDim + kQrGramChunk - 1) / kQrGramChunk;  // partials of V^T V
+constexpr int64_t kQrMaxGram = (kQrMaxDim + kQrGramChunk - 1) / kQrGramChunk;  // partials of V^T V and of W
 
 void plan_qr_buffers(QrSide& s, Arena& a) {
   const size_t f = sizeof(float), col = size_t(s.dp) * kQrBlock * f, sq = size_t(kQrBlock) * kQrBlock * f;
   s.V = a.take(col);
-  s.Vt = a.take(col);
+  for (size_t& v : s.Vt) v = a.take(col);
   s.U = a.take(col);
   s.Ws = a.take(col);
   s.Wq = a.take(col);
   s.T = a.take(sq);
   s.G = a.take(size_t(kQrMaxGram) * sq);
+  s.Wn = a.take(size_t(kQrMaxGram) * sq);
 }
 
 // A grouped product before its tile offset is known (so that a launch can be ordered by cost).
@@ -106,14 +108,14 @@ void add_gemm(Build& b, std::vector<Prod> ps, OpKind kind = kOpGemm) {
 }
 
 // The block update's products for each side, over X = the trailing columns of S (rows [j0 + 128,
-// dp) of St) and X = Q's columns [j0, dp): kW appends W = X V (whole X) to ps; kXNext appends
-// X <- X - W U^T for St's next 128 rows (the next block's columns); kXRest appends it for the
-// remaining St rows and for Q.
-enum WxPart { kW, kXNext, kXRest };
+// dp) of St) and X = Q's columns [j0, dp): kWNext appends W = X V for St's next 128 rows (the next block's
+// columns) in partials of kQrGramChunk, kXNext X <- X - W U^T for them; kWRest and kXRest append the same
+// for the remaining St rows and for Q, W in one piece.
+enum WxPart { kWNext, kXNext, kWRest, kXRest };
 void add_wx(Build& b, const std::vector<QrSide*>& act, int64_t j0, WxPart part, std::vector<Prod>& ps) {
   for (QrSide* s : act) {
     const int64_t vrows = s->dp - j0;
-    const float* Vt = b.ptr<float>(s->Vt);
+    const float* Vt = b.ptr<float>(s->Vt[(j0 / kQrBlock) & 1]);
     const float* U = b.ptr<float>(s->U);
     const int64_t trail = s->dp - j0 - kQrBlock;  // St rows [j0 + 128, dp)
     const bool has_trail = trail > 0 && j0 + kQrBlock < s->d;
@@ -127,8 +129,13 @@ void add_wx(Build& b, const std::vector<QrSide*>& act, int64_t j0, WxPart part, 
     auto x = [&](float* X, const float* W, int64_t rows) {
       ps.push_back(Prod{W, U, X, X, kQrBlock, kQrBlock, s->dp, s->dp, rows, vrows, kQrBlock, 0, -1.0f, 1.0f});
     };
-    if (part == kW) {
-      if (has_trail) w(XS, WS, trail);
+    if (part == kWNext) {
+      float* wn = b.ptr<float>(s->Wn);
+      for (int64_t k0 = 0; has_trail && k0 < vrows; k0 += kQrGramChunk, wn += kQrBlock * kQrBlock)
+        ps.push_back(Prod{XS + k0, Vt + k0, nullptr, wn, s->dp, s->dp, 0, kQrBlock, kQrBlock, kQrBlock,
+                          std::min<int64_t>(kQrGramChunk, vrows - k0), 0, 1.0f, 0.0f});
+    } else if (part == kWRest) {
+      if (has_trail && trail > kQrBlock) w(XS + kQrBlock * s->dp, WS + kQrBlock * kQrBlock, trail - kQrBlock);
       w(XQ, WQ, s->dp);
     } else if (part == kXNext) {
       if (has_trail) x(XS, WS, kQrBlock);
@@ -163,6 +170,7 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
     b.op(kOpEye, ey, et);
   }
   for (int64_t j0 = 0; j0 < sides[0]->d; j0 += kQrBlock) {
+    const int odd = int((j0 / kQrBlock) & 1);
     std::vector<QrSide*> act;
     for (QrSide* s : sides)
       if (s->d > j0) act.push_back(s);
@@ -175,7 +183,7 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
         QrPanelDesc p{};
         p.At = b.ptr<float>(s->St);
         p.ld = s->dp;
-        p.Vt = b.ptr<float>(s->Vt);
+        p.Vt = b.ptr<float>(s->Vt[odd]);
         p.T = b.ptr<float>(s->T);
         p.ldvt = s->dp;
         p.j0 = int32_t(j0);
@@ -189,7 +197,7 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
           QrColDesc q{};
           q.At = b.ptr<float>(s->St);
           q.ld = s->dp;
-          q.Vt = b.ptr<float>(s->Vt) + (c - j0) * s->dp + (c - j0);
+          q.Vt = b.ptr<float>(s->Vt[odd]) + (c - j0) * s->dp + (c - j0);
           q.ldvt = s->dp;
           q.T = b.ptr<float>(s->T) + (c - j0) * kQrBlock + (c - j0);
           q.c = int32_t(c);
@@ -206,7 +214,19 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
     // (the previous block's update of the trailing columns beyond this block and of Q, on the
     // auxiliary stream, overlapped the panels above; it must end before W reads them)
     if (j0 > 0) b.join();
-    // G = V^T V in K chunks together with W = X V (both read only Vt), then the block's T, and V from Vt
+    // W = X V for what the next block does not hold: on the auxiliary stream, beside the chain of this
+    // block's factor and the next block's panels, which leaves most CUs idle (on the chain itself it
+    // was the longest launch after the panels)
+    {
+      std::vector<Prod> wr;
+      add_wx(b, act, j0, kWRest, wr);
+      b.fork();
+      b.aux = 1;
+      add_gemm(b, wr, kOpGemmX3);
+      b.aux = 0;
+    }
+    // G = V^T V and the next block's rows of W in K chunks (both read only Vt), then the block's T, V from
+    // Vt and W's sum
     {
       std::vector<Prod> gp;
       std::vector<QrTDesc> td;
@@ -215,15 +235,17 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
         const int64_t vrows = s->dp - j0;
         int32_t ng = 0;
         for (int64_t k0 = 0; k0 < vrows; k0 += kQrGramChunk, ++ng) {
-          const float* vt = b.ptr<float>(s->Vt) + k0;
+          const float* vt = b.ptr<float>(s->Vt[odd]) + k0;
           float* g = b.ptr<float>(s->G) + size_t(ng) * kQrBlock * kQrBlock;
           gp.push_back(Prod{vt, vt, nullptr, g, s->dp, s->dp, 0, kQrBlock, kQrBlock, kQrBlock,
                             std::min<int64_t>(kQrGramChunk, vrows - k0), 1, 1.0f, 0.0f});
         }
-        td.push_back(QrTDesc{b.ptr<float>(s->T), b.ptr<float>(s->G), b.ptr<float>(s->Vt), b.ptr<float>(s->V), s->dp, ng, tt});
-        tt += int(vrows / 64 * (kQrBlock / 64));
+        const bool next = vrows > kQrBlock && j0 + kQrBlock < s->d;
+        td.push_back(QrTDesc{b.ptr<float>(s->T), b.ptr<float>(s->G), b.ptr<float>(s->Vt[odd]), b.ptr<float>(s->V),
+                             next ? b.ptr<float>(s->Wn) : nullptr, b.ptr<float>(s->Ws), s->dp, ng, tt});
+        tt += int(vrows / 64 * (kQrBlock / 64)) + (next ? kQrSumWgs : 0);
       }
-      add_wx(b, act, j0, kW, gp);
+      add_wx(b, act, j0, kWNext, gp);
       add_gemm(b, gp, kOpGemmX3);
       b.op(kOpQrT, td, tt);
     }

@@ -23,10 +23,11 @@ constexpr int kQrMaxDim = kQrPanelThreads * kQrRowsPerThread;  // 4096
 constexpr int kQrColThreads = 256;    // in-block application: one workgroup per column
 constexpr int kQrColGroups = kQrMaxDim / (4 * kQrColThreads);  // groups of four column entries per thread
 constexpr int kQrTThreads = 512;      // block factor: one workgroup per block
-// K chunk of the split V^T V product: its launch also holds W = X V over the whole K, so chunks of a
-// quarter of the longest side end well before it, and the block factor sums at most 4 partials (12
-// partials of 256 took it 12 rounds of dependent loads on one CU)
-constexpr int kQrGramChunk = 1024;
+constexpr int kQrSumWgs = 8;          // workgroups that sum one block's partials of W
+// K chunk of the split products V^T V and W = X V of the next block's rows: a tile's serial K loop takes
+// 0.46 us per 16 k, a partial more costs the block factor's one CU a round of loads (12 partials of
+// 256 made it 46 us long)
+constexpr int kQrGramChunk = 512;
 static_assert(kQrBlock == kShTile, "the block update runs on the Shampoo GEMM's tiles");
 
 // M <- beta1 M + (1 - beta1) G over the real m x n block, and the padded layouts the products read
@@ -115,15 +116,18 @@ struct QrColDesc {
 // The block's factor T from its panels' diagonal blocks (already in T) and G = V^T V, given as nG
 // partial sums (consecutive 128 x 128 row-major): for neighbouring diagonal blocks T1, T2 of side 16,
 // 32 and 64 the block between them is -T1 G12 T2; zero below the diagonal blocks.
-// One workgroup per block; then, one per 64 x 64 tile, V from Vt over the block's rows.
+// One workgroup per block; then kQrSumWgs per block that sum the nG partials of the next block's rows of W
+// (if any) into Ws, and one per 64 x 64 tile that forms V from Vt over the block's rows.
 struct QrTDesc {
   float* T;
   const float* G;
   const float* Vt;
   float* V;
+  const float* W;  // partials (consecutive 128 x 128 row-major), or null
+  float* Ws;
   int64_t ldvt;
   int32_t nG;
-  int32_t tile_begin;  // first tile of V of this problem, counted after the launch's `count` blocks
+  int32_t tile_begin;  // first of this problem's other workgroups, counted after the launch's `count` blocks
 };
 
 hipError_t launch_soap_prep(const SoapPrepDesc* d, int count, int total_tiles, float beta1,
