@@ -276,6 +276,7 @@ struct Plan {
   std::vector<TileRef> jobs;   // the split problems' upper tiles (second pass)
   DescLayout dl{};
   size_t bytes = 0;
+  bool fine = false;           // every product on 128 x 128 tiles, matrices padded to 128
 };
 
 // Output tile of a product of the fp32 path: 64 x 64 where 128 x 128 tiles would leave more than half of the
@@ -342,6 +343,7 @@ Plan make_plan_tiles(int64_t count, int ns_dtype, ShapeAt shape_at, bool fine) {
     fine_tiles += ((p.r + kTileBF16Small - 1) / kTileBF16Small) * ((p.s + kTileBF16Small - 1) / kTileBF16Small);
   }
   fine = fine && bf && fine_tiles <= small_slots;
+  P.fine = fine;
   if (fine) {
     small_tiles = 0;
     for (NsPlan& p : shapes) {
@@ -426,12 +428,12 @@ Plan make_plan_tiles(int64_t count, int ns_dtype, ShapeAt shape_at, bool fine) {
   return P;
 }
 
-// (The fine plan's update schedule is a few KiB larger: entries that fit the allocation-free step's scratch
-// array without it keep the plan that fits.)
+// in_scratch: for the allocation-free step, whose scratch array has a fixed size. (The fine plan's update schedule
+// is a few KiB larger: entries that fit the array without it keep the plan that fits.)
 template <typename ShapeAt>
-Plan make_plan(int64_t count, int ns_dtype, ShapeAt shape_at) {
+Plan make_plan(int64_t count, int ns_dtype, ShapeAt shape_at, bool in_scratch = false) {
   Plan P = make_plan_tiles(count, ns_dtype, shape_at, true);
-  if (P.bytes > size_t(MFSDP_NOALLOC_SCRATCH_BYTES)) {
+  if (in_scratch && P.fine && P.bytes > size_t(MFSDP_NOALLOC_SCRATCH_BYTES)) {
     Plan coarse = make_plan_tiles(count, ns_dtype, shape_at, false);
     if (coarse.bytes <= size_t(MFSDP_NOALLOC_SCRATCH_BYTES)) return coarse;
   }
@@ -805,7 +807,7 @@ int muon_impl(const mfsdp_muon_entry* entries, int64_t count, const mfsdp_muon_h
   const Plan P = make_plan(count, hp->ns_dtype, [&](int64_t i, int64_t& m, int64_t& n) {
     m = entries[i].m;
     n = entries[i].n;
-  });
+  }, in_scratch);
   const std::vector<NsPlan>& plans = P.ns;
   const size_t need = P.bytes;
   if (in_scratch) {
