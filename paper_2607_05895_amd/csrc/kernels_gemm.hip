@@ -162,10 +162,11 @@ __global__ __launch_bounds__(NW * 64, TB == BT ? 1 : 2) void gemm_bf16_kernel(
       c.bj = r.bj;
       c.ks = r.ks;
       // a split Gram tile covers K range ks of nks (each range a whole number of 16 x 32 blocks:
-      // it starts nk * ks blocks further along every panel)
-      const int nks = (PK == kProdGram && dd.nks > 1) ? dd.nks : 1;
-      c.nk = dd.K / BKE / nks;
-      const int64_t k0 = int64_t(c.nk) * (nks > 1 ? r.ks : 0) * (kBlkRows * BKE);
+      // it starts kper * ks blocks further along every panel)
+      const int kb = (PK == kProdGram && dd.nks > 1) ? dd.kper * r.ks : 0;
+      c.nk = dd.K / BKE - kb;
+      if (PK == kProdGram && dd.nks > 1) c.nk = min(c.nk, dd.kper);
+      const int64_t k0 = int64_t(kb) * (kBlkRows * BKE);
       const uint16_t* P = static_cast<const uint16_t*>(dd.P[parity]);
       const uint16_t* Q = static_cast<const uint16_t*>(dd.Q[parity]);
       c.psrc = P + blk_index(int64_t(c.bi) * TB + drow, dchunk * 8, dd.ldp) + k0;

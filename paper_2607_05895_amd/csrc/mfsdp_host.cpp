@@ -344,16 +344,15 @@ Plan make_plan_tiles(int64_t count, int ns_dtype, ShapeAt shape_at, bool fine) {
   }
   fine = fine && bf && fine_tiles <= small_slots;
   P.fine = fine;
-  if (fine) {
-    small_tiles = 0;
+  const bool small_gram = bf && small_tiles <= small_slots;  // of the plan that is not fine
+  if (fine)
     for (NsPlan& p : shapes) {
       p.r_eff = round_up(p.r, kTileBF16Small);
       p.s_eff = round_up(p.s, kTileBF16Small);
     }
-  }
   size_t sched_bytes[3] = {0, 0, 0};
   for (int ph = 0; ph < 3; ++ph) {
-    const bool small = bf && (fine || (ph < 2 && small_tiles <= small_slots));
+    const bool small = bf && (fine || (ph < 2 && small_gram));
     const int tile = !bf ? h2_tile(shapes, ph) : small ? kTileBF16Small : kTileBF16;
     P.tile[ph] = tile;
     P.order[ph] = phase_order(shapes, ph);
@@ -371,15 +370,21 @@ Plan make_plan_tiles(int64_t count, int ns_dtype, ShapeAt shape_at, bool fine) {
     }
     if (ph == 0) {
       P.split.assign(size_t(count), 1);
-      if (ns_dtype == MFSDP_BF16) {
+      if (bf) {
+        // The K ranges follow from the matrices padded to 256 and the tile of the plan that is not fine, whichever
+        // plan this is: a range's sum is rounded on its own, so both plans give the same bits.
+        const int64_t ct = small_gram ? kTileBF16Small : kTileBF16;
         std::vector<int64_t> tl, kl;
-        for (const TileGrid& g : grids) tl.push_back(int64_t(g.tm) * (g.tm + 1) / 2);
-        for (int64_t c : cost) kl.push_back(c);
         size_t base = 0;
         for (const NsPlan& q : shapes) base += q.bytes;
-        const size_t part_bytes = size_t(tile) * tile * sizeof(float);
-        P.split = gram_splits(tl, kl, int64_t(base / 4 / part_bytes),
-                              small ? small_slots : int64_t(kGemmXcds) * kGemmSlots);
+        for (int k : P.order[0]) {
+          const NsPlan& q = shapes[size_t(k)];
+          const int64_t t = q.r_pad / ct;
+          tl.push_back(t * (t + 1) / 2);
+          kl.push_back(q.s_pad);
+        }
+        P.split = gram_splits(tl, kl, int64_t(base / 4 / size_t(ct * ct * int64_t(sizeof(float)))),
+                              small_gram ? small_slots : int64_t(kGemmXcds) * kGemmSlots);
       }
       if (!bf) {
         P.split = h2_splits(shapes, P.order[0], tile);
@@ -539,6 +544,8 @@ void fill_gemm_descs(const Plan& P, uint8_t* ws, const mfsdp_muon_hparams& hp, u
         d.tile_count = tr * (tr + 1) / 2;
         d.last_c = 1; d.last_ct = 0;
         d.nks = P.split[size_t(k)];
+        // (the last range ends at K, which the padded length that the ranges divide exceeds by less than a range)
+        d.kper = int(p.s_pad / kBlkCols / d.nks);
         d.part = d.nks > 1 && !h2 ? reinterpret_cast<float*>(ws + P.part[size_t(k)]) : nullptr;
         if (h2) {
           d.ldct = sum_begin;

@@ -194,6 +194,7 @@ struct GemmDesc {
   // other buffer, which is free then, and ldct is the problem's first block in the second pass.)
   float* part;
   int32_t nks;
+  int32_t kper;  // bf16 path: K steps of 32 per range (the last range may be shorter)
 };
 // Upper index of tile (bi, bj), bi <= bj, of a symmetric problem with tm tiles per side (row-major
 // over the upper triangle).

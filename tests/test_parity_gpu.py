@@ -284,6 +284,24 @@ def test_muon_small_and_full_size_tiles_give_the_same_bits(native):
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("shape,other", [((517, 2395), (1792, 3968)), ((3676, 1060), (1536, 3712)),
+                                         ((1319, 3796), (1664, 2688))])
+def test_muon_split_gram_ranges_do_not_depend_on_the_padding(native, shape, other):
+    """A matrix whose Gram contraction is split, stepped alone (all launches on 128 x 128 tiles, the matrix
+    padded to 128) and next to one that takes the update to 256 x 256 tiles (padded to 256) with as many K
+    ranges: the ranges begin at the same columns, so the outputs agree bit for bit."""
+    import torch
+    _say(f"muon split Gram ranges: {shape} alone and next to {other}")
+    rng = np.random.default_rng(5350)
+    specs = [synth.MuonSpec(*shape, "a"), synth.MuonSpec(*other, "b")]
+    tensors = [synth.random_muon_tensors(rng, e.m, e.n) for e in specs]
+    hp = synth.MuonHParams(lr=0.02, weight_decay=0.01)
+    alone = _run_muon(native, tensors[:1], specs[:1], hp)[0]
+    mixed = _run_muon(native, tensors, specs, hp)[0]
+    for x, y in zip(alone[:1] + alone[2:], mixed[:1] + mixed[2:]):  # param, momentum, update
+        assert torch.equal(x, y)
+
+
 # both sides of the 128 and 256 tile edges, tall and wide, n % 8 == 0, n % 4 == 0 and neither
 UPDATE_EDGES = [(129, 513), (513, 129), (260, 772), (772, 260), (127, 255), (255, 1), (264, 520), (520, 264)]
 
