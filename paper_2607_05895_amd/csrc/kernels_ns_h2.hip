@@ -32,6 +32,62 @@ __device__ __forceinline__ int find_entry(const D* descs, int count, int key) {
 
 constexpr int kGram = 0, kSquare = 1, kUpdate = 2, kApply = 3;
 
+// Scales. A product's result is split as it is stored, so its buffer's power-of-two scale 2^e must follow from
+// what is known before the product. Two ways, chosen by the host from the coefficients (h2_exponents):
+//   static  bounds on the singular values carried from step to step by the coefficients; no cost here.
+//   DYN     where those bounds leave the singular values behind (a step's polynomial may take the bound outside
+//           the next one's stable interval, from where it grows without end): bounds that start anew in
+//           every step from the data. For X with K columns and A = X X^T:
+//             |A_ij| <= min(K max |X|^2, lambda_max(A))               (|A_ij| <= the row norms' squares)
+//             |B'_ij| <= |a| + |b| max |A| + |c| ||A||_F max |A|       (|(A A)_ij| <= lambda_max(A) max |A|)
+//             |X'_ij| <= max |sqrt(y) (a + b y + c y^2)|, 0 <= y <= sqrt(||A A||_F)    (>= lambda_max(A))
+//           The maxima and the norms (sums of squares, in integers, so that their order does not matter) are
+//           taken by the epilogues, which costs 1 us per launch and 7 % at 768 x 3072; the last bound squared
+//           is the next step's lambda_max(A). They exceed the largest element by up to about r^(1/4) in the
+//           singular values (2^8 for X' at r = 4096): parts lose bits from 2^-28 of the bound down.
+struct TileStats {
+  float big = 0.0f, sq = 0.0f;  // largest |v| (NaN: kept) and sum of v^2 of the thread's elements
+  __device__ __forceinline__ void add(float v, float weight) {
+    const float m = fabsf(v);
+    big = m > big || m != m ? m : big;
+    sq += weight * (v * v);
+  }
+};
+// The workgroup's (NW waves') statistics of values held under the scale 2^e into the matrix's slots: the largest
+// |value| and, if sum is set, the sum of squares under the scale, rounded up, at most 2^45 per tile. lds: NW
+// x 8 bytes that nobody else uses.
+template <int NW>
+__device__ __forceinline__ void put_stats(TileStats s, int e, uint32_t* max_slot, unsigned long long* sum, float* lds) {
+  uint32_t big = __float_as_uint(s.big);
+  if (s.big != s.big) big = 0x7fc00000u;
+  float sq = s.sq;
+  for (int o = 32; o > 0; o >>= 1) {
+    big = max(big, uint32_t(__shfl_xor(int(big), o)));
+    sq += __shfl_xor(sq, o);
+  }
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    lds[2 * w] = __uint_as_float(big);
+    lds[2 * w + 1] = sq;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < NW; ++k) {
+      big = max(big, __float_as_uint(lds[2 * k]));
+      sq += lds[2 * k + 1];
+    }
+    if (max_slot) atomicMax(max_slot, __float_as_uint(ldexpf(__uint_as_float(big), -e)));
+    if (sum) atomicAdd(sum, sq < 0x1p45f ? (unsigned long long)(sq) + 1ull : 1ull << 45);
+  }
+}
+
+__device__ __forceinline__ NsH2State* ns_state(const float* scale) {
+  return reinterpret_cast<NsH2State*>(reinterpret_cast<uintptr_t>(scale) + kNsH2StateOffset);
+}
+__device__ __forceinline__ int gram_exponent(float lam, float xmax, int K) {
+  return ns_h2_exponent(fminf(lam, float(K) * xmax * xmax));
+}
+
 // One tile of one product per workgroup, 128 x 128 (4 waves of 64 x 64, 80 KiB of LDS) or 64 x 64 (32 x 32,
 // 64 KiB), two workgroups per CU. Bound by the matrix pipe and operand loads at large sizes (2048 x 8192, five
 // steps: 1.95 ms, 318 TFLOP/s of the 3 r^2 s + r^3 fp32 flop; the fp32 MFMA kernel before it 6.18 ms) and by
@@ -42,12 +98,12 @@ constexpr int kGram = 0, kSquare = 1, kUpdate = 2, kApply = 3;
 //   Gram, split   the fp32 partial tile of K range ks into CT (the iterate's other buffer, free here)
 //   update        X' in C and X'^T in CT
 //   apply         the parameter update (or the standalone output) in the parameter's orientation
-// alpha, beta, diag: the product's factors with the operands' scales taken in.
-template <typename Core, int PK>
+// ca, cb, cc: this step's a, b, c.
+template <typename Core, int PK, bool DYN>
 __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restrict__ descs, int count, int parity,
-                                                       float alpha, float beta, float diag) {
+                                                       float ca, float cb, float cc, NsH2Exponents he) {
   constexpr int T = Core::TM, PB = T / 16;  // tile side, panels per side
-  static_assert(Core::TM == Core::TN && Core::NST * Core::STAGE >= T * T * 4, "square tile, image in LDS");
+  static_assert(Core::TM == Core::TN && Core::NST * Core::STAGE >= T * T * 4 + 8 * Core::NW, "square tile, image in LDS");
   __shared__ __attribute__((aligned(1024))) uint8_t smem[Core::NST * Core::STAGE];
   const GemmDesc& d = descs[find_entry(descs, count, blockIdx.x)];
   int lt = blockIdx.x - d.tile_begin, ks = 0;
@@ -70,6 +126,22 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
   const int mp = d.M >> 4, np = d.N >> 4;      // panels of C's rows and columns
   const int r0 = bi * PB, c0 = bj * PB;
 
+  // DYN: the matrix's state (loaded here, beside the operands' first loads, and used after the loop)
+  NsH2State* st = ns_state(d.scale);
+  int ex = he.ex, ea = he.ea, eb = he.eb, eq_in = 0;
+  float lam = 0.0f, xmax = 0.0f, amax = 0.0f, a2 = 0.0f, q2 = 0.0f;
+  if constexpr (DYN) {
+    ex = st->ex[parity];
+    ea = st->ea;
+    eb = st->eb;
+    eq_in = st->eq;
+    lam = st->lam[parity];
+    xmax = __uint_as_float(st->xmax[parity]);
+    amax = __uint_as_float(st->amax);
+    a2 = float(st->a2);
+    q2 = float(st->q2);
+  }
+
   h2_f32x16 acc[Core::MI][Core::NI];
 #pragma unroll
   for (int i = 0; i < Core::MI; ++i)
@@ -89,6 +161,36 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
     Core::loop(ps, qs, nk, smem, w, lane, acc);
   }
 
+  // the result's scale 2^eo, and 2^ep that of acc
+  const bool first = bi == 0 && bj == 0 && ks == 0 && t == 0;
+  const int ep = PK == kGram ? 2 * ex : PK == kSquare ? 2 * ea : eb + ex;
+  int eo = PK == kGram ? ea : PK == kSquare ? eb : he.exn, eq = 0;
+  if constexpr (DYN && PK == kGram) {
+    eo = gram_exponent(lam, xmax, d.K);
+    if (first) {
+      st->q2 = 0;
+      st->ea = eo;
+    }
+  } else if constexpr (DYN && PK == kSquare) {
+    const float q = ldexpf(sqrtf(a2), -ea) * amax;  // bounds A A's elements
+    eq = ns_h2_exponent(q);
+    eo = ns_h2_exponent(fabsf(ca) + fabsf(cb) * amax + fabsf(cc) * q);
+    if (first) {
+      st->xmax[parity ^ 1] = 0;
+      st->eb = eo;
+      st->eq = eq;
+    }
+  } else if constexpr (DYN && PK == kUpdate) {
+    const float bound = ns_h2_next_bound(sqrtf(ldexpf(sqrtf(q2), -eq_in)), ca, cb, cc);
+    eo = ns_h2_exponent(bound);
+    if (first) {
+      st->amax = 0;
+      st->a2 = 0;
+      st->ex[parity ^ 1] = eo;
+      st->lam[parity ^ 1] = bound * bound;
+    }
+  }
+
   const int wm = w / Core::WN, wn = w % Core::WN;
   const int fr = lane & 31, fh = lane >> 5;
   // this lane's values: rows il(i), columns jl(j, g) .. + 3 of the tile
@@ -97,7 +199,7 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
   h2_lds* img = (h2_lds*)smem;
 
   if (PK == kGram && nks > 1) {
-    // (alpha is applied by the sum)
+    // (the scale is applied by the sum)
     g_f32* part = (g_f32*)d.CT[parity] + (int64_t(upper_index(bi, bj, d.tiles_n)) * nks + ks) * (T * T);
 #pragma unroll
     for (int i = 0; i < Core::MI; ++i)
@@ -136,8 +238,8 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
         for (int j = 0; j < Core::NI; ++j)
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            const f32x4 o = f32x4{alpha * acc[i][j][4 * g], alpha * acc[i][j][4 * g + 1], alpha * acc[i][j][4 * g + 2],
-                                  alpha * acc[i][j][4 * g + 3]};
+            const f32x4 o = f32x4{ldexpf(acc[i][j][4 * g], -ep), ldexpf(acc[i][j][4 * g + 1], -ep),
+                                  ldexpf(acc[i][j][4 * g + 2], -ep), ldexpf(acc[i][j][4 * g + 3], -ep)};
             if (!tall) {
               *(l_f32x4*)(img + at(il(i), jl(j, g))) = o;
             } else {
@@ -195,6 +297,9 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
       H2_WAIT_VMCNT(0);
       __syncthreads();
     }
+    const float weight = PK != kUpdate && bi != bj ? 2.0f : 1.0f;  // a tile off the diagonal is stored twice
+    const float kc = ldexpf(cc, eo - ep), kb = ldexpf(cb, eo - ea), diag = ldexpf(ca, eo);  // (square)
+    TileStats stats;
 #pragma unroll
     for (int i = 0; i < Core::MI; ++i)
 #pragma unroll
@@ -204,7 +309,11 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
           h2_lds* p = img + ((il(i) >> 4) * PB + (jl(j, g) >> 4)) * 1024 + (fr & 15) * 32 + (((g & 1) ^ sw) << 4) + fh * 8;
           float v[4];
 #pragma unroll
-          for (int k = 0; k < 4; ++k) v[k] = alpha * acc[i][j][4 * g + k];
+          for (int k = 0; k < 4; ++k) {
+            const float x = acc[i][j][4 * g + k];
+            v[k] = PK == kSquare ? kc * x : ldexpf(x, eo - ep);
+            if constexpr (DYN) stats.add(PK == kSquare ? ldexpf(x, eq - ep) : v[k], weight);
+          }
           if constexpr (PK == kSquare) {
             const h2_u32x2 eh = *(h2_lu2*)p, el = *(h2_lu2*)(p + 512);
             float e[4];
@@ -212,7 +321,7 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
             h2_join2(eh.y, el.y, e[2], e[3]);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-              v[k] += beta * e[k];
+              v[k] += kb * e[k];
               if (bi == bj && il(i) == jl(j, g) + k) v[k] += diag;
             }
           }
@@ -222,7 +331,12 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
           *(h2_lu2*)p = h2_u32x2{h0, h1};
           *(h2_lu2*)(p + 512) = h2_u32x2{l0, l1};
         }
-    __syncthreads();
+    if constexpr (DYN)  // (with a barrier of its own)
+      put_stats<Core::NW>(stats, eo, PK == kGram ? &st->amax : PK == kUpdate ? &st->xmax[parity ^ 1] : nullptr,
+                          PK == kGram ? &st->a2 : PK == kSquare ? &st->q2 : nullptr,
+                          reinterpret_cast<float*>(smem + T * T * 4));
+    else
+      __syncthreads();
     const H2BlockLane bl(lane);
     h2_gu16* C = (h2_gu16*)d.C[parity];
     h2_gu16* CT = (h2_gu16*)(PK == kUpdate ? d.CT[parity] : d.C[parity]);
@@ -243,10 +357,11 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
 // Sum of a split Gram product's partial tiles: one workgroup per 16-row slab of an upper tile. Thread t adds
 // the ranges' 8 consecutive columns 8 (t % (T / 8)) of row t / (T / 8) in order, and stores them and, through
 // LDS, the mirrored block rows.
-template <int T>
+template <int T, bool DYN>
 __global__ __launch_bounds__(2 * T) void ns_h2_sum_kernel(const GemmDesc* __restrict__ descs, int count, int parity,
-                                                          float alpha) {
+                                                          NsH2Exponents he) {
   __shared__ float tt[16][T + 1];
+  __shared__ float red[T / 16];
   int lo = 0, hi = count - 1;  // (ldct holds the problem's first block of this launch)
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -269,14 +384,21 @@ __global__ __launch_bounds__(2 * T) void ns_h2_sum_kernel(const GemmDesc* __rest
     a += *(g_cf32x4*)(part + int64_t(k) * (T * T));
     b += *(g_cf32x4*)(part + int64_t(k) * (T * T) + 4);
   }
+  NsH2State* st = ns_state(d.scale);
+  const int ep = 2 * (DYN ? st->ex[parity] : he.ex);
+  const int eo = DYN ? gram_exponent(st->lam[parity], __uint_as_float(st->xmax[parity]), d.K) : he.ea;
   float v[8];
+  TileStats stats;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    v[k] = alpha * a[k];
-    v[4 + k] = alpha * b[k];
+    v[k] = ldexpf(a[k], eo - ep);
+    v[4 + k] = ldexpf(b[k], eo - ep);
   }
 #pragma unroll
-  for (int k = 0; k < 8; ++k) tt[row][c8 * 8 + k] = v[k];
+  for (int k = 0; k < 8; ++k) {
+    tt[row][c8 * 8 + k] = v[k];
+    if constexpr (DYN) stats.add(v[k], bi != bj ? 2.0f : 1.0f);
+  }
   h2_gu16* C = (h2_gu16*)d.C[parity];
   const int64_t ldc = d.ldc;
   auto put = [&](int64_t r, int64_t k0) {
@@ -294,7 +416,8 @@ __global__ __launch_bounds__(2 * T) void ns_h2_sum_kernel(const GemmDesc* __rest
   };
   const int gc = bj * T + c8 * 8;
   if ((gc >> 4) < np && (gc >> 4) >= rp) put(rp * 16 + row, gc);
-  __syncthreads();
+  if constexpr (DYN) put_stats<T / 32>(stats, eo, &st->amax, &st->a2, red);  // (with a barrier of its own)
+  else __syncthreads();
   // mirror: row `c` of the tile's columns, its 8 values of slab rows 8 h .. 8 h + 7
   const int c = t >> 1, h = t & 1, gm = bj * T + c;
   if ((gm >> 4) >= np || (gm >> 4) <= rp) return;
@@ -306,7 +429,7 @@ __global__ __launch_bounds__(2 * T) void ns_h2_sum_kernel(const GemmDesc* __rest
 // First iterate: X_0 = scale u in both layouts, from the momentum pass's fp32 u (panel blocked, stored
 // orientation). One 64 x 64 tile per workgroup: a half wave converts a 16 x 16 block (8 consecutive columns
 // per lane), the transposed blocks through LDS. HBM bound: 4 B read and 8 B written per element.
-__global__ __launch_bounds__(256) void ns_h2_split_kernel(const PrepDesc* __restrict__ descs, int count, float s0) {
+__global__ __launch_bounds__(256) void ns_h2_split_kernel(const PrepDesc* __restrict__ descs, int count) {
   __shared__ float tile[64][65];
   const PrepDesc& d = descs[find_entry(descs, count, blockIdx.x)];
   const int lt = blockIdx.x - d.tile_begin;
@@ -315,8 +438,17 @@ __global__ __launch_bounds__(256) void ns_h2_split_kernel(const PrepDesc* __rest
   // partial sums)
   const int64_t tiles = int64_t(d.tiles_m) * d.tiles_n;
   uint8_t* x_out = static_cast<uint8_t*>(d.d_out) - tiles * (64 * 64 * 4);
-  const float s = s0 * *reinterpret_cast<const float*>(reinterpret_cast<const uint8_t*>(d.partials) +
-                                                       ((tiles * 4 + 255) & ~int64_t(255)));
+  const float* scale = reinterpret_cast<const float*>(reinterpret_cast<const uint8_t*>(d.partials) +
+                                                      ((tiles * 4 + 255) & ~int64_t(255)));
+  const float s = ldexpf(*scale, kNsH2First);
+  if (lt == 0 && threadIdx.x == 0) {
+    NsH2State* st = ns_state(scale);
+    st->ex[0] = kNsH2First;
+    st->lam[0] = 1.0f;                       // ||X_0||_F <= 1
+    st->xmax[0] = __float_as_uint(1.0f);
+    st->amax = 0;
+    st->a2 = 0;
+  }
   const int t = threadIdx.x, l = t & 31, row = l & 15, ch = l >> 4;
   auto put = [&](void* base, int64_t r, int64_t k0, int64_t ld, const float (&v)[8]) {
     h2_u32x4 h, q;
@@ -359,40 +491,54 @@ __global__ __launch_bounds__(256) void ns_h2_split_kernel(const PrepDesc* __rest
   }
 }
 
-template <typename Core>
-void launch_products(const GemmDesc* d, int count, int tiles, int product, int parity, float alpha, float beta,
-                     float diag, hipStream_t st) {
+template <typename Core, bool DYN>
+void launch_products(const GemmDesc* d, int count, int tiles, int product, int parity, float ca, float cb, float cc,
+                     const NsH2Exponents& he, hipStream_t st) {
   switch (product) {
-    case kGram: hipLaunchKernelGGL((ns_h2_kernel<Core, kGram>), dim3(tiles), dim3(256), 0, st, d, count, parity, alpha, beta, diag); break;
-    case kSquare: hipLaunchKernelGGL((ns_h2_kernel<Core, kSquare>), dim3(tiles), dim3(256), 0, st, d, count, parity, alpha, beta, diag); break;
-    case kUpdate: hipLaunchKernelGGL((ns_h2_kernel<Core, kUpdate>), dim3(tiles), dim3(256), 0, st, d, count, parity, alpha, beta, diag); break;
-    default: hipLaunchKernelGGL((ns_h2_kernel<Core, kApply>), dim3(tiles), dim3(256), 0, st, d, count, parity, alpha, beta, diag); break;
+    case kGram: hipLaunchKernelGGL((ns_h2_kernel<Core, kGram, DYN>), dim3(tiles), dim3(256), 0, st, d, count, parity, ca, cb, cc, he); break;
+    case kSquare: hipLaunchKernelGGL((ns_h2_kernel<Core, kSquare, DYN>), dim3(tiles), dim3(256), 0, st, d, count, parity, ca, cb, cc, he); break;
+    case kUpdate: hipLaunchKernelGGL((ns_h2_kernel<Core, kUpdate, DYN>), dim3(tiles), dim3(256), 0, st, d, count, parity, ca, cb, cc, he); break;
+    default: hipLaunchKernelGGL((ns_h2_kernel<Core, kApply, DYN>), dim3(tiles), dim3(256), 0, st, d, count, parity, ca, cb, cc, he); break;
   }
+}
+template <int T, bool DYN>
+void launch_sum(const GemmDesc* d, int count, int blocks, int parity, const NsH2Exponents& he, hipStream_t st) {
+  hipLaunchKernelGGL((ns_h2_sum_kernel<T, DYN>), dim3(blocks), dim3(2 * T), 0, st, d, count, parity, he);
 }
 
 }  // namespace
 
-hipError_t launch_ns_h2(const GemmDesc* d, int count, int total_tiles, int product, int parity, float alpha,
-                        float beta, float diag, int tile, hipStream_t st) {
+hipError_t launch_ns_h2(const GemmDesc* d, int count, int total_tiles, int product, int parity, float ca, float cb,
+                        float cc, const NsH2Exponents* he, int tile, hipStream_t st) {
+  using Small = H2Core<2, 2, 1, 1, 8>;
+  using Large = H2Core<2, 2, 2, 2, 5>;
+  const NsH2Exponents none{};
   if (total_tiles <= 0) return hipSuccess;
-  if (tile == 64)
-    launch_products<H2Core<2, 2, 1, 1, 8>>(d, count, total_tiles, product, parity, alpha, beta, diag, st);
-  else
-    launch_products<H2Core<2, 2, 2, 2, 5>>(d, count, total_tiles, product, parity, alpha, beta, diag, st);
+  if (tile == 64) {
+    if (he) launch_products<Small, false>(d, count, total_tiles, product, parity, ca, cb, cc, *he, st);
+    else launch_products<Small, true>(d, count, total_tiles, product, parity, ca, cb, cc, none, st);
+  } else {
+    if (he) launch_products<Large, false>(d, count, total_tiles, product, parity, ca, cb, cc, *he, st);
+    else launch_products<Large, true>(d, count, total_tiles, product, parity, ca, cb, cc, none, st);
+  }
   return hipGetLastError();
 }
-hipError_t launch_ns_h2_sum(const GemmDesc* d, int count, int blocks, int parity, float alpha, int tile,
+hipError_t launch_ns_h2_sum(const GemmDesc* d, int count, int blocks, int parity, const NsH2Exponents* he, int tile,
                             hipStream_t st) {
+  const NsH2Exponents none{};
   if (blocks <= 0) return hipSuccess;
-  if (tile == 64)
-    hipLaunchKernelGGL(ns_h2_sum_kernel<64>, dim3(blocks), dim3(128), 0, st, d, count, parity, alpha);
-  else
-    hipLaunchKernelGGL(ns_h2_sum_kernel<128>, dim3(blocks), dim3(256), 0, st, d, count, parity, alpha);
+  if (tile == 64) {
+    if (he) launch_sum<64, false>(d, count, blocks, parity, *he, st);
+    else launch_sum<64, true>(d, count, blocks, parity, none, st);
+  } else {
+    if (he) launch_sum<128, false>(d, count, blocks, parity, *he, st);
+    else launch_sum<128, true>(d, count, blocks, parity, none, st);
+  }
   return hipGetLastError();
 }
-hipError_t launch_ns_h2_split(const PrepDesc* d, int count, int total_tiles, float s0, hipStream_t st) {
+hipError_t launch_ns_h2_split(const PrepDesc* d, int count, int total_tiles, hipStream_t st) {
   if (total_tiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(ns_h2_split_kernel, dim3(total_tiles), dim3(256), 0, st, d, count, s0);
+  hipLaunchKernelGGL(ns_h2_split_kernel, dim3(total_tiles), dim3(256), 0, st, d, count);
   return hipGetLastError();
 }
 

@@ -460,32 +460,32 @@ std::vector<double> step_coeffs(double a, double b, double c, int steps, const d
 // the fp32 accumulators); otherwise a separate apply pass reads the iterate.
 bool apply_fused(int steps) { return steps >= 1; }
 
-// Scales of the fp32 path's split-fp16 buffers, step by step. Every buffer's elements are bounded by a bound
-// on its singular values: sigma of X (1 at first: the Frobenius norm), sigma^2 of A, max |a + b y + c y^2| over
-// [0, sigma^2] of B', max |x (a + b x^2 + c x^4)| over [0, sigma] of the next X (with 1 % for rounding). A
-// buffer's scale is the power of two that takes its bound to at most 2^14 (2^15 for X_0), a factor of
-// four (two) inside fp16's range.
-struct H2Scales {
-  double x, a, b, xn;
-};
-constexpr double kH2First = 32768.0;
-std::vector<H2Scales> h2_scales(const double* coeffs, int steps) {
-  auto pow2 = [](double bound) {
-    if (!(bound > 0.0) || !std::isfinite(bound)) return 1.0;
-    return std::exp2(std::min(100.0, std::max(-100.0, std::floor(14.0 - std::log2(bound)))));
-  };
-  std::vector<H2Scales> s;
-  double sigma = 1.0, sx = kH2First;
+// The fp32 path's scales, step by step, where bounds from the coefficients alone serve; else none (the kernels
+// then form them from the data). Every buffer's elements are bounded by a bound on its singular values: sigma of X
+// (1 at first: the Frobenius norm), sigma^2 of A, max |a + b y + c y^2| over [0, sigma^2] of B', max |x (a + b x^2 +
+// c x^4)| over [0, sigma] of the next X (with 1 % for rounding). A buffer's exponent takes its bound to at
+// most 2^14, a factor of four inside fp16's range (2^15 and two for X_0).
+// slack bounds by how much the true singular values can have shrunk against sigma since the start: a step moves
+// every singular value by at least min |a + b y + c y^2| and the bound by its ratio. The fixed triple reaches 2^3.4
+// in five steps; a schedule whose bounds run away, or that may cancel singular values, passes 2^10 at once.
+constexpr double kH2MaxSlack = 1024.0;
+std::vector<NsH2Exponents> h2_exponents(const double* coeffs, int steps) {
+  auto exponent = [](double bound) { return int(std::min(100.0, std::max(-100.0, std::floor(14.0 - std::log2(bound))))); };
+  std::vector<NsH2Exponents> s;
+  double sigma = 1.0, slack = 1.0;
+  int ex = kNsH2First;
   for (int k = 0; k < steps; ++k) {
     const double a = coeffs[3 * k], b = coeffs[3 * k + 1], c = coeffs[3 * k + 2];
     auto q = [&](double y) { return std::fabs(a + b * y + c * y * y); };
     auto p = [&](double y) { return std::sqrt(y) * q(y); };
     const double y1 = sigma * sigma;
-    double bb = std::max(q(0.0), q(y1)), bx = p(y1);
+    double bb = std::max(q(0.0), q(y1)), bx = p(y1), low = std::min(q(0.0), q(y1));
+    if ((a > 0.0) != (a + b * y1 + c * y1 * y1 > 0.0)) low = 0.0;  // a zero between
     auto at = [&](double y) {
       if (!(y > 0.0 && y < y1)) return;
       bb = std::max(bb, q(y));
       bx = std::max(bx, p(y));
+      low = (a > 0.0) != (a + b * y + c * y * y > 0.0) ? 0.0 : std::min(low, q(y));
     };
     if (c != 0.0) {
       at(-b / (2.0 * c));
@@ -497,9 +497,12 @@ std::vector<H2Scales> h2_scales(const double* coeffs, int steps) {
     } else if (b != 0.0) {
       at(-a / (3.0 * b));
     }
-    sigma = 1.01 * bx;
-    H2Scales h{sx, pow2(y1), pow2(bb), pow2(sigma)};
-    sx = h.xn;
+    const double next = 1.01 * bx;
+    slack *= next / (sigma * low);
+    if (!(slack <= kH2MaxSlack) || !(bb > 1e-18 && bb < 1e18) || !(next > 1e-18 && next < 1e18)) return {};
+    sigma = next;
+    NsH2Exponents h{ex, exponent(y1), exponent(bb), exponent(sigma)};
+    ex = h.exn;
     s.push_back(h);
   }
   return s;
@@ -661,29 +664,24 @@ int enqueue_pipeline(const Plan& P, uint8_t* ws, int slot, int steps, const doub
   if ((rc = record(events, 1, st))) return rc;
   auto descs = [&](int ph) { return reinterpret_cast<const GemmDesc*>(ws + dl.off_gemm[ph]); };
   if (ns_dtype == MFSDP_F32 && steps > 0) {
-    e = launch_ns_h2_split(reinterpret_cast<const PrepDesc*>(ws + dl.off_prep), count, prep_tiles, float(kH2First), st);
+    e = launch_ns_h2_split(reinterpret_cast<const PrepDesc*>(ws + dl.off_prep), count, prep_tiles, st);
     if (e != hipSuccess) return hip_fail(e, "split launch");
-    const std::vector<H2Scales> sc = h2_scales(coeffs, steps);
     const bool split = std::any_of(P.split.begin(), P.split.end(), [](int f) { return f > 1; });
     int sum_blocks = 0;
     for (const NsPlan& p : P.ns) {
       const int tr = int((p.r_pad + P.tile[0] - 1) / P.tile[0]);
       sum_blocks += tr * (tr + 1) / 2 * (P.tile[0] / 16);
     }
+    const std::vector<NsH2Exponents> hs = h2_exponents(coeffs, steps);
     for (int k = 0; k < steps; ++k) {
-      const H2Scales& s = sc[size_t(k)];
-      const double* c = coeffs + 3 * k;
+      const NsH2Exponents* he = hs.empty() ? nullptr : &hs[size_t(k)];
+      const float ca = float(coeffs[3 * k]), cb = float(coeffs[3 * k + 1]), cc = float(coeffs[3 * k + 2]);
       const int par = k & 1;
-      const bool last = k == steps - 1;
-      const float ga = float(s.a / (s.x * s.x));
-      e = launch_ns_h2(descs(0), count, P.tiles[0], 0, par, ga, 0.0f, 0.0f, P.tile[0], st);
-      if (e == hipSuccess && split) e = launch_ns_h2_sum(descs(0), count, sum_blocks, par, ga, P.tile[0], st);
-      if (e == hipSuccess)
-        e = launch_ns_h2(descs(1), count, P.tiles[1], 1, par, float(c[2] * s.b / (s.a * s.a)), float(c[1] * s.b / s.a),
-                         float(c[0] * s.b), P.tile[1], st);
-      if (e == hipSuccess)
-        e = launch_ns_h2(descs(2), count, P.tiles[2], last ? 3 : 2, par, float((last ? 1.0 : s.xn) / (s.b * s.x)), 0.0f,
-                         0.0f, P.tile[2], st);
+      for (int ph = 0; ph < 3 && e == hipSuccess; ++ph) {
+        const int product = ph == 2 && k == steps - 1 ? 3 : ph;
+        e = launch_ns_h2(descs(ph), count, P.tiles[ph], product, par, ca, cb, cc, he, P.tile[ph], st);
+        if (e == hipSuccess && ph == 0 && split) e = launch_ns_h2_sum(descs(0), count, sum_blocks, par, he, P.tile[0], st);
+      }
       if (e != hipSuccess) return hip_fail(e, "NS GEMM launch");
     }
   }

@@ -196,6 +196,48 @@ struct GemmDesc {
   int32_t nks;
   int32_t kper;  // bf16 path: K steps of 32 per range (the last range may be shorter)
 };
+// The fp32 path's scales (kernels_ns_h2.hip): a buffer's elements are held times 2^e, e from a bound on them. One
+// step's exponents of X, A, B' and X' where the host's bounds hold for every matrix; else one matrix's state,
+// formed on the device step by step, which lies kNsH2StateOffset bytes after the matrix's norm scale (the pairs
+// alternate with the iterate's buffers).
+struct NsH2Exponents {
+  int32_t ex, ea, eb, exn;
+};
+constexpr size_t kNsH2StateOffset = 64;
+constexpr int kNsH2First = 15;  // X_0's exponent: its elements are at most 1
+struct NsH2State {
+  int32_t ex[2], ea, eb, eq;  // exponents of X, A, B' and of A A in q2
+  float lam[2];               // bound on lambda_max(A) of the step that reads this X
+  uint32_t xmax[2], amax;     // largest |X|, |A| (bit patterns)
+  unsigned long long a2, q2;  // sums of squares of A's and A A's elements, each times 2^e
+};
+static_assert(kNsH2StateOffset + sizeof(NsH2State) <= 256, "the norm scale's block");
+// The exponent under which a buffer with this bound (>= 0, inf or NaN: unknown) stays below 2^14, a factor of four
+// inside fp16's range.
+__host__ __device__ __forceinline__ int ns_h2_exponent(float bound) {
+  return 140 - int(__builtin_bit_cast(uint32_t, bound) >> 23 & 0xff);
+}
+// Bound on the singular values (and so the elements) of X' = (a + b A + c A^2) X where lam bounds A's eigenvalues:
+// the largest |sqrt(y) (a + b y + c y^2)| over [0, lam], at its end or where a + 3 b y + 5 c y^2 = 0; 1 % for
+// rounding.
+__host__ __device__ __forceinline__ float ns_h2_next_bound(float lam, float a, float b, float c) {
+  const float end = 1.001f * lam;
+  float best = 0.0f;
+  auto at = [&](float y) {
+    if (!(y > 0.0f && y <= end)) return;
+    const float p = __builtin_sqrtf(y) * __builtin_fabsf(a + y * (b + c * y));
+    if (!(p <= best)) best = p;  // (keeps a NaN)
+  };
+  at(end);
+  if (!(end < 3.0e38f)) return end;
+  const float disc = 9.0f * b * b - 20.0f * a * c;
+  if (disc >= 0.0f) {  // the roots q / (10 c) and 2 a / q, neither by a difference of like numbers
+    const float q = -3.0f * b - __builtin_copysignf(__builtin_sqrtf(disc), b);
+    if (c != 0.0f) at(q / (10.0f * c));
+    if (q != 0.0f) at(2.0f * a / q);
+  }
+  return 1.01f * best;
+}
 // Upper index of tile (bi, bj), bi <= bj, of a symmetric problem with tm tiles per side (row-major
 // over the upper triangle).
 __host__ __device__ constexpr int upper_index(int bi, int bj, int tm) { return bi * tm - bi * (bi - 1) / 2 + (bj - bi); }
@@ -236,14 +278,15 @@ hipError_t launch_gemm(const GemmDesc* d_descs, int total_tiles, const TileRef* 
                        int parity, int first_step, int last_step, float ca, float cb, float cc, int tile,
                        hipStream_t st);
 // The fp32 path's products (on split fp16): one workgroup per tile (and K range) in the order of the
-// descriptors; alpha, beta and diag take in the operands' scales. tile: 128 or 64.
-hipError_t launch_ns_h2(const GemmDesc* d, int count, int total_tiles, int product, int parity, float alpha,
-                        float beta, float diag, int tile, hipStream_t st);
+// descriptors; ca, cb, cc: the step's a, b, c; he: its scales, or null for scales formed on the device. tile: 128 or
+// 64.
+hipError_t launch_ns_h2(const GemmDesc* d, int count, int total_tiles, int product, int parity, float ca, float cb,
+                        float cc, const NsH2Exponents* he, int tile, hipStream_t st);
 // Second pass of a split Gram product there (blocks: tile / 16 per upper tile of every problem).
-hipError_t launch_ns_h2_sum(const GemmDesc* d, int count, int blocks, int parity, float alpha, int tile,
+hipError_t launch_ns_h2_sum(const GemmDesc* d, int count, int blocks, int parity, const NsH2Exponents* he, int tile,
                             hipStream_t st);
-// X_0 = s0 scale u in both layouts from the momentum pass's u.
-hipError_t launch_ns_h2_split(const PrepDesc* d, int count, int total_tiles, float s0, hipStream_t st);
+// X_0 = scale u in both layouts from the momentum pass's u; starts the matrix's NsH2State.
+hipError_t launch_ns_h2_split(const PrepDesc* d, int count, int total_tiles, hipStream_t st);
 hipError_t launch_apply(const ApplyDesc* d_descs, int count, int total_tiles, int ns_dtype,
                         hipStream_t st);
 // The second pass of a split Gram product: for each job (problem e in the Gram launch's order,

@@ -519,6 +519,50 @@ def test_ns_schedule_matches_oracle(native, ns_dtype, tol, shape, which):
     assert err <= tol, err
 
 
+# Schedules whose worst-case bounds on the singular values leave the true ones behind: a minimax schedule (each
+# polynomial is optimal on the interval that the last one leaves, and grows fast beyond it), factors
+# before the fixed triple that the Frobenius norm makes room for, and far scales undone again.
+MINIMAX_SCHEDULE = [(8.2872, -23.5959, 17.3004), (4.1071, -2.9478, 0.5448), (3.9487, -2.9089, 0.5518),
+                    (3.3184, -2.4885, 0.5100), (2.3007, -1.6689, 0.4188)]
+WIDE_SCHEDULES = {"minimax": MINIMAX_SCHEDULE, "minimax_polished": MINIMAX_SCHEDULE + [(1.875, -1.25, 0.375)] * 2,
+                  "factor_first": [(2.0, 0.0, 0.0)] * 2 + [(A, B, C)] * 5,
+                  "down_and_up": [(1e-9, 0.0, 0.0), (1e9, 0.0, 0.0)] + [(A, B, C)] * 5,
+                  "up_and_down": [(1e7, 0.0, 0.0), (1e-7, 0.0, 0.0)] + [(A, B, C)] * 5,
+                  "to_zero": [(A, B, C), (0.0, 0.0, 0.0)]}
+
+
+@pytest.mark.parametrize("shape", [(128, 256), (513, 257), (64, 80), (20, 3000), (1024, 1500)])
+@pytest.mark.parametrize("which", sorted(WIDE_SCHEDULES))
+def test_ns_f32_schedules_with_loose_bounds(native, shape, which):
+    """The fp32 path holds its iterates in scaled parts: the scales follow the data, so a schedule that is
+    stable for the true singular values stays accurate. Bar: four times the largest error that plain fp32
+    arithmetic shows on these inputs (4.6e-6, the minimax schedule on 128 x 256)."""
+    import torch
+    m, n = shape
+    sched = WIDE_SCHEDULES[which]
+    _say(f"ns f32 schedule {which} {m}x{n}")
+    x = np.random.default_rng(315 + m + n).standard_normal((m, n), dtype=np.float32)
+    out = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    native.newton_schulz_schedule_t(to_dev(x, synth.F32), out, sched, 1e-7, "f32")
+    _sync()
+    ref = oracle.newton_schulz(x, A, B, C, len(sched), schedule=sched)
+    if which == "to_zero":
+        assert not np.any(from_dev(out))
+        return
+    err = rel_fro(from_dev(out), ref)
+    assert err <= 2e-5, err
+
+
+def test_muon_f32_with_minimax_schedule_matches_oracle(native):
+    _say("muon f32, minimax schedule")
+    rng = np.random.default_rng(335)
+    specs = [synth.MuonSpec(m, n, f"s{m}x{n}", synth.F32, synth.F32) for (m, n) in [(256, 512), (700, 100), (384, 384)]]
+    tensors = [synth.random_muon_tensors(rng, e.m, e.n, e.param_dtype, e.grad_dtype) for e in specs]
+    hp = synth.MuonHParams(lr=0.02, weight_decay=0.01, ns_steps=5, ns_schedule=tuple(MINIMAX_SCHEDULE), ns_dtype="f32")
+    dev = _run_muon(native, tensors, specs, hp)
+    _check_muon(tensors, specs, dev, hp, 2e-5)
+
+
 @pytest.mark.parametrize("ns_dtype", ["bf16", "f32"])
 def test_ns_constant_schedule_is_bitwise_the_fixed_triple(native, ns_dtype):
     import torch
