@@ -275,10 +275,10 @@ size_t mfsdp_shampoo_workspace_size(const mfsdp_shampoo_entry* entries, int64_t 
 
 /* One Shampoo step on every entry (host array of count entries), enqueued on `stream`
  * (hipStream_t, NULL = default stream); no host synchronisation. Statistics update, inverse
- * fourth roots (on refresh), U = P_L G P_R and the parameter update, every product at fp32 accuracy
- * on the 16-bit MFMA (each fp32 operand split into two scaled fp16 parts, fp32 accumulation; products
- * of a bf16 gradient with itself in bf16). With stored preconditioners part of the work may run on the
- * auxiliary stream that mfsdp_soap_step describes, joined before the call returns. The workspace (device, 256-byte aligned, >= the size query) must not be in use by
+ * fourth roots (on refresh), U = P_L G P_R and the parameter update. The products outside the roots run at fp32
+ * accuracy on the bf16 MFMA for operands of any range (each fp32 operand split into three bf16 parts, a bf16
+ * gradient as it is, fp32 accumulation); for the roots see mfsdp_inverse_root. The workspace (device, 256-byte
+ * aligned, >= the size query) must not be in use by
  * another call still running. Returns MFSDP_OK, MFSDP_E_INVALID, MFSDP_E_WORKSPACE or
  * MFSDP_E_HIP; on an argument error nothing is enqueued. At most 4096 entries per call. */
 int mfsdp_shampoo_step(const mfsdp_shampoo_entry* entries, int64_t count,

@@ -53,12 +53,6 @@ __device__ __forceinline__ void h2_split2(float a, float b, uint32_t& hi, uint32
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(h2_f32x2{kH2LoScale * (a - float(h.x)), kH2LoScale * (b - float(h.y))},
                                                          h2_f16x2));
 }
-// The same with the lo part as it is (lo = fp16(x - hi)).
-__device__ __forceinline__ void h2_split2_plain(float a, float b, uint32_t& hi, uint32_t& lo) {
-  const h2_f16x2 h = __builtin_convertvector(h2_f32x2{a, b}, h2_f16x2);
-  hi = __builtin_bit_cast(uint32_t, h);
-  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(h2_f32x2{a - float(h.x), b - float(h.y)}, h2_f16x2));
-}
 // The two (scaled) values of packed parts.
 __device__ __forceinline__ void h2_join2(uint32_t hi, uint32_t lo, float& a, float& b) {
   const h2_f16x2 h = __builtin_bit_cast(h2_f16x2, hi), l = __builtin_bit_cast(h2_f16x2, lo);

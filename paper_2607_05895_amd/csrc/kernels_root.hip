@@ -223,7 +223,6 @@ __global__ __launch_bounds__(256) void h2_root_out_kernel(const RootConvDesc* __
   const int t = threadIdx.x;
   const float zp = d.sc[2] / d.sc[3];
   const uint16_t* X = *d.xsel ? d.X1 : d.X0;
-  uint32_t big = 0;
   const int l = t & 31, row = l & 15, ch = l >> 4;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -242,10 +241,7 @@ __global__ __launch_bounds__(256) void h2_root_out_kernel(const RootConvDesc* __
     float* o = d.out + int64_t(gr) * d.dp + gc;
     *(g_f32x4*)o = f32x4{v[0], v[1], v[2], v[3]};
     *(g_f32x4*)(o + 4) = f32x4{v[4], v[5], v[6], v[7]};
-#pragma unroll
-    for (int k = 0; k < 8; ++k) big = max(big, __float_as_uint(v[k]) & 0x7fffffffu);
   }
-  if (d.amax) slot_max(d.amax, big);
 }
 
 }  // namespace

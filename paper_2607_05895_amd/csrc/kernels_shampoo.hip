@@ -71,14 +71,12 @@ __device__ __forceinline__ int scale_exponent(uint32_t bits) {
   return e == 0 || e == 0xff ? 0 : min(140 - e, 100);
 }
 
-// Two scaled fp16 parts of four fp32 values: x s = hi + 2^-11 lo (h2_core.h) or, PLAIN, hi + lo.
-template <bool PLAIN>
+// Two scaled fp16 parts of four fp32 values: x s = hi + 2^-11 lo (h2_core.h).
 __device__ __forceinline__ void split2x4(const f32x4& x, float s, u32x2& hi, u32x2& lo) {
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     uint32_t h, l;
-    if constexpr (PLAIN) h2_split2_plain(s * x[2 * j], s * x[2 * j + 1], h, l);
-    else h2_split2(s * x[2 * j], s * x[2 * j + 1], h, l);
+    h2_split2(s * x[2 * j], s * x[2 * j + 1], h, l);
     hi[j] = h;
     lo[j] = l;
   }
@@ -89,16 +87,15 @@ __device__ __forceinline__ void split2x4(const f32x4& x, float s, u32x2& hi, u32
 //         (lo.hi, hi.lo, mid.mid, mid.hi, hi.mid, hi.hi) accumulated together; any fp32 range
 //   kH2   both fp32, two scaled fp16 parts each: hi.hi, and lo.hi + hi.lo in an accumulator of their own
 //   kH2B  P fp32 in two scaled fp16 parts, Q stored as bf16 (a gradient), scaled to one fp16 part
-//   kP2B  as kH2B with the lo part as it is and one accumulator: fewer registers, for a P whose elements that
-//         matter lie within 2^-17 of its largest (Shampoo's preconditioners: fourth roots)
+//   kX1   P fp32 in three bf16 parts, Q stored as bf16 (a gradient) and so its own one part: three products
 //   kB    both stored as bf16: one bf16 product
-enum ShMode { kX3, kH2, kH2B, kP2B, kB };
+enum ShMode { kX3, kX1, kH2, kH2B, kB };
 
 // The products of one 128 x 128 output tile, P rows from bi, Q rows from bj, into acc (zero on entry).
 // 4 waves in a 2 x 2 arrangement, each 64 x 64 as 2 x 2 blocks of 32 x 32 outputs, on the 16-bit MFMAs
 // (v_mfma_f32_32x32x16, fp32 accumulation): when a K step of 16 is staged into LDS every element is split
 // once into its parts (one plane per part); a lane's fragment is 8 consecutive k of one row from each plane.
-// sp, sq: the operands' scales (kH2, kH2B, kP2B; acc is then sp sq times the product).
+// sp, sq: the operands' scales (kH2, kH2B; acc is then sp sq times the product).
 // A stage holds KS K steps (KS (PA + PB) planes, at most six: 24 KiB); the LDS is double
 // buffered, and two register sets hold the global loads of the next two stages, so that the loads
 // of stage k + 2 are issued while stage k multiplies and stage k + 1's loads (issued a stage
@@ -107,10 +104,11 @@ enum ShMode { kX3, kH2, kH2B, kP2B, kB };
 template <ShMode MODE>
 __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, int bj, float sp, float sq,
                                                  uint8_t* lds_raw, f32x16 (&acc)[2][2]) {
-  constexpr bool ABF = MODE == kB, BBF = MODE >= kH2B;  // operands stored as bf16
-  constexpr int PA = MODE == kX3 ? 3 : MODE == kB ? 1 : 2;            // parts per operand
+  constexpr bool ABF = MODE == kB, BBF = MODE == kX1 || MODE >= kH2B;  // operands stored as bf16
+  constexpr bool F16 = MODE == kH2 || MODE == kH2B;
+  constexpr int PA = MODE <= kX1 ? 3 : MODE == kB ? 1 : 2;             // parts per operand
   constexpr int PB = MODE == kX3 ? 3 : MODE == kH2 ? 2 : 1;
-  constexpr int KS = BBF ? 2 : 1;                                     // K steps per stage
+  constexpr int KS = MODE >= kH2B ? 2 : 1;                             // K steps per stage
   static_assert(KS * (PA + PB) <= 6, "a stage holds at most six planes");
   typedef __attribute__((address_space(1))) const uint8_t g_cu8;
   typedef __attribute__((address_space(1))) const u32x2 g_cu32x2;
@@ -153,7 +151,7 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
   auto put = [&](uint8_t* base, int u, int o, auto v, float sc) {
     u32x2 h, m, l;
     auto st = [&](int p, const u32x2& x) { *reinterpret_cast<u32x2*>(base + plane(u, o, p) * kShPlane) = x; };
-    if constexpr (MODE == kB) {
+    if constexpr (!F16 && std::is_same<decltype(v), u32x2>::value) {
       st(0, v);
     } else if constexpr (std::is_same<decltype(v), u32x2>::value) {  // bf16 to one scaled fp16 part
       typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -164,13 +162,13 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
             uint32_t, __builtin_convertvector(
                           f32x2{sc * __uint_as_float(v[j] << 16), sc * __uint_as_float(v[j] & 0xffff0000u)}, f16x2));
       st(0, h);
-    } else if constexpr (MODE == kX3) {
+    } else if constexpr (!F16) {
       split3x4(v, h, m, l);
       st(0, h);
       st(1, m);
       st(2, l);
     } else {
-      split2x4<MODE == kP2B>(v, sc, h, l);
+      split2x4(v, sc, h, l);
       st(0, h);
       st(1, l);
     }
@@ -186,12 +184,11 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
         put(base, u, 1, rb[u][j], sq);
       }
   };
-  constexpr bool F16 = MODE == kH2 || MODE == kH2B || MODE == kP2B;
   using Frag = typename std::conditional<F16, h2_f16x8, bf16x8_t>::type;
   auto frag = [&](int s, int pl, int r) {
     return *reinterpret_cast<const Frag*>(lds_raw + s * kShStage + pl * kShPlane + split_slot(r, fh) * 16);
   };
-  constexpr bool MIX = MODE == kH2 || MODE == kH2B;
+  constexpr bool MIX = F16;
   f32x16 mix[MIX ? 2 : 1][2];  // 2^11 times the products with a lo part
   if constexpr (MIX) {
 #pragma unroll
@@ -224,8 +221,6 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
             if constexpr (MIX) {
               if (pa + pb > 0) mix[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i][pa], bf[j][pb], mix[i][j], 0, 0, 0);
               else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i][pa], bf[j][pb], acc[i][j], 0, 0, 0);
-            } else if constexpr (F16) {
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i][pa], bf[j][pb], acc[i][j], 0, 0, 0);
             } else {
               acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i][pa], bf[j][pb], acc[i][j], 0, 0, 0);
             }
@@ -234,10 +229,10 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
     }
   };
   constexpr int kStep = 16 * KS;  // k per stage
-  constexpr int kTerms = MODE == kX3 ? 6 : MODE == kH2 ? 3 : MODE == kB ? 1 : 2;
+  constexpr int kTerms = MODE == kX3 ? 6 : MODE == kX1 || MODE == kH2 ? 3 : MODE == kB ? 1 : 2;
   constexpr int kMfma = KS * 4 * kTerms;  // MFMAs per stage and wave
   // split VALU per stage, about
-  constexpr int kSplitValu = MODE == kX3 ? 88 : MODE == kH2 ? 72 : MODE == kB ? 0 : 2 * (36 + 20);
+  constexpr int kSplitValu = MODE == kX3 ? 88 : MODE == kX1 ? 44 : MODE == kH2 ? 72 : MODE == kB ? 0 : 2 * (36 + 20);
   // one stage's products on LDS buffer mb while the next stage's loads (set) are split into buffer
   // sb: with split operands the split's vector instructions and LDS stores are interleaved with the
   // MFMAs (they are independent), so that a wave's MFMA pipe and vector ALU work at the same time
@@ -284,11 +279,12 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
 }
 
 // C = alpha P Q^T + beta E + diag I on one 128 x 128 output tile per workgroup, four kernels:
-//   kKindX3      the kX3 products: Newton's roots and the QR block updates, whose operands have no bound; three
-//                workgroups per CU (48 KiB of LDS, 170 registers)
+//   kKindX3      the kX3 products: Shampoo's, Newton's roots and the QR block updates, whose operands have no bound
+//                or any grading; three workgroups per CU (48 KiB of LDS, 170 registers)
+//   kKindX3U     the kX3 products whose problems all apply the parameter update (in kKindX3 it would spill); three
+//   kKindX1      the kX1 products (Shampoo's P_L G of a bf16 gradient); three per CU
 //   kKindB       both operands bf16 (the statistics of a bf16 gradient); three per CU
-//   kKindP2B     the kP2B products; three per CU
-//   kKindScaled  any operand types, fp32 ones in scaled fp16 parts; two per CU (the second accumulator)
+//   kKindScaled  any operand types, fp32 ones in scaled fp16 parts (SOAP); two per CU (the second accumulator)
 // Scaled against three-way split products: the four product launches of one decoder layer (two 14336 x 4096
 // with their transposed third, two 4096 x 4096, two 1024 x 4096; SOAP without refresh) 28.4 -> 21.1 ms.
 // A problem with `fused` applies the parameter update p <- p decay - step C instead of storing C.
@@ -297,7 +293,7 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
 // The tile that workgroup b of n takes: workgroups are dealt to the 8 XCDs round robin; runs of eight
 // consecutive tiles go to one XCD, so that tiles that share operand panels share its L2. The last, partial
 // round keeps the plain order. For the load-bound products with a bf16 operand: statistics of the decoder layer
-// 1.88 -> 1.67 ms, P_L G of two 768/3072-wide layers 241 -> 224 us; the scaled and X3 products gain nothing
+// 1.88 -> 1.67 ms; the scaled and X3 products gain nothing
 // (runs of 32 or 64 cost the scaled ones 5 %).
 __device__ __forceinline__ int xcd_order(int b, int n) {
   if (b >= n / 64 * 64) return b;
@@ -305,13 +301,13 @@ __device__ __forceinline__ int xcd_order(int b, int n) {
   return b - in + (in & 7) * 8 + (in >> 3);
 }
 
-enum ShKind { kKindX3, kKindB, kKindP2B, kKindScaled };
+enum ShKind { kKindX3, kKindX3U, kKindX1, kKindB, kKindScaled };
 template <ShKind KIND>
 __global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kernel(
     const ShGemmDesc* __restrict__ descs, int count, float decay, float step) {
-  constexpr bool X3 = KIND == kKindX3;
+  constexpr bool X3 = KIND == kKindX3, X3U = KIND == kKindX3U;
   __shared__ __attribute__((aligned(16))) uint8_t lds_raw[2 * kShStage];
-  const int tile = KIND == kKindB || KIND == kKindP2B ? xcd_order(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int tile = KIND == kKindB || KIND == kKindX1 ? xcd_order(blockIdx.x, gridDim.x) : blockIdx.x;
   const int e = find_desc(descs, count, tile);
   const ShGemmDesc& d = descs[e];
   int lt = tile - d.tile_begin;
@@ -355,8 +351,10 @@ __global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kern
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
   int ex = 0;  // acc is 2^ex times the product
-  if constexpr (X3) {
+  if constexpr (X3 || X3U) {
     sh_tile_products<kX3>(d, bi, bj, 1.0f, 1.0f, lds_raw, acc);
+  } else if constexpr (KIND == kKindX1) {
+    sh_tile_products<kX1>(d, bi, bj, 1.0f, 1.0f, lds_raw, acc);
   } else if (KIND == kKindB || (KIND == kKindScaled && d.q_bf16 && d.p_bf16)) {
     sh_tile_products<kB>(d, bi, bj, 1.0f, 1.0f, lds_raw, acc);
   } else {
@@ -364,18 +362,14 @@ __global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kern
     const int ep = d.pmax ? scale_exponent(*d.pmax) : 13, eq = d.qmax ? scale_exponent(*d.qmax) : 13;
     const float sp = ldexpf(1.0f, ep), sq = ldexpf(1.0f, eq);
     ex = ep + eq;
-    if constexpr (KIND == kKindP2B) {
-      sh_tile_products<kP2B>(d, bi, bj, sp, sq, lds_raw, acc);
-    } else {
-      if (d.q_bf16)
-        sh_tile_products<kH2B>(d, bi, bj, sp, sq, lds_raw, acc);
-      else
-        sh_tile_products<kH2>(d, bi, bj, sp, sq, lds_raw, acc);
-    }
+    if (d.q_bf16)
+      sh_tile_products<kH2B>(d, bi, bj, sp, sq, lds_raw, acc);
+    else
+      sh_tile_products<kH2>(d, bi, bj, sp, sq, lds_raw, acc);
   }
 
-  if constexpr (KIND == kKindScaled) {
-    if (d.fused) {
+  if constexpr (X3U || KIND == kKindScaled) {
+    if (X3U || d.fused) {
       // The parameter update, a row half of the tile at a time: C through LDS (64 rows of 128 fp32, 16-byte
       // slots XOR-permuted by the row), the old parameter's words loaded before the exchange, four
       // consecutive elements per lane where rows and buffers are aligned to them, or one at a time over a
@@ -401,28 +395,30 @@ __global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kern
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                   const int rl = i * 32 + 8 * (v >> 2) + 4 * fh + (v & 3), c = wc * 64 + j * 32 + fr;
-                  *(l_f32*)(img + at(rl, c)) = d.alpha * ldexpf(acc[i][j][v], -ex);
+                  *(l_f32*)(img + at(rl, c)) = d.alpha * (X3U ? acc[i][j][v] : ldexpf(acc[i][j][v], -ex));
                 }
           }
           __syncthreads();
         };
         if (vec) {
           const int c = (t & 31) * 4;
-          ParamWords<4> pw[8];
+          constexpr int NB = X3U ? 4 : 8;  // rows per thread whose words are held at a time (8: 17 registers spill, 4: 10)
+          ParamWords<4> pw[NB];
+          auto row = [&](int it) { return it * 8 + (t >> 5); };
+          auto inside = [&](int it) { return r0 + 64 * h + row(it) < a.m && c0 + c < a.n; };
+          auto at_param = [&](int it) { return (r0 + 64 * h + row(it)) * a.n + c0 + c; };
 #pragma unroll
-          for (int it = 0; it < 8; ++it) {
-            const int64_t r = r0 + 64 * h + it * 8 + (t >> 5);
-            if (r < a.m && c0 + c < a.n) pw[it].load(a.param, a.param_dtype, r * a.n + c0 + c);
-          }
-          exchange();
+          for (int b0 = 0; b0 < 8; b0 += NB) {
 #pragma unroll
-          for (int it = 0; it < 8; ++it) {
-            const int rl = it * 8 + (t >> 5);
-            const int64_t r = r0 + 64 * h + rl;
-            if (r < a.m && c0 + c < a.n) {
-              const f32x4 o = *(l_f32x4*)(img + at(rl, c));
-              pw[it].store(a.param, a.param_dtype, a.update_out, r * a.n + c0 + c, decay, step, {o[0], o[1], o[2], o[3]});
-            }
+            for (int k = 0; k < NB; ++k)
+              if (inside(b0 + k)) pw[k].load(a.param, a.param_dtype, at_param(b0 + k));
+            if (b0 == 0) exchange();
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+              if (inside(b0 + k)) {
+                const f32x4 o = *(l_f32x4*)(img + at(row(b0 + k), c));
+                pw[k].store(a.param, a.param_dtype, a.update_out, at_param(b0 + k), decay, step, {o[0], o[1], o[2], o[3]});
+              }
           }
         } else {
           exchange();
@@ -489,14 +485,14 @@ __global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kern
             const int r = 64 * h + rl, c = wc * 64 + j * 32 + fr;
             if (diag_tile && r > c) continue;  // filled from the upper triangle below
             const int64_t gr = r0 + r, gc = c0 + c;
-            float x = d.alpha * (X3 ? acc[i][j][v] : ldexpf(acc[i][j][v], -ex));
+            float x = d.alpha * (KIND != kKindScaled ? acc[i][j][v] : ldexpf(acc[i][j][v], -ex));
             if (E) x += d.beta * tl[rl * kShTile + c];
             if (gr == gc) x += d.diag;
             C[gr * d.ldc + gc] = x;
             acc[i][j][v] = x;
-            if constexpr (!X3) {
+            if constexpr (KIND == kKindScaled) {
               big = max(big, __float_as_uint(x) & 0x7fffffffu);
-            } else if (gr < d.valid && gc < d.valid) {
+            } else if (X3 && gr < d.valid && gc < d.valid) {
               const float dv = fabsf(x - (gr == gc ? 1.0f : 0.0f));
               res = (dv > res || dv != dv) ? dv : res;  // keeps a NaN
             }
@@ -526,7 +522,7 @@ __global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kern
       }
     }
   }
-  if constexpr (!X3) {
+  if constexpr (KIND == kKindScaled) {
     if (d.cmax) slot_max(d.cmax, big);
   }
   if (X3 && d.resid_out) {
@@ -572,24 +568,6 @@ __global__ __launch_bounds__(256) void sh_copy_in_kernel(const ShCopyDesc* __res
       put(d.dstT, (int64_t(tj) * kShCopyTile + r) * d.ld_dstT + int64_t(ti) * kShCopyTile + c, tt[c][r]);
     }
   }
-}
-
-// The largest |element| of dense fp32 buffers into their slots: 16384 elements per workgroup, 16-byte loads.
-__global__ __launch_bounds__(256) void sh_max_kernel(const ShMaxDesc* __restrict__ descs, int count) {
-  const int e = find_desc(descs, count, blockIdx.x);
-  const ShMaxDesc& d = descs[e];
-  const int64_t i0 = int64_t(blockIdx.x - d.tile_begin) * kShMaxElems + threadIdx.x * 4;
-  uint32_t big = 0;
-#pragma unroll
-  for (int i = 0; i < kShMaxElems / 1024; ++i) {
-    const int64_t o = i0 + i * 1024;
-    if (o < d.n) {
-      const f32x4 x = *(const g_cf32x4*)(d.p + o);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) big = max(big, __float_as_uint(x[k]) & 0x7fffffffu);
-    }
-  }
-  slot_max(d.slot, big);
 }
 
 // Boundary copy out of the padded workspace into a caller fp32 rows x cols buffer.
@@ -722,8 +700,10 @@ hipError_t launch_sh_gemm(const ShGemmDesc* d, int count, int total_tiles, int k
     hipLaunchKernelGGL(sh_gemm_kernel<kKindX3>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
   else if (kind == kShB)
     hipLaunchKernelGGL(sh_gemm_kernel<kKindB>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
-  else if (kind == kShP2B)
-    hipLaunchKernelGGL(sh_gemm_kernel<kKindP2B>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
+  else if (kind == kShX3U)
+    hipLaunchKernelGGL(sh_gemm_kernel<kKindX3U>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
+  else if (kind == kShX1)
+    hipLaunchKernelGGL(sh_gemm_kernel<kKindX1>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
   else
     hipLaunchKernelGGL(sh_gemm_kernel<kKindScaled>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
   return hipGetLastError();
@@ -735,12 +715,6 @@ hipError_t launch_sh_copy(const ShCopyDesc* d, int count, int total_tiles, int d
     hipLaunchKernelGGL(sh_copy_in_kernel, dim3(total_tiles), dim3(256), 0, st, d, count);
   else
     hipLaunchKernelGGL(sh_copy_out_kernel, dim3(total_tiles), dim3(256), 0, st, d, count);
-  return hipGetLastError();
-}
-
-hipError_t launch_sh_max(const ShMaxDesc* d, int count, int total_blocks, hipStream_t st) {
-  if (total_blocks <= 0 || count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(sh_max_kernel, dim3(total_blocks), dim3(256), 0, st, d, count);
   return hipGetLastError();
 }
 

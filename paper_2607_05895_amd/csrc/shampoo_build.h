@@ -46,7 +46,7 @@ struct Arena {
 };
 
 enum OpKind {
-  kOpCopyIn, kOpCopyOut, kOpGemm, kOpGemmX3, kOpGemmB, kOpGemmP2B, kOpMax, kOpNorm, kOpScalars, kOpInit, kOpApply,
+  kOpCopyIn, kOpCopyOut, kOpGemm, kOpGemmX3, kOpGemmX3U, kOpGemmB, kOpGemmX1, kOpNorm, kOpScalars, kOpInit, kOpApply,
   kOpRoot, kOpRootIn, kOpRootOut,
   kOpSoapPrep, kOpSoapAdam, kOpEye, kOpQrPanel, kOpQrCol, kOpQrT,
   kOpFork,  // the auxiliary stream waits for everything enqueued so far on the caller's stream
@@ -179,13 +179,14 @@ inline int run(Build& b, char* ws, size_t desc_at, hipStream_t main_st, const Ru
       case kOpCopyOut: e = launch_sh_copy(reinterpret_cast<ShCopyDesc*>(dp), o.count, o.total, 1, st); break;
       case kOpGemm:
       case kOpGemmX3:
+      case kOpGemmX3U:
       case kOpGemmB:
-      case kOpGemmP2B:
-        e = launch_sh_gemm(reinterpret_cast<ShGemmDesc*>(dp), o.count, o.total,
-                           o.kind == kOpGemmX3 ? kShX3 : o.kind == kOpGemmB ? kShB : o.kind == kOpGemmP2B ? kShP2B : kShScaled,
-                           s.decay, s.step, st);
+      case kOpGemmX1: {
+        const int kind = o.kind == kOpGemm ? kShScaled : o.kind == kOpGemmX3 ? kShX3 : o.kind == kOpGemmX3U ? kShX3U
+                         : o.kind == kOpGemmB ? kShB : kShX1;
+        e = launch_sh_gemm(reinterpret_cast<ShGemmDesc*>(dp), o.count, o.total, kind, s.decay, s.step, st);
         break;
-      case kOpMax: e = launch_sh_max(reinterpret_cast<ShMaxDesc*>(dp), o.count, o.total, st); break;
+      }
       case kOpRoot:
         e = launch_root(reinterpret_cast<RootDesc*>(dp), reinterpret_cast<TileRef*>(ws + desc_at + o.tiles_off),
                         o.total, st);

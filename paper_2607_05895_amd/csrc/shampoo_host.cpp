@@ -50,7 +50,6 @@ struct Side {
   size_t M = 0, T2 = 0, T4 = 0, X[2] = {0, 0}, partials = 0, sc = 0, resid = 0, xsel = 0;
   const float* S = nullptr;
   float* out = nullptr;  // caller destination of the root (d x d, row stride d)
-  uint32_t* amax = nullptr;  // slot that receives the root's largest element
   bool has_out = false;  // copy the root out (decided by the call, not by the pointer value,
                          // so that the size query, which sees no pointers, builds the same ops)
   // the fourth root in the padded fp32 layout: the caller's buffer when the side works in place
@@ -293,7 +292,6 @@ void add_root_ops(Build& b, std::vector<Side*> sides, int p, int iters, double e
       r.sc = c.out;
       r.resid = b.ptr<float>(s->resid);
       r.xsel = b.ptr<int32_t>(s->xsel);
-      r.amax = s->amax;
       r.dp = int32_t(s->dp);
       r.tile_begin = itiles;
       itiles += tn * tn;
@@ -406,44 +404,26 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
   desc_at = a.off;
   const bool refresh = hp->refresh != 0;
   const int iters = hp->root_iters;
-  // slots of one entry: the largest |element| of G, P_L, P_R and Y
-  enum { kSG, kSPL, kSPR, kSY, kSlots };
-  b.reserve_slots(desc_at, size_t(count) * kSlots);
-  auto slot = [&](int64_t i, int k) { return b.slot(size_t(i) * kSlots + size_t(k)); };
 
   std::vector<ShCopyDesc> cin;
-  std::vector<ShMaxDesc> smax;
-  int ct = 0, mt = 0;
+  int ct = 0;
   for (int64_t i = 0; i < count; ++i) {
     EntryPlan& e = P[size_t(i)];
     // a bf16 gradient is copied as bf16 (exact): the GEMM reads it as a one-part operand
     cin.push_back(copy_desc(en[i].grad, en[i].grad_dtype, b.ptr<float>(e.g()), b.ptr<float>(e.gt()), e.m, e.n,
                             e.n, e.np, e.mp, e.mp, e.np, ct));
     cin.back().dst_bf16 = e.grad_bf16 ? 1 : 0;
-    cin.back().amax = slot(i, kSG);
-    e.L.amax = slot(i, kSPL);
-    e.R.amax = slot(i, kSPR);
     if (!e.L.S)
       cin.push_back(copy_desc(en[i].L, kDtF32, b.ptr<float>(e.L.M), nullptr, e.m, e.m, e.m, e.mp, 0, e.mp,
                               e.mp, ct));
     if (!e.R.S)
       cin.push_back(copy_desc(en[i].R, kDtF32, b.ptr<float>(e.R.M), nullptr, e.n, e.n, e.n, e.np, 0, e.np,
                               e.np, ct));
-    // a stored preconditioner: copied (which takes its largest element), or read where it lies
+    // a stored preconditioner is read where it lies, or copied
     auto stored = [&](const float* p, Side& side) {
-      if (side.S) {
-        ShMaxDesc x{};
-        x.p = p;
-        x.n = side.d * side.d;
-        x.slot = side.amax;
-        x.tile_begin = mt;
-        mt += int((x.n + kShMaxElems - 1) / kShMaxElems);
-        smax.push_back(x);
-        return;
-      }
-      cin.push_back(copy_desc(p, kDtF32, b.ptr<float>(side.X[0]), nullptr, side.d, side.d, side.d, side.dp, 0, side.dp,
-                              side.dp, ct));
-      cin.back().amax = side.amax;
+      if (!side.S)
+        cin.push_back(copy_desc(p, kDtF32, b.ptr<float>(side.X[0]), nullptr, side.d, side.d, side.d, side.dp, 0, side.dp,
+                                side.dp, ct));
     };
     if (!refresh) {
       stored(en[i].PL, e.L);
@@ -451,14 +431,6 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
     }
   }
   b.op(kOpCopyIn, cin, ct);
-  // the stored preconditioners' largest elements (one read of the buffers) are taken on the auxiliary
-  // stream, beside the statistics, which are not HBM bound
-  if (!smax.empty()) {
-    b.fork();
-    b.aux = 1;
-    b.op(kOpMax, smax, mt);
-    b.aux = 0;
-  }
 
   // grouped products over the entries, largest first (see add_root_ops)
   std::vector<EntryPlan*> order;
@@ -479,14 +451,12 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
         gs.push_back(gemm_desc(b.ptr<float>(g), b.ptr<float>(g), S, S, k, k, d, d, d, d, k, 1, float(hp->weight),
                                float(hp->beta), 0.0f, gt));
         gs.back().p_bf16 = gs.back().q_bf16 = bf;
-        gs.back().pmax = gs.back().qmax = slot(ep - P.data(), kSG);
       };
       sym(e.g(), stat(e.L, c.L), e.mp, e.np);
       sym(e.gt(), stat(e.R, c.R), e.np, e.mp);
     }
-    b.op(bf ? kOpGemmB : kOpGemm, gs, gt);
+    b.op(bf ? kOpGemmB : kOpGemmX3, gs, gt);
   }
-  if (!smax.empty()) b.join();
 
   std::vector<ShCopyDesc> cst;
   ct = 0;
@@ -531,13 +501,8 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
     // the preconditioners: this step's roots, or the stored ones (read where they lie, or copied)
     const float* pl = refresh ? e.L.root(b) : e.L.S ? en[i].PL : b.ptr<float>(e.L.X[0]);
     const float* pr = refresh ? e.R.root(b) : e.R.S ? en[i].PR : b.ptr<float>(e.R.X[0]);
-    auto max_slots = [&](ShGemmDesc& g, int p, int q, int c) {
-      g.pmax = slot(int64_t(i), p);
-      g.qmax = slot(int64_t(i), q);
-      g.cmax = c < 0 ? nullptr : slot(int64_t(i), c);
-    };
     // U = P_L G P_R^T. Both association orders take the same fp32 flop, but with a bf16 G the product
-    // that reads G takes two MFMAs per step and the other three, so the larger of the two
+    // that reads G takes three MFMAs per step and the other six, so the larger of the two
     // products should be the one with G: a wide G (n > m) forms Y^T = P_R G^T (n x m) first and then
     // U = P_L Y; otherwise Y = P_L G, then U = Y P_R^T.
     std::vector<ShGemmDesc>& gy = e.grad_bf16 ? gyb : gyf;
@@ -546,24 +511,20 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
       gy.push_back(gemm_desc(pr, b.ptr<float>(e.g()), nullptr, b.ptr<float>(e.Y), e.np, e.np, 0, e.mp, e.np,
                              e.mp, e.np, 0, 1.0f, 0.0f, 0.0f, ty));
       gy.back().q_bf16 = 1;
-      max_slots(gy.back(), kSPR, kSG, kSY);
       gu.push_back(gemm_desc(pl, b.ptr<float>(e.Y), nullptr, b.ptr<float>(e.u()), e.mp, e.mp, 0, e.np, e.mp,
                              e.np, e.mp, 0, 1.0f, 0.0f, 0.0f, tu));
-      max_slots(gu.back(), kSPL, kSY, -1);
     } else {
       gy.push_back(gemm_desc(pl, b.ptr<float>(e.gt()), nullptr, b.ptr<float>(e.Y), e.mp, e.mp, 0, e.np, e.mp,
                              e.np, e.mp, 0, 1.0f, 0.0f, 0.0f, ty));
       gy.back().q_bf16 = e.grad_bf16 ? 1 : 0;
-      max_slots(gy.back(), kSPL, kSG, kSY);
       gu.push_back(gemm_desc(b.ptr<float>(e.Y), pr, nullptr, b.ptr<float>(e.u()), e.np, e.np, 0, e.np, e.mp,
                              e.np, e.np, 0, 1.0f, 0.0f, 0.0f, tu));
-      max_slots(gu.back(), kSY, kSPR, -1);
     }
   }
   for (size_t k = 0; k < gu.size(); ++k) gu[k].fused = fused + (order[k] - P.data());
-  b.op(kOpGemmP2B, gyb, tyb);
-  b.op(kOpGemm, gyf, tyf);
-  b.op(kOpGemm, gu, tu);
+  b.op(kOpGemmX1, gyb, tyb);
+  b.op(kOpGemmX3, gyf, tyf);
+  b.op(kOpGemmX3U, gu, tu);
 
   return desc_at + al(b.h.size());
 }

@@ -82,7 +82,7 @@ struct ShGemmDesc {
   const uint32_t* pmax;
   const uint32_t* qmax;
   uint32_t* cmax;
-  // scaled products: apply the parameter update p <- p decay - step C (and C to update_out) to the real
+  // kShX3U, kShScaled: apply the parameter update p <- p decay - step C (and C to update_out) to the real
   // block instead of storing C; null: store C
   const struct ShApplyDesc* fused;
 };
@@ -103,15 +103,6 @@ struct ShCopyDesc {
   int32_t tile_begin;
   int32_t dst_bf16;    // dir 0: dst and dstT hold bf16
   uint32_t* amax;      // dir 0: receives the largest |element| (bit pattern, atomic max; may be null)
-};
-
-// The largest |element| of n (a multiple of 4) dense, 16-byte aligned fp32 values, into a slot.
-constexpr int kShMaxElems = 16384;
-struct ShMaxDesc {
-  const float* p;
-  int64_t n;
-  uint32_t* slot;
-  int32_t tile_begin;  // kShMaxElems elements per workgroup
 };
 
 // Sum of squares and trace of a padded d_pad x d_pad statistic, in row chunks (fp64 partials).
@@ -177,7 +168,6 @@ struct RootConvDesc {
   const float* sc;
   float* resid;          // the two residual slots: {0, not converged}
   const int32_t* xsel;
-  uint32_t* amax;        // out: receives the largest |element| (bit pattern, atomic max; may be null)
   int32_t dp;
   int32_t tile_begin;    // 64 x 64 tiles
 };
@@ -194,12 +184,12 @@ struct ShApplyDesc {
   int32_t tile_begin;
 };
 
-// kind: three-way bf16 splits (operands of any range), all operands bf16, scaled two-way fp16 splits of a
-// preconditioner P with a bf16 Q, or scaled two-way fp16 splits and one-part operands; decay and step are those of the problems that apply a parameter update
-enum { kShX3, kShB, kShP2B, kShScaled };
+// kind: three-way bf16 splits (operands of any range), without or with the parameter update in every problem, the
+// same of P with a bf16 Q, all operands bf16, or scaled two-way fp16 splits and one-part operands; decay and
+// step are those of the problems that apply a parameter update (kShX3U and kShScaled)
+enum { kShX3, kShX3U, kShX1, kShB, kShScaled };
 hipError_t launch_sh_gemm(const ShGemmDesc* d, int count, int total_tiles, int kind, float decay, float step,
                           hipStream_t st);
-hipError_t launch_sh_max(const ShMaxDesc* d, int count, int total_blocks, hipStream_t st);
 hipError_t launch_sh_copy(const ShCopyDesc* d, int count, int total_tiles, int dir, hipStream_t st);
 hipError_t launch_sh_norm(const ShNormDesc* d, int count, int total_blocks, hipStream_t st);
 hipError_t launch_sh_scalars(const ShScalarDesc* d, int count, double eps, double eps_rel, int p,

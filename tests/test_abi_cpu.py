@@ -2,6 +2,7 @@
 declares, and rejects invalid arguments before anything is enqueued."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -286,6 +287,34 @@ def test_shampoo_size_query_equals_what_the_call_needs(refresh):
                                                                  grad_dtype=e.grad_dtype) for e in ents], hp)
     assert q > 0
     assert _needed_bytes(lambda: native.mfsdp_shampoo_step(ents, hp, FAKE * 16, 0, 0)) == q
+
+
+@pytest.mark.parametrize("kind", ["shampoo", "soap"])
+@pytest.mark.parametrize("refresh", [0, 1])
+def test_step_never_needs_more_than_its_size_query(kind, refresh):
+    """Over random entry sets (sides that are multiples of the tile and not, buffers that are 16-byte aligned and
+    not, one matrix or several): a step on a workspace of the queried size is not refused."""
+    rng = random.Random(60 + refresh)
+    sizes = [1, 50, 128, 256, 384, 512, 768, 777, 1000, 1024, 1600, 4096]
+    for _ in range(400):
+        ents = []
+        for _ in range(rng.choice((1, 1, 2, 3, 6))):
+            off = {k: rng.choice((0, 0, 4, 8)) for k in ("L", "R", "PL", "PR", "QL", "QR")}
+            kw = dict(m=rng.choice(sizes), n=rng.choice(sizes), param_dtype=rng.choice((0, 1)),
+                      grad_dtype=rng.choice((0, 1)), L=FAKE * 5 + off["L"], R=FAKE * 6 + off["R"])
+            if kind == "shampoo":
+                ents.append(_sh_entry(PL=FAKE * 7 + off["PL"], PR=FAKE * 8 + off["PR"], **kw))
+            else:
+                ents.append(_soap_entry(QL=FAKE * 7 + off["QL"], QR=FAKE * 8 + off["QR"], **kw))
+        if kind == "shampoo":
+            hp = native.shampoo_hparams(refresh=bool(refresh), root_iters=rng.choice((1, 2, 3, 20)))
+            q = native.mfsdp_shampoo_workspace_size(ents, hp)
+            need = _needed_bytes(lambda: native.mfsdp_shampoo_step(ents, hp, FAKE * 16, 0, 0))
+        else:
+            hp = native.soap_hparams(refresh=bool(refresh), refresh_iters=rng.choice((1, 3)), step=4)
+            q = native.mfsdp_soap_workspace_size(ents, hp)
+            need = _needed_bytes(lambda: native.mfsdp_soap_step(ents, hp, FAKE * 16, 0, 0))
+        assert 0 < need <= q, [(e.m, e.n, e.L, e.R) for e in ents]
 
 
 @pytest.mark.parametrize("p,iters", [(1, 1), (2, 8), (4, 20)])

@@ -379,6 +379,44 @@ def test_shampoo_stored_step_is_exact_under_power_of_two_scaling(native, shape, 
         assert torch.equal(a, b) and bool(torch.isfinite(a).all())
 
 
+@pytest.mark.parametrize("gdt", [synth.BF16, synth.F32])
+@pytest.mark.parametrize("shape", [(129, 300), (300, 129), (256, 384)])
+def test_shampoo_stored_step_keeps_rows_of_any_size(native, shape, gdt):
+    """Rows and columns far below the largest keep their relative accuracy: gradients graded over 2^-60 along both
+    sides, a preconditioner graded against them, so that U is not. Every element of a dense block of U is the
+    sum of at most two products chains of K terms; bound: (K + 8) 2^-24 of the sum of their magnitudes. The
+    statistics likewise against sqrt(S_ii S_jj)."""
+    import torch
+    m, n = shape
+    _say(f"shampoo graded operands {m}x{n} {gdt}")
+    rng = np.random.default_rng(4350 + m)
+    gm, gn = 2.0 ** -np.linspace(0, 30, m).round(), 2.0 ** -np.linspace(0, 30, n).round()
+    x = _Mat(rng, m, n, synth.F32, gdt).device()
+    g = rng.standard_normal((m, n)) * gm[:, None] * gn[None, :]
+    x.dg.copy_(torch.from_numpy(g).to(x.dg.dtype))
+    g = from_dev(x.dg)
+    pl = (rng.standard_normal((m, m)) / gm[None, :]).astype(np.float32)   # columns graded against G's rows
+    pr = (rng.standard_normal((n, n)) / gn[:, None]).astype(np.float32).T.copy()
+    pl[1::2] *= np.float32(2.0 ** -50)                                     # and rows of its own
+    x.dPL.copy_(to_dev(pl, synth.F32))
+    x.dPR.copy_(to_dev(pr, synth.F32))
+    x.dL.zero_()
+    x.dR.zero_()
+    hpn, _ = _hp(native, refresh=False, beta=0.5, weight=0.5)
+    ents = [x.entry(native)]
+    native.shampoo_step_t(ents, hpn, native.shampoo_workspace_t(ents, hpn))
+    _sync()
+    pl, pr = pl.astype(np.float64), pr.astype(np.float64)
+    tol = (m + n + 16) * 2.0 ** -24
+    # (U = P_L G P_R^T: the preconditioners are read as symmetric, so P_R by rows)
+    ref, mag = pl @ g @ pr.T, np.abs(pl) @ np.abs(g) @ np.abs(pr).T
+    assert np.all(np.abs(from_dev(x.dU) - ref) <= tol * mag), np.max(np.abs(from_dev(x.dU) - ref) / mag)
+    for got, s in ((from_dev(x.dL), g @ g.T), (from_dev(x.dR), g.T @ g)):
+        d = np.sqrt(np.diag(s))
+        err = np.max(np.abs(got - 0.5 * s) / (d[:, None] * d[None, :]))
+        assert err <= tol, err
+
+
 def test_shampoo_stored_step_propagates_non_finite_gradients(native):
     import torch
     _say("shampoo non-finite gradient")
