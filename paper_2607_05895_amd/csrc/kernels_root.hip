@@ -50,9 +50,12 @@ __global__ __launch_bounds__(256, 2) void h2_root_kernel(const RootDesc* __restr
 
   // coefficients (scaled) from the row that the residual selects
   const float r = *d.conv_in;
-  const bool done = r == kRootDone, fin = r < kRootFinalTol;
+  const bool done = r == kRootDone, fin = root_ends(*d.sum_in);
   if (bi == 0 && bj == 0 && t == 0) {
-    if (d.clear) *d.clear = fin ? kRootDone : 0.0f;
+    if (d.clear) {
+      *d.clear = fin ? kRootDone : 0.0f;
+      *d.sum_clear = 0;
+    }
     if (d.xsel && !done) *d.xsel = d.out_idx;
   }
   if (done || (fin && d.op >= kRootT2)) return;
@@ -106,7 +109,7 @@ __global__ __launch_bounds__(256, 2) void h2_root_kernel(const RootDesc* __restr
   const int fr = lane & 31, fh = lane >> 5;
   const int sw = h2_swz(fr & 15);
   const H2BlockLane bl(lane);
-  float res = 0.0f;
+  float res = 0.0f, sum = 0.0f;
   if (E) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -152,6 +155,7 @@ __global__ __launch_bounds__(256, 2) void h2_root_kernel(const RootDesc* __restr
             if (gr <= gc + k && gr < d.valid && gc + k < d.valid) {
               const float dv = fabsf(v[k] * (1.0f / kScM) - (gr == gc + k ? 1.0f : 0.0f));
               res = (dv > res || dv != dv) ? dv : res;  // keeps a NaN
+              sum += (gr == gc + k ? 1.0f : 2.0f) * (dv * dv);
             }
         }
         uint32_t h0, l0, h1, l1;
@@ -176,8 +180,14 @@ __global__ __launch_bounds__(256, 2) void h2_root_kernel(const RootDesc* __restr
     // NaN propagates as the largest bit pattern, so a diverged side never counts as converged
     uint32_t rb = __float_as_uint(res);
     if (res != res) rb = 0x7fc00000u;
-    for (int o = 32; o > 0; o >>= 1) rb = max(rb, uint32_t(__shfl_xor(int(rb), o)));
-    if (lane == 0) atomicMax(reinterpret_cast<unsigned int*>(d.resid_out), rb);
+    for (int o = 32; o > 0; o >>= 1) {
+      rb = max(rb, uint32_t(__shfl_xor(int(rb), o)));
+      sum += __shfl_xor(sum, o);
+    }
+    if (lane == 0) {
+      atomicMax(reinterpret_cast<unsigned int*>(d.resid_out), rb);
+      atomicAdd(d.sum_out, (unsigned long long)(root_sum_term(sum)));
+    }
   }
 }
 
@@ -189,7 +199,10 @@ __global__ __launch_bounds__(256) void h2_root_init_kernel(const RootConvDesc* _
   const int lt = blockIdx.x - d.tile_begin, tn = d.dp / 64;
   const int ti = lt / tn, tj = lt - ti * tn;
   const int t = threadIdx.x;
-  if (lt == 0 && t < 2) d.resid[t] = t == 0 ? 0.0f : 3.0e38f;
+  if (lt == 0 && t < 2) {
+    d.resid[t] = t == 0 ? 0.0f : 3.0e38f;
+    d.sum[t] = t == 0 ? 0 : kRootSumOpen;
+  }
   const float rho = d.sc[0], zs = d.sc[1] * kScM;
   const int l = t & 31, row = l & 15, ch = l >> 4;
 #pragma unroll

@@ -9,11 +9,11 @@
 // Inverse p-th root of A = S + rho I. All iterates are polynomials in A, hence symmetric and commuting:
 // every product is an NT product of symmetric operands, computed on its upper tiles, and T_k's affine
 // parts are folded into the products' epilogues. The M product of every iteration also records
-// max |M - I| over the real block, which ends the iteration of its side.
+// max |M - I| over the real block (and for p = 4 ||M - I||_F), which ends the iteration of its side.
 //
 // p = 4 (Shampoo): X <- X T, M <- T^4 M, M_0 = A / ||A||_F, T = a I + b M + c M^2: a quadratic T makes
 // one iteration of five products raise the small eigenvalues 11.9-fold where Newton's four raise them
-// 2.44-fold (shampoo_internal.h has the rows of coefficients and the reason for them). The iterates are
+// 2.44-fold (root_rule.h has the rows of coefficients, the rules and their reasons). The iterates are
 // held as split fp16 and multiplied by h2_root_kernel. Two layers of width 768 / 3072 (24 sides, spectra
 // 1 / (1 + i)), the whole step: Newton on three-way bf16 splits 35.96 ms, the quadratic T on them 21.74 ms,
 // on split fp16 14.3 ms; one 768-wide root of a rank-deficient statistic 2.99, 1.84, 0.76 ms.
@@ -47,7 +47,7 @@ constexpr int64_t kMaxDim = 1 << 16;
 // (a caller buffer, row stride d_pad; M then only receives the iteration's first M).
 struct Side {
   int64_t d = 0, dp = 0;
-  size_t M = 0, T2 = 0, T4 = 0, X[2] = {0, 0}, partials = 0, sc = 0, resid = 0, xsel = 0;
+  size_t M = 0, T2 = 0, T4 = 0, X[2] = {0, 0}, partials = 0, sc = 0, resid = 0, sum = 0, xsel = 0;
   const float* S = nullptr;
   float* out = nullptr;  // caller destination of the root (d x d, row stride d)
   bool has_out = false;  // copy the root out (decided by the call, not by the pointer value,
@@ -67,7 +67,8 @@ void plan_side(Side& s, int64_t d, Arena& a) {
   s.X[1] = a.take(mat);
   s.partials = a.take(size_t(s.dp / kNormChunkRows) * 2 * sizeof(double));
   s.sc = a.take(4 * sizeof(float));
-  s.resid = a.take(2 * sizeof(float));
+  s.resid = a.take(64 + 2 * sizeof(unsigned long long));
+  s.sum = s.resid + 64;
   s.xsel = a.take(sizeof(int32_t));
 }
 
@@ -145,18 +146,6 @@ int add_newton_products(Build& b, const std::vector<Side*>& sides, int p, int it
   return iters & 1;
 }
 
-// Iterations of the fourth-root iteration after which a side with this relative ridge has converged,
-// with two to spare: the smallest eigenvalue of M_0 is at least eps_rel / (1 + eps_rel sqrt(d)) (half of
-// it is taken, for rounding), it grows a^4-fold per iteration up to the 0.0863 that the next one maps
-// into [0.7, 1]; two third-order iterations and the last X update follow.
-int root4_iters(double eps_rel, int64_t d, int iters) {
-  const double l0 = 0.5 * eps_rel / (1.0 + eps_rel * std::sqrt(double(d)));
-  if (!(l0 > 1e-30)) return iters;
-  const double grow = std::pow(double(kRootAggressive[0]), 4.0);
-  const int k = int(std::ceil(std::max(0.0, std::log(0.0863 / l0) / std::log(grow))));
-  return std::min(iters, k + 6);
-}
-
 // The upper 128 x 128 tiles of a launch in the order in which its workgroups take them: bands of 8 block
 // rows, column by column; runs of 64 (two workgroups on each CU of an XCD) go to one XCD, so that the
 // tiles running side by side share operand panels in its L2 (workgroup b runs on XCD b mod 8). The last,
@@ -206,13 +195,19 @@ void add_root4_products(Build& b, const std::vector<Side*>& sides, int iters) {
         g.E = E;
         g.C = C;
         g.sc = b.ptr<float>(s->sc);
+        auto sum = [&](int k) { return b.ptr<unsigned long long>(s->sum) + k; };
         g.conv_in = b.ptr<float>(s->resid + sizeof(float) * (q ^ 1));
+        g.sum_in = sum(q ^ 1);
         if (op == kRootX || op == kRootFirst) {
           g.out_idx = q ^ 1;
           g.xsel = b.ptr<int32_t>(s->xsel);
           g.clear = b.ptr<float>(s->resid + sizeof(float) * q);
+          g.sum_clear = sum(q);
         }
-        if (op == kRootM) g.resid_out = b.ptr<float>(s->resid + sizeof(float) * q);
+        if (op == kRootM) {
+          g.resid_out = b.ptr<float>(s->resid + sizeof(float) * q);
+          g.sum_out = sum(q);
+        }
         g.K = int32_t(s->dp);
         g.valid = int32_t(s->d);
         g.op = op;
@@ -291,6 +286,7 @@ void add_root_ops(Build& b, std::vector<Side*> sides, int p, int iters, double e
       r.out = s->root(b);
       r.sc = c.out;
       r.resid = b.ptr<float>(s->resid);
+      r.sum = b.ptr<unsigned long long>(s->sum);
       r.xsel = b.ptr<int32_t>(s->xsel);
       r.dp = int32_t(s->dp);
       r.tile_begin = itiles;

@@ -14,6 +14,7 @@
 #include <stdint.h>
 
 #include "gemm_schedule.h"
+#include "root_rule.h"
 
 namespace mfsdp {
 
@@ -24,19 +25,7 @@ constexpr int kShCopyTile = 64;  // copy / init / apply tile
 // quadratic), and the side's remaining products are skipped.
 constexpr float kShConvTol = 1e-5f;
 
-// The fourth-root iteration (p = 4): X <- X T, M <- T^4 M with T = a I + b M + c M^2, M_0 = z (S + rho I),
-// z = 1 / ||S + rho I||_F, so that the spectrum of every M stays in (0, 1] (rounding aside).
-// While max |M - I| >= kRootSwitch the coefficients are the aggressive row: the quadratic q for which
-// f(x) = x q(x)^4 has its inner maximum and f(1) equal to 1 and its inner minimum equal to 0.7. Small
-// eigenvalues grow by a^4 = 11.9 per iteration (Newton: (5/4)^4 = 2.44), and [0.0863, 1] maps into
-// [0.7, 1], so no eigenvalue already near 1 is pushed far down again (which would cost it its relative
-// accuracy: the unconstrained minimax quadratic grows 37-fold but loses a digit or two). Below
-// kRootSwitch the row is the expansion of x^(-1/4) about 1 (third-order convergence). Below
-// kRootFinalTol one last X update follows (its cubic error is negligible), nothing else.
-constexpr float kRootAggressive[3] = {1.85835485f, -2.08442379f, 1.22606893f};
-constexpr float kRootFinal[3] = {45.0f / 32.0f, -18.0f / 32.0f, 5.0f / 32.0f};
-constexpr float kRootSwitch = 0.31f;
-constexpr float kRootFinalTol = 1e-4f;
+// The fourth-root iteration (p = 4; root_rule.h):
 constexpr float kRootDone = -1.0f;  // residual slot of a side whose last X update is done
 // Every iterate is held as split fp16 (h2_core.h) under a power-of-two scale from a bound on its
 // eigenvalues, which bound its elements: M <= 1, |U| <= 0.9, T^2 <= 3.46, T^4 <= 11.93 (each times its scale at
@@ -150,6 +139,10 @@ struct RootDesc {
   const float* conv_in;
   float* clear;          // (tile (0, 0)) set to 0, or to kRootDone in the side's last iteration
   float* resid_out;      // max |C - I| over the real block, atomic max
+  // and two slots of ||C - I||_F^2 over the real block (root_rule.h), read, cleared and added to alike
+  const unsigned long long* sum_in;
+  unsigned long long* sum_clear;
+  unsigned long long* sum_out;
   int32_t* xsel;         // (tile (0, 0)) receives out_idx, the index of the X buffer written
   int32_t out_idx;
   int32_t K;
@@ -167,6 +160,7 @@ struct RootConvDesc {
   float* out;
   const float* sc;
   float* resid;          // the two residual slots: {0, not converged}
+  unsigned long long* sum;  // the two sum slots, likewise
   const int32_t* xsel;
   int32_t dp;
   int32_t tile_begin;    // 64 x 64 tiles

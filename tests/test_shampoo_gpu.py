@@ -126,6 +126,47 @@ def test_inverse_fourth_root_spectra(native, d, spectrum):
         np.testing.assert_array_equal(got, got.T)
 
 
+@pytest.mark.parametrize("d,small", [(2048, 0.2), (2048, 0.05), (777, 0.05), (100, 1e-3)])
+def test_inverse_fourth_root_of_one_spread_out_eigenvalue(native, d, small):
+    """A = I - (1 - s) u u^T with u constant: its one small eigenvalue s moves no element of M - I by more than
+    1 / d, and the iteration still waits for it. In u's direction the bound is that of the spectra above."""
+    import torch
+    _say(f"fourth root d={d}, one eigenvalue {small} along the constant vector")
+    a = np.eye(d) - (1.0 - small) / d
+    out = torch.empty((d, d), dtype=torch.float32, device="cuda")
+    native.inverse_root_t(to_dev(a, synth.F32), out, p=4, eps=1e-9, eps_rel=0.0, iters=30)
+    _sync()
+    u = np.full(d, d ** -0.5)
+    ref = small ** -0.25
+    err = np.linalg.norm(from_dev(out) @ u - ref * u) / ref
+    tol = 2e-6 + 0.25 * 8 * 2.0 ** -24 * np.linalg.norm(a) / small
+    assert err <= tol, (err, tol)
+
+
+@pytest.mark.parametrize("part,small", [(0.05, 1e-3), (0.2, 1e-3), (0.05, 1e-4), (0.2, 1e-2)])
+def test_inverse_fourth_root_of_few_small_eigenvalues(native, part, small):
+    """A flat spectrum but for a few small eigenvalues, which hardly move M's diagonal: P within their space,
+    where the bound is that of the spectra above, at the ridge's own cap of iterations."""
+    import torch
+    d = 384
+    _say(f"fourth root d={d}, {part} of the eigenvalues {small}")
+    q, _ = np.linalg.qr(np.random.default_rng(45).standard_normal((d, d)))
+    k = int(part * d)
+    w = np.where(np.arange(d) < k, small, 1.0)
+    a = ((q * w) @ q.T).astype(np.float32)
+    a = (a + a.T) * np.float32(0.5)
+    eps_rel = small * 1e-2
+    out = torch.empty((d, d), dtype=torch.float32, device="cuda")
+    native.inverse_root_t(to_dev(a, synth.F32), out, p=4, eps=1e-9, eps_rel=eps_rel, iters=100)
+    _sync()
+    ref = OS.inverse_root(a.astype(np.float64), 4, 1e-9, eps_rel)
+    v = q[:, :k]
+    err = np.linalg.norm((from_dev(out) - ref) @ v) / np.linalg.norm(ref @ v)
+    norm = np.linalg.norm(w)
+    tol = 2e-6 + 0.25 * 8 * 2.0 ** -24 * norm / (small + eps_rel * norm)
+    assert err <= tol, (err, tol)
+
+
 def test_inverse_root_input_read_in_place_or_copied(native):
     """A tile-multiple d whose input is 16-byte aligned is read where it lies; the same values at a
     4-byte offset take the copy path. Same bits either way."""
