@@ -39,16 +39,16 @@ constexpr bool root_ends(uint64_t sum) {
   return float(sum) * (1.0f / kRootSumUnit) < kRootFinalTol * kRootFinalTol;
 }
 
-// Iterations of the fourth-root iteration after which a side with this relative ridge has converged,
-// with two to spare: the smallest eigenvalue of M_0 is at least eps_rel / (1 + eps_rel sqrt(d)) (half of
-// it is taken, for rounding), it grows a^4-fold per iteration up to the 0.0863 that the next one maps
-// into [0.7, 1]; two third-order iterations and the last X update follow.
+// Iterations after which a side with this relative ridge has converged: the smallest eigenvalue of M_0 is at
+// least eps_rel / (1 + eps_rel sqrt(d)) (half of it is taken, for rounding) and grows at least by the second row's
+// a^4 per iteration up to 0.5; then 0.5 -> 0.918 -> 1 - 3e-4 -> 1 - 1e-11, the last X update, and one to
+// spare. (Sides that end earlier skip their later products on the device.)
 inline int root4_iters(double eps_rel, int64_t d, int iters) {
   const double l0 = 0.5 * eps_rel / (1.0 + eps_rel * std::sqrt(double(d)));
   if (!(l0 > 1e-30)) return iters;
-  const double grow = std::pow(double(kRootAggressive[0]), 4.0);
-  const int k = int(std::ceil(std::max(0.0, std::log(0.0863 / l0) / std::log(grow))));
-  return std::min(iters, k + 6);
+  const double grow = std::pow(double(kRootFinal[0]), 4.0);
+  const int k = int(std::ceil(std::max(0.0, std::log(0.5 / l0) / std::log(grow))));
+  return std::min(iters, k + 5);
 }
 
 }  // namespace mfsdp

@@ -1,6 +1,7 @@
 // CPU check of the fourth-root iteration's rules (root_rule.h) in 64-bit arithmetic, on spectra whose eigenvectors
 // are spread over all entries, so that the largest element of M - I says little about its spectrum: every
-// eigenvalue's root is accurate when the rules end the iteration, and the end is not put off on easy spectra. Exit code 0 on success; every failure prints what it found.
+// eigenvalue's root is accurate when the rules end the iteration, within the host's cap, and the end
+// is not put off on easy spectra. Exit code 0 on success; every failure prints what it found.
 #include <cstdio>
 #include <utility>
 #include <vector>
@@ -64,7 +65,7 @@ int main() {
           const int large = int(std::min(16.0, d - n));
           for (int i = 0; i < large; ++i) g.push_back(Group{0.5 + i / 15.0, (d - n) / large});
           if (n > 0) g.push_back(Group{low, n});
-          const auto [k, err] = run(g, eps_rel, 100);
+          const auto [k, err] = run(g, eps_rel, root4_iters(eps_rel, int64_t(d), 100));
           if (!(err <= 1e-6)) {
             ++g_fail;
             std::printf("FAIL d %g eps_rel %g, %g of eigenvalue %g: error %.2e after %d iterations\n", d, eps_rel, n, low,
@@ -75,6 +76,8 @@ int main() {
             std::printf("FAIL d %g eps_rel %g, flat: %d iterations\n", d, eps_rel, k);
           }
         }
+  // the caller's own cap stays
+  if (root4_iters(1e-6, 768, 5) != 5 || root4_iters(0.0, 768, 33) != 33) ++g_fail;
   // a NaN and huge sums never end it, and do not wrap
   if (root_ends(root_sum_term(std::nanf("")) * (uint64_t(1) << 19)) || root_ends(root_sum_term(3e38f))) ++g_fail;
   if (!root_ends(root_sum_term(0.0f) * (uint64_t(1) << 19))) ++g_fail;
