@@ -373,8 +373,7 @@ size_t mfsdp_soap_workspace_size(const mfsdp_soap_entry* entries, int64_t count,
 
 /* One SOAP step on every entry (host array of count entries), enqueued on `stream` (hipStream_t,
  * NULL = default stream); no host synchronisation. Every product runs at fp32 accuracy on the
- * 16-bit MFMA as in mfsdp_shampoo_step (grouped over the entries; in the refresh QR each fp32 operand is
- * split into three bf16 parts); the refresh QR is a blocked
+ * bf16 MFMA for operands of any range, as in mfsdp_shampoo_step (grouped over the entries); the refresh QR is a blocked
  * Householder factorization (16-column panels in 128-column blocks whose updates run on the same
  * GEMM). Part of each block update runs on a library-owned auxiliary stream of the current device
  * (default priority, created on first use, kept until the process ends), forked from `stream` and

@@ -6,7 +6,6 @@
 
 #include <type_traits>
 
-#include "h2_core.h"
 #include "mfsdp_internal.h"
 #include "shampoo_internal.h"
 
@@ -65,50 +64,28 @@ __device__ __forceinline__ int split_slot(int r, int c) { return r * 2 + (c ^ ((
 constexpr int kShPlane = kShTile * 32;  // bytes of one split plane (128 x 16 bf16)
 constexpr int kShStage = 6 * kShPlane;  // both operands of one K step, three planes each
 
-// Power of two that takes a bound (the largest |x|, as an fp32 bit pattern; 0, inf and NaN: 1) to at most 2^14.
-__device__ __forceinline__ int scale_exponent(uint32_t bits) {
-  const int e = int(bits >> 23) & 0xff;
-  return e == 0 || e == 0xff ? 0 : min(140 - e, 100);
-}
-
-// Two scaled fp16 parts of four fp32 values: x s = hi + 2^-11 lo (h2_core.h).
-__device__ __forceinline__ void split2x4(const f32x4& x, float s, u32x2& hi, u32x2& lo) {
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    uint32_t h, l;
-    h2_split2(s * x[2 * j], s * x[2 * j + 1], h, l);
-    hi[j] = h;
-    lo[j] = l;
-  }
-}
-
 // How the operands of a tile are multiplied.
 //   kX3   both fp32, three bf16 parts each (hi + mid + lo): the six partial products above 2^-24 relative
 //         (lo.hi, hi.lo, mid.mid, mid.hi, hi.mid, hi.hi) accumulated together; any fp32 range
-//   kH2   both fp32, two scaled fp16 parts each: hi.hi, and lo.hi + hi.lo in an accumulator of their own
-//   kH2B  P fp32 in two scaled fp16 parts, Q stored as bf16 (a gradient), scaled to one fp16 part
 //   kX1   P fp32 in three bf16 parts, Q stored as bf16 (a gradient) and so its own one part: three products
 //   kB    both stored as bf16: one bf16 product
-enum ShMode { kX3, kX1, kH2, kH2B, kB };
+enum ShMode { kX3, kX1, kB };
 
 // The products of one 128 x 128 output tile, P rows from bi, Q rows from bj, into acc (zero on entry).
 // 4 waves in a 2 x 2 arrangement, each 64 x 64 as 2 x 2 blocks of 32 x 32 outputs, on the 16-bit MFMAs
 // (v_mfma_f32_32x32x16, fp32 accumulation): when a K step of 16 is staged into LDS every element is split
 // once into its parts (one plane per part); a lane's fragment is 8 consecutive k of one row from each plane.
-// sp, sq: the operands' scales (kH2, kH2B; acc is then sp sq times the product).
 // A stage holds KS K steps (KS (PA + PB) planes, at most six: 24 KiB); the LDS is double
 // buffered, and two register sets hold the global loads of the next two stages, so that the loads
 // of stage k + 2 are issued while stage k multiplies and stage k + 1's loads (issued a stage
 // earlier) are split into LDS. Few products per step take several steps per stage, so that a
 // barrier and the load latency are spread over more MFMAs.
 template <ShMode MODE>
-__device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, int bj, float sp, float sq,
-                                                 uint8_t* lds_raw, f32x16 (&acc)[2][2]) {
-  constexpr bool ABF = MODE == kB, BBF = MODE == kX1 || MODE >= kH2B;  // operands stored as bf16
-  constexpr bool F16 = MODE == kH2 || MODE == kH2B;
-  constexpr int PA = MODE <= kX1 ? 3 : MODE == kB ? 1 : 2;             // parts per operand
-  constexpr int PB = MODE == kX3 ? 3 : MODE == kH2 ? 2 : 1;
-  constexpr int KS = MODE >= kH2B ? 2 : 1;                             // K steps per stage
+__device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, int bj, uint8_t* lds_raw,
+                                                 f32x16 (&acc)[2][2]) {
+  constexpr bool ABF = MODE == kB, BBF = MODE != kX3;  // operands stored as bf16
+  constexpr int PA = ABF ? 1 : 3, PB = BBF ? 1 : 3;    // parts per operand
+  constexpr int KS = MODE == kB ? 2 : 1;               // K steps per stage
   static_assert(KS * (PA + PB) <= 6, "a stage holds at most six planes");
   typedef __attribute__((address_space(1))) const uint8_t g_cu8;
   typedef __attribute__((address_space(1))) const u32x2 g_cu32x2;
@@ -148,29 +125,16 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
   // row r holding k 4 lch .. + 3
   auto plane = [](int u, int o, int p) { return u * (PA + PB) + o * PA + p; };
   // the parts of one operand's four elements into its planes
-  auto put = [&](uint8_t* base, int u, int o, auto v, float sc) {
-    u32x2 h, m, l;
+  auto put = [&](uint8_t* base, int u, int o, auto v) {
     auto st = [&](int p, const u32x2& x) { *reinterpret_cast<u32x2*>(base + plane(u, o, p) * kShPlane) = x; };
-    if constexpr (!F16 && std::is_same<decltype(v), u32x2>::value) {
+    if constexpr (std::is_same<decltype(v), u32x2>::value) {
       st(0, v);
-    } else if constexpr (std::is_same<decltype(v), u32x2>::value) {  // bf16 to one scaled fp16 part
-      typedef float f32x2 __attribute__((ext_vector_type(2)));
-      typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        h[j] = __builtin_bit_cast(
-            uint32_t, __builtin_convertvector(
-                          f32x2{sc * __uint_as_float(v[j] << 16), sc * __uint_as_float(v[j] & 0xffff0000u)}, f16x2));
-      st(0, h);
-    } else if constexpr (!F16) {
+    } else {
+      u32x2 h, m, l;
       split3x4(v, h, m, l);
       st(0, h);
       st(1, m);
       st(2, l);
-    } else {
-      split2x4(v, sc, h, l);
-      st(0, h);
-      st(1, l);
     }
   };
   auto lstore = [&](int s, const TA (&ra)[KS][2], const TB (&rb)[KS][2]) {
@@ -180,28 +144,19 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
       for (int j = 0; j < 2; ++j) {
         const int r = lrow + 64 * j;
         uint8_t* base = lds_raw + s * kShStage + split_slot(r, lch >> 1) * 16 + (lch & 1) * 8;
-        put(base, u, 0, ra[u][j], sp);
-        put(base, u, 1, rb[u][j], sq);
+        put(base, u, 0, ra[u][j]);
+        put(base, u, 1, rb[u][j]);
       }
   };
-  using Frag = typename std::conditional<F16, h2_f16x8, bf16x8_t>::type;
   auto frag = [&](int s, int pl, int r) {
-    return *reinterpret_cast<const Frag*>(lds_raw + s * kShStage + pl * kShPlane + split_slot(r, fh) * 16);
+    return *reinterpret_cast<const bf16x8_t*>(lds_raw + s * kShStage + pl * kShPlane + split_slot(r, fh) * 16);
   };
-  constexpr bool MIX = F16;
-  f32x16 mix[MIX ? 2 : 1][2];  // 2^11 times the products with a lo part
-  if constexpr (MIX) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) mix[i][j] = f32x16{};
-  }
   // the products term by term over the four blocks, so that consecutive MFMAs use different
-  // accumulators (parts 0, 1, 2 = hi, mid or lo, lo)
+  // accumulators (parts 0, 1, 2 = hi, mid, lo)
   auto mfma_stage = [&](int s) {
 #pragma unroll
     for (int u = 0; u < KS; ++u) {
-      Frag af[2][PA], bf[2][PB];
+      bf16x8_t af[2][PA], bf[2][PB];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
 #pragma unroll
@@ -213,26 +168,19 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
 #pragma unroll
       for (int tm = 0; tm < 6; ++tm) {
         const int pa = kTerm[tm][0], pb = kTerm[tm][1];
-        if (pa >= PA || pb >= PB || (F16 && pa + pb > 1)) continue;
+        if (pa >= PA || pb >= PB) continue;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            if constexpr (MIX) {
-              if (pa + pb > 0) mix[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i][pa], bf[j][pb], mix[i][j], 0, 0, 0);
-              else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i][pa], bf[j][pb], acc[i][j], 0, 0, 0);
-            } else {
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i][pa], bf[j][pb], acc[i][j], 0, 0, 0);
-            }
-          }
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i][pa], bf[j][pb], acc[i][j], 0, 0, 0);
       }
     }
   };
   constexpr int kStep = 16 * KS;  // k per stage
-  constexpr int kTerms = MODE == kX3 ? 6 : MODE == kX1 || MODE == kH2 ? 3 : MODE == kB ? 1 : 2;
+  constexpr int kTerms = MODE == kX3 ? 6 : MODE == kX1 ? 3 : 1;
   constexpr int kMfma = KS * 4 * kTerms;  // MFMAs per stage and wave
-  // split VALU per stage, about
-  constexpr int kSplitValu = MODE == kX3 ? 88 : MODE == kX1 ? 44 : MODE == kH2 ? 72 : MODE == kB ? 0 : 2 * (36 + 20);
+  constexpr int kSplitValu = MODE == kX3 ? 88 : MODE == kX1 ? 44 : 0;  // split VALU per stage, about
   // one stage's products on LDS buffer mb while the next stage's loads (set) are split into buffer
   // sb: with split operands the split's vector instructions and LDS stores are interleaved with the
   // MFMAs (they are independent), so that a wave's MFMA pipe and vector ALU work at the same time
@@ -269,43 +217,35 @@ __device__ __forceinline__ void sh_tile_products(const ShGemmDesc& d, int bi, in
   stage(0, 1, ra1, rb1);
   __syncthreads();
   mfma_stage(1);
-  if constexpr (MIX) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] += (1.0f / kH2LoScale) * mix[i][j];
-  }
   __syncthreads();
 }
 
 // C = alpha P Q^T + beta E + diag I on one 128 x 128 output tile per workgroup, four kernels:
-//   kKindX3      the kX3 products: Shampoo's, Newton's roots and the QR block updates, whose operands have no bound
-//                or any grading; three workgroups per CU (48 KiB of LDS, 170 registers)
-//   kKindX3U     the kX3 products whose problems all apply the parameter update (in kKindX3 it would spill); three
-//   kKindX1      the kX1 products (Shampoo's P_L G of a bf16 gradient); three per CU
-//   kKindB       both operands bf16 (the statistics of a bf16 gradient); three per CU
-//   kKindScaled  any operand types, fp32 ones in scaled fp16 parts (SOAP); two per CU (the second accumulator)
-// Scaled against three-way split products: the four product launches of one decoder layer (two 14336 x 4096
-// with their transposed third, two 4096 x 4096, two 1024 x 4096; SOAP without refresh) 28.4 -> 21.1 ms.
-// A problem with `fused` applies the parameter update p <- p decay - step C instead of storing C.
+//   kKindX3   the kX3 products
+//   kKindX3U  the kX3 products whose problems all apply the parameter update p <- p decay - step C instead of
+//             storing C (in kKindX3 it would spill)
+//   kKindX1   the kX1 products (P_L G of a bf16 gradient)
+//   kKindB    both operands bf16 (the statistics of a bf16 gradient)
+// Three workgroups per CU each (48 KiB of LDS, 170 registers). No operand is scaled: gradients, moments,
+// statistics and the QR's columns may be graded over any range of rows and columns, and every element keeps its
+// 24 bits (two fp16 parts under one scale per buffer lose them from 2^-28 of its largest element down).
 // Symmetric problems compute the upper tiles only and store each tile transposed as well, through
 // LDS, with coalesced row stores.
 // The tile that workgroup b of n takes: workgroups are dealt to the 8 XCDs round robin; runs of eight
 // consecutive tiles go to one XCD, so that tiles that share operand panels share its L2. The last, partial
 // round keeps the plain order. For the load-bound products with a bf16 operand: statistics of the decoder layer
-// 1.88 -> 1.67 ms; the scaled and X3 products gain nothing
-// (runs of 32 or 64 cost the scaled ones 5 %).
+// 1.88 -> 1.67 ms; the X3 products gain nothing.
 __device__ __forceinline__ int xcd_order(int b, int n) {
   if (b >= n / 64 * 64) return b;
   const int in = b % 64;
   return b - in + (in & 7) * 8 + (in >> 3);
 }
 
-enum ShKind { kKindX3, kKindX3U, kKindX1, kKindB, kKindScaled };
+enum ShKind { kKindX3, kKindX3U, kKindX1, kKindB };
 template <ShKind KIND>
-__global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kernel(
-    const ShGemmDesc* __restrict__ descs, int count, float decay, float step) {
-  constexpr bool X3 = KIND == kKindX3, X3U = KIND == kKindX3U;
+__global__ __launch_bounds__(256, 3) void sh_gemm_kernel(const ShGemmDesc* __restrict__ descs, int count, float decay,
+                                                          float step) {
+  constexpr bool X3 = KIND == kKindX3;
   __shared__ __attribute__((aligned(16))) uint8_t lds_raw[2 * kShStage];
   const int tile = KIND == kKindB || KIND == kKindX1 ? xcd_order(blockIdx.x, gridDim.x) : blockIdx.x;
   const int e = find_desc(descs, count, tile);
@@ -350,92 +290,74 @@ __global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kern
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
-  int ex = 0;  // acc is 2^ex times the product
-  if constexpr (X3 || X3U) {
-    sh_tile_products<kX3>(d, bi, bj, 1.0f, 1.0f, lds_raw, acc);
-  } else if constexpr (KIND == kKindX1) {
-    sh_tile_products<kX1>(d, bi, bj, 1.0f, 1.0f, lds_raw, acc);
-  } else if (KIND == kKindB || (KIND == kKindScaled && d.q_bf16 && d.p_bf16)) {
-    sh_tile_products<kB>(d, bi, bj, 1.0f, 1.0f, lds_raw, acc);
-  } else {
-    // the operands' scales, from their bounds (no slot: elements are at most 1)
-    const int ep = d.pmax ? scale_exponent(*d.pmax) : 13, eq = d.qmax ? scale_exponent(*d.qmax) : 13;
-    const float sp = ldexpf(1.0f, ep), sq = ldexpf(1.0f, eq);
-    ex = ep + eq;
-    if (d.q_bf16)
-      sh_tile_products<kH2B>(d, bi, bj, sp, sq, lds_raw, acc);
-    else
-      sh_tile_products<kH2>(d, bi, bj, sp, sq, lds_raw, acc);
-  }
+  sh_tile_products<KIND == kKindB ? kB : KIND == kKindX1 ? kX1 : kX3>(d, bi, bj, lds_raw, acc);
 
-  if constexpr (X3U || KIND == kKindScaled) {
-    if (X3U || d.fused) {
-      // The parameter update, a row half of the tile at a time: C through LDS (64 rows of 128 fp32, 16-byte
-      // slots XOR-permuted by the row), the old parameter's words loaded before the exchange, four
-      // consecutive elements per lane where rows and buffers are aligned to them, or one at a time over a
-      // row's 64 lanes.
-      const ShApplyDesc& a = *d.fused;
-      typedef __attribute__((address_space(3))) float l_f32;
-      typedef __attribute__((address_space(3))) f32x4 l_f32x4;
-      typedef __attribute__((address_space(3))) uint8_t l_u8;
-      l_u8* img = (l_u8*)lds_raw;
-      const bool vec = (a.n & 3) == 0 && (reinterpret_cast<uintptr_t>(a.update_out) & 15) == 0 &&
-                       (reinterpret_cast<uintptr_t>(a.param) & (a.param_dtype == kDtBF16 ? 7 : 15)) == 0;
-      auto at = [](int r, int c) { return r * 512 + (((c >> 2) ^ (r & 31)) << 4) + (c & 3) * 4; };
-      const int64_t r0 = int64_t(bi) * kShTile, c0 = int64_t(bj) * kShTile;
+  if constexpr (KIND == kKindX3U) {
+    // The parameter update, a row half of the tile at a time: C through LDS (64 rows of 128 fp32, 16-byte
+    // slots XOR-permuted by the row), the old parameter's words loaded before the exchange, four
+    // consecutive elements per lane where rows and buffers are aligned to them, or one at a time over a
+    // row's 64 lanes.
+    const ShApplyDesc& a = *d.fused;
+    typedef __attribute__((address_space(3))) float l_f32;
+    typedef __attribute__((address_space(3))) f32x4 l_f32x4;
+    typedef __attribute__((address_space(3))) uint8_t l_u8;
+    l_u8* img = (l_u8*)lds_raw;
+    const bool vec = (a.n & 3) == 0 && (reinterpret_cast<uintptr_t>(a.update_out) & 15) == 0 &&
+                     (reinterpret_cast<uintptr_t>(a.param) & (a.param_dtype == kDtBF16 ? 7 : 15)) == 0;
+    auto at = [](int r, int c) { return r * 512 + (((c >> 2) ^ (r & 31)) << 4) + (c & 3) * 4; };
+    const int64_t r0 = int64_t(bi) * kShTile, c0 = int64_t(bj) * kShTile;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        auto exchange = [&] {
-          if (h == 1) __syncthreads();  // the first half's reads are done
-          if (wr == h) {
+    for (int h = 0; h < 2; ++h) {
+      auto exchange = [&] {
+        if (h == 1) __syncthreads();  // the first half's reads are done
+        if (wr == h) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+          for (int i = 0; i < 2; ++i)
 #pragma unroll
-              for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                  const int rl = i * 32 + 8 * (v >> 2) + 4 * fh + (v & 3), c = wc * 64 + j * 32 + fr;
-                  *(l_f32*)(img + at(rl, c)) = d.alpha * (X3U ? acc[i][j][v] : ldexpf(acc[i][j][v], -ex));
-                }
-          }
-          __syncthreads();
-        };
-        if (vec) {
-          const int c = (t & 31) * 4;
-          constexpr int NB = X3U ? 4 : 8;  // rows per thread whose words are held at a time (8: 17 registers spill, 4: 10)
-          ParamWords<4> pw[NB];
-          auto row = [&](int it) { return it * 8 + (t >> 5); };
-          auto inside = [&](int it) { return r0 + 64 * h + row(it) < a.m && c0 + c < a.n; };
-          auto at_param = [&](int it) { return (r0 + 64 * h + row(it)) * a.n + c0 + c; };
-#pragma unroll
-          for (int b0 = 0; b0 < 8; b0 += NB) {
-#pragma unroll
-            for (int k = 0; k < NB; ++k)
-              if (inside(b0 + k)) pw[k].load(a.param, a.param_dtype, at_param(b0 + k));
-            if (b0 == 0) exchange();
-#pragma unroll
-            for (int k = 0; k < NB; ++k)
-              if (inside(b0 + k)) {
-                const f32x4 o = *(l_f32x4*)(img + at(row(b0 + k), c));
-                pw[k].store(a.param, a.param_dtype, a.update_out, at_param(b0 + k), decay, step, {o[0], o[1], o[2], o[3]});
+              for (int v = 0; v < 16; ++v) {
+                const int rl = i * 32 + 8 * (v >> 2) + 4 * fh + (v & 3), c = wc * 64 + j * 32 + fr;
+                *(l_f32*)(img + at(rl, c)) = d.alpha * acc[i][j][v];
               }
-          }
-        } else {
-          exchange();
-#pragma unroll 8
-          for (int it = 0; it < 32; ++it) {
-            const int rl = (it >> 1) * 4 + (t >> 6), c = (it & 1) * 64 + lane;
-            const int64_t r = r0 + 64 * h + rl;
-            if (r < a.m && c0 + c < a.n) {
-              ParamWords<1> pw;
-              pw.load(a.param, a.param_dtype, r * a.n + c0 + c);
-              pw.store(a.param, a.param_dtype, a.update_out, r * a.n + c0 + c, decay, step, {*(l_f32*)(img + at(rl, c))});
+        }
+        __syncthreads();
+      };
+      if (vec) {
+        const int c = (t & 31) * 4;
+        constexpr int NB = 4;  // rows per thread whose words are held at a time (8: 17 registers spill, 4: 10)
+        ParamWords<4> pw[NB];
+        auto row = [&](int it) { return it * 8 + (t >> 5); };
+        auto inside = [&](int it) { return r0 + 64 * h + row(it) < a.m && c0 + c < a.n; };
+        auto at_param = [&](int it) { return (r0 + 64 * h + row(it)) * a.n + c0 + c; };
+#pragma unroll
+        for (int b0 = 0; b0 < 8; b0 += NB) {
+#pragma unroll
+          for (int k = 0; k < NB; ++k)
+            if (inside(b0 + k)) pw[k].load(a.param, a.param_dtype, at_param(b0 + k));
+          if (b0 == 0) exchange();
+#pragma unroll
+          for (int k = 0; k < NB; ++k)
+            if (inside(b0 + k)) {
+              const f32x4 o = *(l_f32x4*)(img + at(row(b0 + k), c));
+              pw[k].store(a.param, a.param_dtype, a.update_out, at_param(b0 + k), decay, step, {o[0], o[1], o[2], o[3]});
             }
+        }
+      } else {
+        exchange();
+#pragma unroll 8
+        for (int it = 0; it < 32; ++it) {
+          const int rl = (it >> 1) * 4 + (t >> 6), c = (it & 1) * 64 + lane;
+          const int64_t r = r0 + 64 * h + rl;
+          if (r < a.m && c0 + c < a.n) {
+            ParamWords<1> pw;
+            pw.load(a.param, a.param_dtype, r * a.n + c0 + c);
+            pw.store(a.param, a.param_dtype, a.update_out, r * a.n + c0 + c, decay, step, {*(l_f32*)(img + at(rl, c))});
           }
         }
       }
-      return;
     }
+    return;
   }
 
   // Epilogue, in two passes over the tile's row halves (the waves with wr = h hold rows
@@ -456,8 +378,7 @@ __global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kern
   const bool diag_tile = d.sym && bi == bj;
   const int64_t r0 = int64_t(bi) * kShTile, c0 = int64_t(bj) * kShTile;
   float* tl = reinterpret_cast<float*>(lds_raw);
-  float res = 0.0f;   // max |C - I| over this thread's elements of the real block
-  uint32_t big = 0;  // the largest |C| among this thread's elements (bit pattern: NaN above infinity)
+  float res = 0.0f;  // max |C - I| over this thread's elements of the real block
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     if (h == 1 && (E || d.sym)) __syncthreads();  // the first half's LDS reads are done
@@ -485,14 +406,12 @@ __global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kern
             const int r = 64 * h + rl, c = wc * 64 + j * 32 + fr;
             if (diag_tile && r > c) continue;  // filled from the upper triangle below
             const int64_t gr = r0 + r, gc = c0 + c;
-            float x = d.alpha * (KIND != kKindScaled ? acc[i][j][v] : ldexpf(acc[i][j][v], -ex));
+            float x = d.alpha * acc[i][j][v];
             if (E) x += d.beta * tl[rl * kShTile + c];
             if (gr == gc) x += d.diag;
             C[gr * d.ldc + gc] = x;
             acc[i][j][v] = x;
-            if constexpr (KIND == kKindScaled) {
-              big = max(big, __float_as_uint(x) & 0x7fffffffu);
-            } else if (X3 && gr < d.valid && gc < d.valid) {
+            if (X3 && gr < d.valid && gc < d.valid) {
               const float dv = fabsf(x - (gr == gc ? 1.0f : 0.0f));
               res = (dv > res || dv != dv) ? dv : res;  // keeps a NaN
             }
@@ -522,9 +441,6 @@ __global__ __launch_bounds__(256, KIND == kKindScaled ? 2 : 3) void sh_gemm_kern
       }
     }
   }
-  if constexpr (KIND == kKindScaled) {
-    if (d.cmax) slot_max(d.cmax, big);
-  }
   if (X3 && d.resid_out) {
     // NaN propagates as the largest bit pattern, so a diverged side never counts as converged
     uint32_t rb = __float_as_uint(res);
@@ -544,7 +460,6 @@ __global__ __launch_bounds__(256) void sh_copy_in_kernel(const ShCopyDesc* __res
   const int t = threadIdx.x, c = t & 63, rr = t >> 6;
   typedef __attribute__((address_space(1))) uint16_t g_u16;
   const int64_t gc = int64_t(tj) * kShCopyTile + c;
-  uint32_t big = 0;  // largest |v| (bit pattern)
   // a bf16 destination takes the value's upper 16 bits: exact, the values being bf16 numbers
   auto put = [&](void* base, int64_t i, float v) {
     if (d.dst_bf16) ((g_u16*)base)[i] = uint16_t(__float_as_uint(v) >> 16);
@@ -557,9 +472,7 @@ __global__ __launch_bounds__(256) void sh_copy_in_kernel(const ShCopyDesc* __res
     const float v = (gr < d.rows && gc < d.cols) ? ld_any(d.src, gr * d.ld_src + gc, d.src_dtype) : 0.0f;
     if (d.dst) put(d.dst, gr * d.ld_dst + gc, v);
     tt[r][c] = v;
-    big = max(big, __float_as_uint(v) & 0x7fffffffu);
   }
-  if (d.amax) slot_max(d.amax, big);
   if (d.dstT) {
     __syncthreads();
 #pragma unroll 4
@@ -698,14 +611,12 @@ hipError_t launch_sh_gemm(const ShGemmDesc* d, int count, int total_tiles, int k
   if (total_tiles <= 0 || count <= 0) return hipSuccess;
   if (kind == kShX3)
     hipLaunchKernelGGL(sh_gemm_kernel<kKindX3>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
-  else if (kind == kShB)
-    hipLaunchKernelGGL(sh_gemm_kernel<kKindB>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
   else if (kind == kShX3U)
     hipLaunchKernelGGL(sh_gemm_kernel<kKindX3U>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
   else if (kind == kShX1)
     hipLaunchKernelGGL(sh_gemm_kernel<kKindX1>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
   else
-    hipLaunchKernelGGL(sh_gemm_kernel<kKindScaled>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
+    hipLaunchKernelGGL(sh_gemm_kernel<kKindB>, dim3(total_tiles), dim3(256), 0, st, d, count, decay, step);
   return hipGetLastError();
 }
 

@@ -122,7 +122,6 @@ __global__ __launch_bounds__(256) void soap_prep_kernel(const SoapPrepDesc* __re
   g_f32* GMt = (g_f32*)(d.GMt);
   g_f32* GM = (g_f32*)(d.GM);
   g_f32* Mr = (g_f32*)(d.Mr);
-  uint32_t gbig = 0, mbig = 0;
   // G (and G^T) as bf16: the value's upper 16 bits, exact for a bf16 gradient
   auto put_g = [&](g_f32* base, int64_t i, float v) {
     if (d.g_bf16) ((g_u16*)base)[i] = uint16_t(__float_as_uint(v) >> 16);
@@ -149,11 +148,7 @@ __global__ __launch_bounds__(256) void soap_prep_kernel(const SoapPrepDesc* __re
     }
     tg[r][c] = g;
     tm[r][c] = mo;
-    gbig = max(gbig, __float_as_uint(g) & 0x7fffffffu);
-    mbig = max(mbig, __float_as_uint(mo) & 0x7fffffffu);
   }
-  slot_max(d.gmax, gbig);
-  slot_max(d.mmax, mbig);
   if (!GMt) return;  // (uniform over the workgroup: no barrier is skipped by part of it)
   __syncthreads();
 #pragma unroll 4
@@ -176,7 +171,6 @@ __global__ __launch_bounds__(256) void soap_adam_kernel(const SoapAdamDesc* __re
   const int t = threadIdx.x, c = t & 63, rr = t >> 6;
   const int64_t gc = int64_t(tj) * kTile + c;
   const g_cf32* GMr = (const g_cf32*)(d.GMr);
-  uint32_t big = 0;
 #pragma unroll 4
   for (int i = 0; i < 16; ++i) {
     const int r = rr + 4 * i;
@@ -191,10 +185,8 @@ __global__ __launch_bounds__(256) void soap_adam_kernel(const SoapAdamDesc* __re
       np_ = (mq * inv_bc1) / (sqrtf(v) * inv_sqrt_bc2 + eps);
     }
     tn[r][c] = np_;
-    big = max(big, __float_as_uint(np_) & 0x7fffffffu);
     if (d.Np) ((g_f32*)(d.Np))[gr * d.np + gc] = np_;
   }
-  slot_max(d.nmax, big);
   if (!d.NpT) return;  // (uniform over the workgroup)
   __syncthreads();
   g_f32* NpT = (g_f32*)(d.NpT);

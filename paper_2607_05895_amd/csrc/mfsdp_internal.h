@@ -47,21 +47,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 constexpr int kDtF32 = 0;
 constexpr int kDtBF16 = 1;
 
-// The largest of the workgroup's values (bit patterns of |x|: NaN above infinity) into a slot. Every thread
-// calls it. One atomic per workgroup, and only when it raises the slot (tens of thousands of workgroups of
-// an elementwise pass share one slot).
-__device__ __forceinline__ void slot_max(uint32_t* slot, uint32_t big) {
-  __shared__ uint32_t red[16];
-  for (int o = 32; o > 0; o >>= 1) big = max(big, uint32_t(__shfl_xor(int(big), o)));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = big;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (unsigned w = 1; w < blockDim.x >> 6; ++w) big = max(big, red[w]);
-    if (big > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(slot, big);
-  }
-  __syncthreads();
-}
-
 // A parameter update p <- p decay - step O of V = 1 or 4 consecutive elements, in two halves: the old words are
 // loaded long before O is there. Four elements are one access at any address of their own type's alignment (rows
 // of odd n): global memory takes unaligned vectors, split by the hardware only where they cross a line.

@@ -46,7 +46,7 @@ struct Arena {
 };
 
 enum OpKind {
-  kOpCopyIn, kOpCopyOut, kOpGemm, kOpGemmX3, kOpGemmX3U, kOpGemmB, kOpGemmX1, kOpNorm, kOpScalars, kOpInit, kOpApply,
+  kOpCopyIn, kOpCopyOut, kOpGemmX3, kOpGemmX3U, kOpGemmB, kOpGemmX1, kOpNorm, kOpScalars, kOpInit, kOpApply,
   kOpRoot, kOpRootIn, kOpRootOut,
   kOpSoapPrep, kOpSoapAdam, kOpEye, kOpQrPanel, kOpQrCol, kOpQrT,
   kOpFork,  // the auxiliary stream waits for everything enqueued so far on the caller's stream
@@ -84,14 +84,6 @@ struct Build {
     std::memcpy(h.data() + o, v.data(), v.size() * sizeof(T));
     return o;
   }
-  // Slots for the largest |element| of a buffer (bit patterns), in the descriptor region, so that the
-  // upload clears them. reserve_slots comes first; desc_at: the region's offset in the workspace.
-  size_t desc_at = 0, slots = 0;
-  void reserve_slots(size_t region, size_t n) {
-    desc_at = region;
-    slots = put(std::vector<uint32_t>(n, 0u));
-  }
-  uint32_t* slot(size_t i) const { return ptr<uint32_t>(desc_at + slots) + i; }
   int aux = 0;  // stream of the ops added next
   template <class T>
   void op(OpKind k, const std::vector<T>& v, int total) {
@@ -177,13 +169,11 @@ inline int run(Build& b, char* ws, size_t desc_at, hipStream_t main_st, const Ru
     switch (o.kind) {
       case kOpCopyIn: e = launch_sh_copy(reinterpret_cast<ShCopyDesc*>(dp), o.count, o.total, 0, st); break;
       case kOpCopyOut: e = launch_sh_copy(reinterpret_cast<ShCopyDesc*>(dp), o.count, o.total, 1, st); break;
-      case kOpGemm:
       case kOpGemmX3:
       case kOpGemmX3U:
       case kOpGemmB:
       case kOpGemmX1: {
-        const int kind = o.kind == kOpGemm ? kShScaled : o.kind == kOpGemmX3 ? kShX3 : o.kind == kOpGemmX3U ? kShX3U
-                         : o.kind == kOpGemmB ? kShB : kShX1;
+        const int kind = o.kind == kOpGemmX3 ? kShX3 : o.kind == kOpGemmX3U ? kShX3U : o.kind == kOpGemmB ? kShB : kShX1;
         e = launch_sh_gemm(reinterpret_cast<ShGemmDesc*>(dp), o.count, o.total, kind, s.decay, s.step, st);
         break;
       }

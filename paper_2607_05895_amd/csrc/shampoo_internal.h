@@ -66,13 +66,8 @@ struct ShGemmDesc {
   int32_t valid;
   // operand stored as bf16 (a bf16 gradient; row stride in elements): both P and Q, or Q alone
   int32_t p_bf16, q_bf16;
-  // scaled products: the largest |element| of P and of Q so far, as fp32 bit patterns (null: elements are
-  // at most 1), and a slot that receives C's (atomic max; null: not needed)
-  const uint32_t* pmax;
-  const uint32_t* qmax;
-  uint32_t* cmax;
-  // kShX3U, kShScaled: apply the parameter update p <- p decay - step C (and C to update_out) to the real
-  // block instead of storing C; null: store C
+  // kShX3U: apply the parameter update p <- p decay - step C (and C to update_out) to the real block instead of
+  // storing C
   const struct ShApplyDesc* fused;
 };
 
@@ -91,7 +86,6 @@ struct ShCopyDesc {
   int32_t tiles_n;     // column tiles of the domain
   int32_t tile_begin;
   int32_t dst_bf16;    // dir 0: dst and dstT hold bf16
-  uint32_t* amax;      // dir 0: receives the largest |element| (bit pattern, atomic max; may be null)
 };
 
 // Sum of squares and trace of a padded d_pad x d_pad statistic, in row chunks (fp64 partials).
@@ -179,9 +173,8 @@ struct ShApplyDesc {
 };
 
 // kind: three-way bf16 splits (operands of any range), without or with the parameter update in every problem, the
-// same of P with a bf16 Q, all operands bf16, or scaled two-way fp16 splits and one-part operands; decay and
-// step are those of the problems that apply a parameter update (kShX3U and kShScaled)
-enum { kShX3, kShX3U, kShX1, kShB, kShScaled };
+// same of P with a bf16 Q, or all operands bf16; decay and step are those of the parameter update (kShX3U)
+enum { kShX3, kShX3U, kShX1, kShB };
 hipError_t launch_sh_gemm(const ShGemmDesc* d, int count, int total_tiles, int kind, float decay, float step,
                           hipStream_t st);
 hipError_t launch_sh_copy(const ShCopyDesc* d, int count, int total_tiles, int dir, hipStream_t st);

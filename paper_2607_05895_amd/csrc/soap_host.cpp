@@ -16,11 +16,10 @@
 //   N       = Z Q_R^T            P = Z,      Q = Q_R                (mp x np, K = np)
 //   L, R statistics              P = Q = G (sym, K = np), P = Q = G^T (sym, K = mp)
 //   refresh S^T = Q_L^T L        P = Q_L^T,  Q = L                  (mp x mp, K = mp)
-// The products run on the GEMM's scaled fp16 splits: the pass or product that writes an operand
-// records its largest element in a slot, from which the operand's scale follows. A bf16 gradient is
+// fp32 operands are split into three bf16 parts, which hold operands of any grading (moments and gradients
+// with rows or columns far below the largest, statistics, the QR's columns). A bf16 gradient is
 // kept as bf16 (G, and the G^T half of [G^T ; M^T]) and is a one-part operand: the statistics then take one
-// product per step, Q_L^T G two, the others three. The QR's block updates keep three-way bf16 splits,
-// which hold columns of any grading. For a wide matrix (n > m) with both bases the right product runs first (X1 = Q_R^T [G^T | M^T] with G
+// product per step, Q_L^T G three, the others six. For a wide matrix (n > m) with both bases the right product runs first (X1 = Q_R^T [G^T | M^T] with G
 // and M read row-major, then [G' | M'] = Q_L^T X1^T), so that the larger product is the one with
 // the one-part G.
 // The first-moment pass writes G, G^T and M^T; the Adam pass writes N'^T; both bases are copied in
@@ -80,18 +79,13 @@ struct Prod {
   int sym;
   float alpha, beta;
   bool pbf = false, qbf = false;  // P, Q stored as bf16 (one-part operands; both, or Q alone)
-  // scaled products: slots of the operands' largest elements, and the one that receives C's
-  uint32_t *pmax = nullptr, *qmax = nullptr, *cmax = nullptr;
   const ShApplyDesc* fused = nullptr;  // apply the parameter update instead of storing C
 };
 
-// kind: kOpGemm (scaled fp16 splits), kOpGemmX3 (three-way bf16 splits: the QR, columns of any grading) or
-// kOpGemmB (both operands bf16).
-void add_gemm(Build& b, std::vector<Prod> ps, OpKind kind = kOpGemm) {
+void add_gemm_kind(Build& b, std::vector<Prod> ps, OpKind kind) {
   if (ps.empty()) return;
-  // longest tiles first (K times the MFMAs per step): the hardware dispatches blocks in order
-  auto cost = [](const Prod& x) { return x.K * (x.pbf && x.qbf ? 1 : x.qbf ? 2 : 3); };
-  std::stable_sort(ps.begin(), ps.end(), [&](const Prod& x, const Prod& y) { return cost(x) > cost(y); });
+  // longest tiles first: the hardware dispatches blocks in order
+  std::stable_sort(ps.begin(), ps.end(), [](const Prod& x, const Prod& y) { return x.K > y.K; });
   std::vector<ShGemmDesc> gs;
   int gt = 0;
   for (const Prod& p : ps) {
@@ -99,12 +93,19 @@ void add_gemm(Build& b, std::vector<Prod> ps, OpKind kind = kOpGemm) {
                            p.beta, 0.0f, gt));
     gs.back().p_bf16 = p.pbf ? 1 : 0;
     gs.back().q_bf16 = p.qbf ? 1 : 0;
-    gs.back().pmax = p.pmax;
-    gs.back().qmax = p.qmax;
-    gs.back().cmax = p.cmax;
     gs.back().fused = p.fused;
   }
   b.op(kind, gs, gt);
+}
+
+// A launch for each kind of product: both operands bf16, Q bf16, both fp32 with the parameter update or without.
+void add_gemm(Build& b, const std::vector<Prod>& all) {
+  for (OpKind kind : {kOpGemmB, kOpGemmX1, kOpGemmX3, kOpGemmX3U}) {
+    std::vector<Prod> ps;
+    for (const Prod& p : all)
+      if (kind == (p.pbf ? kOpGemmB : p.qbf ? kOpGemmX1 : p.fused ? kOpGemmX3U : kOpGemmX3)) ps.push_back(p);
+    add_gemm_kind(b, ps, kind);
+  }
 }
 
 // The block update's products for each side, over X = the trailing columns of S (rows [j0 + 128,
@@ -222,7 +223,7 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
       add_wx(b, act, j0, kWRest, wr);
       b.fork();
       b.aux = 1;
-      add_gemm(b, wr, kOpGemmX3);
+      add_gemm(b, wr);
       b.aux = 0;
     }
     // G = V^T V and the next block's rows of W in K chunks (both read only Vt), then the block's T, V from
@@ -246,7 +247,7 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
         tt += int(vrows / 64 * (kQrBlock / 64)) + (next ? kQrSumWgs : 0);
       }
       add_wx(b, act, j0, kWNext, gp);
-      add_gemm(b, gp, kOpGemmX3);
+      add_gemm(b, gp);
       b.op(kOpQrT, td, tt);
     }
     // U = V T^T; X <- X - W U^T for the next block's columns first, then (on the auxiliary stream,
@@ -256,14 +257,14 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
       for (QrSide* s : act)
         up.push_back(Prod{b.ptr<float>(s->V), b.ptr<float>(s->T), nullptr, b.ptr<float>(s->U), kQrBlock, kQrBlock, 0,
                           kQrBlock, s->dp - j0, kQrBlock, kQrBlock, 0, 1.0f, 0.0f});
-      add_gemm(b, up, kOpGemmX3);
+      add_gemm(b, up);
       std::vector<Prod> xn, xr;
       add_wx(b, act, j0, kXNext, xn);
-      add_gemm(b, xn, kOpGemmX3);
+      add_gemm(b, xn);
       add_wx(b, act, j0, kXRest, xr);
       b.fork();
       b.aux = 1;
-      add_gemm(b, xr, kOpGemmX3);
+      add_gemm(b, xr);
       b.aux = 0;
     }
   }
@@ -390,10 +391,6 @@ size_t build_soap(const mfsdp_soap_entry* en, int64_t count, const mfsdp_soap_hp
     }
   }
   desc_at = a.off;
-  // slots of one entry: the largest |element| of G, M, Q_L, Q_R, the two halves of X1, N', Z, L and R
-  enum { kSG, kSM, kSQL, kSQR, kSX, kSXm, kSN, kSZ, kSL, kSR, kSlots };
-  b.reserve_slots(desc_at, size_t(count) * kSlots);
-  auto slot = [&](int64_t i, int k) { return b.slot(size_t(i) * kSlots + size_t(k)); };
   auto fp = [&](size_t off) { return off == kNone ? nullptr : b.ptr<float>(off); };
   // statistic and basis (row-major) of each side: the caller's buffers or their padded copies
   auto Lb = [&](const SoapPlan& e) { return e.lin ? en[&e - P.data()].L : b.ptr<float>(e.Lp); };
@@ -411,18 +408,14 @@ size_t build_soap(const mfsdp_soap_entry* en, int64_t count, const mfsdp_soap_hp
         cin.push_back(copy_desc(en[i].L, kDtF32, b.ptr<float>(e.Lp), nullptr, e.m, e.m, e.m, e.mp, 0, e.mp, e.mp, ct));
       cin.push_back(copy_desc(en[i].QL, kDtF32, e.lin ? nullptr : b.ptr<float>(e.QLp), b.ptr<float>(e.QLt), e.m, e.m,
                               e.m, e.mp, e.mp, e.mp, e.mp, ct));
-      cin.back().amax = slot(i, kSQL);
     }
     if (e.right) {
       if (!e.rin)
         cin.push_back(copy_desc(en[i].R, kDtF32, b.ptr<float>(e.Rp), nullptr, e.n, e.n, e.n, e.np, 0, e.np, e.np, ct));
       cin.push_back(copy_desc(en[i].QR, kDtF32, e.rin ? nullptr : b.ptr<float>(e.QRp), b.ptr<float>(e.QRt), e.n, e.n,
                               e.n, e.np, e.np, e.np, e.np, ct));
-      cin.back().amax = slot(i, kSQR);
     }
     SoapPrepDesc d{};
-    d.gmax = slot(i, kSG);
-    d.mmax = slot(i, kSM);
     d.grad = en[i].grad;
     d.exp_avg = en[i].exp_avg;
     d.Gp = fp(e.Gp);
@@ -473,58 +466,48 @@ size_t build_soap(const mfsdp_soap_entry* en, int64_t count, const mfsdp_soap_hp
   }
   const ShApplyDesc* fused = b.ptr<ShApplyDesc>(desc_at + b.put(ap));
   const float ws_ = float(hp->shampoo_weight), bs_ = float(hp->shampoo_beta);
-  std::vector<Prod> ps, p1, p2, p3, p4;  // ps: the statistics of bf16 gradients
+  std::vector<Prod> p1, p2, p3, p4;
   for (SoapPlan& e : P) {
     float* X1 = b.ptr<float>(e.X1);
     float* GMr = b.ptr<float>(e.GMr);
     const int64_t mp = e.mp, np = e.np, i = &e - P.data();
     // a bf16 gradient (stored as bf16 by the first-moment pass) is one part: one product per
-    // statistic, two for Q_L^T G
+    // statistic, three for Q_L^T G
     const bool gbf = en[i].grad_dtype == MFSDP_BF16;
-    auto add = [&](std::vector<Prod>& to, Prod p, int ks, int qs, int cs) {
-      p.pmax = slot(i, ks);
-      p.qmax = slot(i, qs);
-      p.cmax = cs < 0 ? nullptr : slot(i, cs);
-      to.push_back(p);
-    };
     if (e.rfirst) {
       // X1 (as 2 np x mp, row stride mp) = [(G Q_R)^T ; (M Q_R)^T] = Q_R^T [G^T | M^T]; then
       // [G' | M'] = Q_L^T [G Q_R | M Q_R] into GMr; G is bf16 in Gp, M row-major after GMt's G^T rows
       const float* QRt = b.ptr<float>(e.QRt);
-      const float* QLt = b.ptr<float>(e.QLt);
       const float* Mr = b.ptr<float>(e.GMt) + np * mp;
-      add(p1, Prod{QRt, b.ptr<float>(e.Gp), nullptr, X1, np, np, 0, mp, np, mp, np, 0, 1.0f, 0.0f, false, true}, kSQR,
-          kSG, kSX);
-      add(p1, Prod{QRt, Mr, nullptr, X1 + np * mp, np, np, 0, mp, np, mp, np, 0, 1.0f, 0.0f}, kSQR, kSM, kSXm);
-      add(p2, Prod{QLt, X1, nullptr, GMr, mp, mp, 0, 2 * np, mp, np, mp, 0, 1.0f, 0.0f}, kSQL, kSX, -1);
-      add(p2, Prod{QLt, X1 + np * mp, nullptr, GMr + np, mp, mp, 0, 2 * np, mp, np, mp, 0, 1.0f, 0.0f}, kSQL, kSXm, -1);
+      p1.push_back(Prod{QRt, b.ptr<float>(e.Gp), nullptr, X1, np, np, 0, mp, np, mp, np, 0, 1.0f, 0.0f, false, true});
+      p1.push_back(Prod{QRt, Mr, nullptr, X1 + np * mp, np, np, 0, mp, np, mp, np, 0, 1.0f, 0.0f});
+      p2.push_back(Prod{b.ptr<float>(e.QLt), X1, nullptr, GMr, mp, mp, 0, 2 * np, mp, 2 * np, mp, 0, 1.0f, 0.0f});
     } else if (e.left) {
       const float* GMt = b.ptr<float>(e.GMt);
       // the G half of Q_L^T [G | M] has a one-part Q when the gradient is bf16
-      add(p1, Prod{b.ptr<float>(e.QLt), GMt, nullptr, X1, mp, mp, 0, 2 * np, mp, np, mp, 0, 1.0f, 0.0f, false, gbf},
-          kSQL, kSG, kSX);
-      add(p1, Prod{b.ptr<float>(e.QLt), GMt + np * mp, nullptr, X1 + np, mp, mp, 0, 2 * np, mp, np, mp, 0, 1.0f, 0.0f},
-          kSQL, kSM, kSXm);
+      p1.push_back(Prod{b.ptr<float>(e.QLt), GMt, nullptr, X1, mp, mp, 0, 2 * np, mp, np, mp, 0, 1.0f, 0.0f, false,
+                        gbf});
+      p1.push_back(Prod{b.ptr<float>(e.QLt), GMt + np * mp, nullptr, X1 + np, mp, mp, 0, 2 * np, mp, np, mp, 0,
+                        1.0f, 0.0f});
     }
     if (e.left) {
       const float* Gp = b.ptr<float>(e.Gp);
       // the statistics read only G and G^T: an fp32 gradient's join the first launch
-      add(gbf ? ps : p1, Prod{Gp, Gp, Lb(e), Lb(e), np, np, mp, mp, mp, mp, np, 1, ws_, bs_, gbf, gbf}, kSG, kSG, kSL);
-      add(p3, Prod{QLb(e), b.ptr<float>(e.NpT), nullptr, X1, mp, mp, 0, np, mp, np, mp, 0, 1.0f, 0.0f}, kSQL, kSN, kSZ);
+      p1.push_back(Prod{Gp, Gp, Lb(e), Lb(e), np, np, mp, mp, mp, mp, np, 1, ws_, bs_, gbf, gbf});
+      p3.push_back(Prod{QLb(e), b.ptr<float>(e.NpT), nullptr, X1, mp, mp, 0, np, mp, np, mp, 0, 1.0f, 0.0f});
       if (!e.right) p3.back().fused = fused + i;
     }
     if (e.right) {
       const float* GMt = b.ptr<float>(e.GMt);
-      add(gbf ? ps : p1, Prod{GMt, GMt, Rb(e), Rb(e), mp, mp, np, np, np, np, mp, 1, ws_, bs_, gbf, gbf}, kSG, kSG, kSR);
+      p1.push_back(Prod{GMt, GMt, Rb(e), Rb(e), mp, mp, np, np, np, np, mp, 1, ws_, bs_, gbf, gbf});
       if (!e.rfirst)
-        for (int h = 0; h < 2; ++h)  // (without a left basis X1 is [G | M] itself)
-          add(p2, Prod{X1 + h * np, b.ptr<float>(e.QRt), nullptr, GMr + h * np, 2 * np, np, 0, 2 * np, mp, np, np, 0,
-                       1.0f, 0.0f}, (e.left ? kSX : kSG) + h, kSQR, -1);
-      add(p4, Prod{X1, QRb(e), nullptr, GMr, np, np, 0, np, mp, np, np, 0, 1.0f, 0.0f}, e.left ? kSZ : kSN, kSQR, -1);
+        for (int h = 0; h < 2; ++h)
+          p2.push_back(Prod{X1 + h * np, b.ptr<float>(e.QRt), nullptr, GMr + h * np, 2 * np, np, 0, 2 * np, mp, np,
+                            np, 0, 1.0f, 0.0f});
+      p4.push_back(Prod{X1, QRb(e), nullptr, GMr, np, np, 0, np, mp, np, np, 0, 1.0f, 0.0f});
       p4.back().fused = fused + i;
     }
   }
-  add_gemm(b, ps, kOpGemmB);
   add_gemm(b, p1);
   add_gemm(b, p2);
 
@@ -536,7 +519,6 @@ size_t build_soap(const mfsdp_soap_entry* en, int64_t count, const mfsdp_soap_hp
     d.exp_avg_sq = en[&e - P.data()].exp_avg_sq;
     d.NpT = fp(e.NpT);
     d.Np = e.left ? nullptr : b.ptr<float>(e.right ? e.X1 : e.GMr);
-    d.nmax = slot(&e - P.data(), kSN);
     d.m = e.m;
     d.n = e.n;
     d.mp = e.mp;
@@ -570,15 +552,11 @@ size_t build_soap(const mfsdp_soap_entry* en, int64_t count, const mfsdp_soap_hp
       if (e.left) {
         ps.push_back(Prod{b.ptr<float>(e.QLt), Lb(e), nullptr, b.ptr<float>(e.QLp), e.mp, e.mp, 0, e.mp,
                           e.mp, e.mp, e.mp, 0, 1.0f, 0.0f});
-        ps.back().pmax = slot(&e - P.data(), kSQL);
-        ps.back().qmax = slot(&e - P.data(), kSL);
         sides.push_back(&e.L);
       }
       if (e.right) {
         ps.push_back(Prod{b.ptr<float>(e.QRt), Rb(e), nullptr, b.ptr<float>(e.QRp), e.np, e.np, 0, e.np,
                           e.np, e.np, e.np, 0, 1.0f, 0.0f});
-        ps.back().pmax = slot(&e - P.data(), kSQR);
-        ps.back().qmax = slot(&e - P.data(), kSR);
         sides.push_back(&e.R);
       }
     }
@@ -590,11 +568,9 @@ size_t build_soap(const mfsdp_soap_entry* en, int64_t count, const mfsdp_soap_hp
       // one's descriptors.
       std::vector<ShCopyDesc> t1, t2;
       int n1 = 0, n2 = 0;
-      for (size_t k = 0; k < sides.size(); ++k) {
-        QrSide* q = sides[k];
+      for (QrSide* q : sides) {
         t1.push_back(copy_desc(b.ptr<float>(q->Q), kDtF32, b.ptr<float>(q->St), nullptr, q->d, q->d, q->dp, q->dp, 0,
                                q->dp, q->dp, n1));
-        t1.back().amax = ps[k].pmax;  // (the new basis may have larger elements than the old one)
         t2.push_back(copy_desc(b.ptr<float>(q->St), kDtF32, b.ptr<float>(q->St), b.ptr<float>(q->Q), q->d, q->d,
                                q->dp, q->dp, q->dp, q->dp, q->dp, n2));
       }

@@ -50,8 +50,6 @@ struct SoapPrepDesc {
   int32_t tiles_n;
   int32_t tile_begin;
   int32_t g_bf16;
-  uint32_t* gmax;  // receive the largest |G| and |M| (bit patterns, atomic max)
-  uint32_t* mmax;
 };
 
 // Adam in the eigenbasis over the real block: GMr = [G' | M'] (mp x 2 np, row stride 2 np);
@@ -67,7 +65,6 @@ struct SoapAdamDesc {
   int64_t m, n, mp, np;
   int32_t tiles_n;
   int32_t tile_begin;
-  uint32_t* nmax;  // receives the largest |N'| (bit pattern, atomic max)
 };
 
 // X = I over the real d x d block of a padded dp x dp buffer (row stride ld), zero elsewhere.

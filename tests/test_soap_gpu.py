@@ -530,3 +530,86 @@ def test_soap_llama_ffn_shapes_one_sided(native, shape):
     _sync()
     _oracle_step(mat, step, hpo)
     _check(mat, hpo)
+
+
+@pytest.mark.parametrize("gdt", [synth.BF16, synth.F32])
+@pytest.mark.parametrize("shape,maxd", [((129, 300), 4096), ((300, 129), 4096), ((256, 384), 4096), ((300, 140), 200),
+                                        ((140, 300), 200)])
+def test_soap_products_keep_rows_of_any_size(native, shape, maxd, gdt):
+    """Rows and columns far below the largest keep their relative accuracy: gradient and first moment graded over
+    2^-60 along both sides, the bases graded against them (the products do not ask for orthogonal ones). Each
+    projection's element is a sum of products over the chains of K terms; bound: (K + 16) 2^-24 of the sum
+    of their magnitudes (twice that for its square V); the projection back adds the same of N', whose own
+    relative error is M' s and sqrt(V)'s. The statistics against sqrt(S_ii S_jj)."""
+    import torch
+    m, n = shape
+    _say(f"soap graded operands {m}x{n} maxd {maxd} {gdt}")
+    rng = np.random.default_rng(5350 + m)
+    gm, gn = 2.0 ** -np.linspace(0, 30, m).round(), 2.0 ** -np.linspace(0, 30, n).round()
+    x = _Mat(rng, m, n, synth.F32, gdt, maxd=maxd).device()
+    scale = gm[:, None] * gn[None, :]
+    x.dg.copy_(torch.from_numpy(rng.standard_normal((m, n)) * scale).to(x.dg.dtype))
+    x.dM.copy_(to_dev((rng.standard_normal((m, n)) * scale).astype(np.float32), synth.F32))
+    x.dV.zero_()
+    g, mo = from_dev(x.dg), from_dev(x.dM)
+    ql, qr = np.eye(m), np.eye(n)
+    if x.dQL is not None:
+        ql = (rng.standard_normal((m, m)) / gm[:, None] * 2.0 ** -20).astype(np.float32)
+        x.dQL.copy_(to_dev(ql, synth.F32))
+        x.dL.zero_()
+    if x.dQR is not None:
+        qr = (rng.standard_normal((n, n)) / gn[:, None] * 2.0 ** -20).astype(np.float32)
+        x.dQR.copy_(to_dev(qr, synth.F32))
+        x.dR.zero_()
+    ql, qr = ql.astype(np.float64), qr.astype(np.float64)
+    hpn = native.soap_hparams(refresh=False, beta1=0.5, beta2=0.5, eps=1e-30, shampoo_beta=0.5, shampoo_weight=0.5, step=1,
+                               max_precond_dim=maxd)
+    ents = [x.entry(native)]
+    native.soap_step_t(ents, hpn, native.soap_workspace_t(ents, hpn))
+    _sync()
+    tol = (m + n + 32) * 2.0 ** -24
+    a = np.abs
+    mo = 0.5 * mo + 0.5 * g
+    gp, gmag = ql.T @ g @ qr, a(ql).T @ a(g) @ a(qr)
+    v = 0.5 * gp * gp
+    assert np.all(a(from_dev(x.dV) - v) <= tol * (gmag + a(gp)) * gmag), "second moment"
+    # N' from the device's own V, so that only M' and the division enter
+    vd = from_dev(x.dV)
+    den = np.sqrt(vd / 0.5) + 1e-30
+    mp, mmag = (ql.T @ mo @ qr) / 0.5, (a(ql).T @ (a(mo) + 2.0 ** -1 * a(g)) @ a(qr)) / 0.5
+    npr, nerr = mp / den, 2 * tol * mmag / den
+    u, bound = ql @ npr @ qr.T, a(ql) @ (nerr + tol * a(npr)) @ a(qr).T
+    got = from_dev(x.dN)
+    assert np.all(a(got - u) <= bound), np.max(a(got - u) / bound)
+    for dev, s in ((x.dL, g @ g.T), (x.dR, g.T @ g)):
+        if dev is None:
+            continue
+        d = np.sqrt(np.diag(s))
+        err = np.max(a(from_dev(dev) - 0.5 * s) / (d[:, None] * d[None, :]))
+        assert err <= tol, err
+
+
+@pytest.mark.parametrize("low", [2.0 ** -30, 2.0 ** -60])
+def test_soap_refresh_keeps_small_blocks_of_the_statistic(native, low):
+    """A statistic whose second diagonal block is 2^-30 or 2^-60 of the first: the refreshed basis is that of each
+    block on its own (the power step S = L Q_L keeps its small columns; the factor does not depend on their scale
+    while their squares stay in fp32's range)."""
+    import torch
+    m, h = 256, 128
+    _say(f"soap refresh, a diagonal block {low} of the other")
+    rng = np.random.default_rng(54)
+    x = _Mat(rng, m, 200, synth.F32, synth.F32)
+    blocks = [_f32(np.eye(h) + 0.02 * (c + c.T)) for c in (rng.standard_normal((h, h)) for _ in range(2))]
+    L = np.zeros((m, m))
+    L[:h, :h], L[h:, h:] = 2.0 ** 30 * blocks[0], 2.0 ** 30 * low * blocks[1]
+    x.L, x.QL, x.g = L, np.eye(m), np.zeros((m, 200), dtype=np.float32)
+    x.device()
+    hpn = native.soap_hparams(refresh=True, shampoo_beta=0.5, shampoo_weight=0.5, step=2)
+    ents = [x.entry(native)]
+    native.soap_step_t(ents, hpn, native.soap_workspace_t(ents, hpn))
+    _sync()
+    q = from_dev(x.dQL)
+    for k in range(2):
+        s = slice(k * h, (k + 1) * h)
+        assert _sign_aligned_err(q[s, s], OS.orthonormal_factor(blocks[k])) <= Q_TOL
+    np.testing.assert_allclose(q.T @ q, np.eye(m), atol=2e-5)
