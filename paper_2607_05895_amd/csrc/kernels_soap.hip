@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
 #include <utility>
 
 #include "mfsdp_internal.h"
@@ -434,8 +435,9 @@ __global__ __launch_bounds__(kQrColThreads) void qr_col_kernel(const QrColDesc* 
 // first, row by row (one thread per row i; T_kk = tau_k, T_ik = -tau_k sum_{j=i}^{k-1} T_ij (v_j . v_k),
 // from the tau and dot products the panel left in its block); then, with the blocks of G above the
 // diagonal (G summed over its partials in order), neighbouring diagonal blocks T1, T2 of side L = 16, 32,
-// 64 are joined: M = G12 T2, T12 = -T1 M, on the fp32 MFMA (16 x 16 x 4), M held below the diagonal, where T
-// is zero. Three levels of two products: the panel-by-panel form with one output element per thread
+// 64 are joined: M = G12 T2, T12 = -T1 M, on the fp64 MFMA (16 x 16 x 4; with fp32 sums the refreshed basis was 2 to
+// 4 % less orthogonal than with the panel-by-panel form, now it is up to 13 % more), M held below the diagonal,
+// where T is zero. Three levels of two products: the panel-by-panel form with one output element per thread
 // had seven, on a chain that every block waits for. The launch's other workgroups form V from Vt,
 // 64 x 64 elements each, meanwhile.
 __global__ __launch_bounds__(kQrTThreads) void qr_t_kernel(const QrTDesc* __restrict__ descs, int count) {
@@ -453,7 +455,7 @@ __global__ __launch_bounds__(kQrTThreads) void qr_t_kernel(const QrTDesc* __rest
         static_assert(kQrBlock * kQrBlock == 4 * kQrTThreads * kQrSumWgs, "four elements per thread");
         const int o = 4 * (lt * kQrTThreads + t);
         f32x4 s = *(const g_cf32x4*)((const g_cf32*)(d.W) + o);
-        for (int q = 1; q < d.nG; ++q) s += *(const g_cf32x4*)((const g_cf32*)(d.W) + q * kQrBlock * kQrBlock + o);
+        for (int q = 1; q < d.nW; ++q) s += *(const g_cf32x4*)((const g_cf32*)(d.W) + q * kQrBlock * kQrBlock + o);
         *(g_f32x4*)((g_f32*)(d.Ws) + o) = s;
         return;
       }
@@ -473,24 +475,37 @@ __global__ __launch_bounds__(kQrTThreads) void qr_t_kernel(const QrTDesc* __rest
   const QrTDesc& d = descs[blockIdx.x];
   g_f32* T = (g_f32*)(d.T);
   const g_cf32* G = (const g_cf32*)(d.G);
-  // thread t owns column j = t % 128 and every fourth row of both matrices; the partials of G are
-  // summed with every load of one partial in flight together
+  // thread t owns column j = t % 128 and every fourth row of both matrices; G's partials (only what lies
+  // above the diagonal is used: of the left half of the columns, the upper half of the rows) are summed in
+  // order, the loads of four partials in flight together (one partial at a time, the 12 partials of a
+  // 3072-sided statistic cost the refresh of a GPT-2-small layer 0.9 ms)
   constexpr int kM = kQrBlock * kQrBlock / kQrTThreads, kStep = kQrTThreads / kQrBlock;
   const int tj = t % kQrBlock, ti = t / kQrBlock;
-  float g[kM];
 #pragma unroll
-  for (int m = 0; m < kM; ++m) g[m] = 0.0f;
-  for (int q = 0; q < d.nG; ++q) {
-    const g_cf32* Gq = G + int64_t(q) * kQrBlock * kQrBlock;
+  for (int m = 0; m < kM; ++m) Tl[ti + kStep * m][tj] = 0.0f;
+  auto sum_g = [&](auto rows_c) {
+    constexpr int M = decltype(rows_c)::value;
+    float g[M] = {};
+    auto add = [&](int q0, auto parts_c) {
+      constexpr int N = decltype(parts_c)::value;
+      float x[N][M];
 #pragma unroll
-    for (int m = 0; m < kM; ++m) g[m] += Gq[(ti + kStep * m) * kQrBlock + tj];  // (every partial is whole)
-  }
+      for (int p = 0; p < N; ++p)
 #pragma unroll
-  for (int m = 0; m < kM; ++m) {
-    const int i = ti + kStep * m;
-    Tl[i][tj] = 0.0f;
-    Gl[i][tj] = g[m];
-  }
+        for (int m = 0; m < M; ++m) x[p][m] = G[(int64_t(q0 + p) * kQrBlock + ti + kStep * m) * kQrBlock + tj];
+#pragma unroll
+      for (int p = 0; p < N; ++p)
+#pragma unroll
+        for (int m = 0; m < M; ++m) g[m] += x[p][m];
+    };
+    int q = 0;
+    for (; q + 4 <= d.nG; q += 4) add(q, std::integral_constant<int, 4>{});
+    for (; q < d.nG; ++q) add(q, std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int m = 0; m < M; ++m) Gl[ti + kStep * m][tj] = g[m];
+  };
+  if (__builtin_amdgcn_readfirstlane(tj) < kQrBlock / 2) sum_g(std::integral_constant<int, kM / 2>{});
+  else sum_g(std::integral_constant<int, kM>{});
 #pragma unroll
   for (int idx = t; idx < kQrBlock * kQrPanel; idx += kQrTThreads) {
     const int i = idx / kQrPanel, jj = idx % kQrPanel;
@@ -518,34 +533,33 @@ __global__ __launch_bounds__(kQrTThreads) void qr_t_kernel(const QrTDesc* __rest
   }
   __syncthreads();
   // one wave per 16 x 16 output tile; a lane's operands are row (column) lane % 16, k = lane / 16, its
-  // outputs rows 4 (lane / 16) .. + 3 of column lane % 16
+  // outputs rows lane / 16 + 4 r of column lane % 16
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
   const int lane = t & 63, w = t >> 6, lc = lane & 15, lk = lane >> 4;
   for (int L = kQrPanel; L < kQrBlock; L *= 2) {
     const int n = L / 16, per = n * n, tiles = kQrBlock / (2 * L) * per;
     for (int tile = w; tile < tiles; tile += kQrTThreads / 64) {
       const int b = tile / per * 2 * L, i0 = tile % per / n * 16, j0 = tile % n * 16;
-      f32x4 acc[4] = {};
+      f64x4 acc[2] = {};
       for (int k = 0; k < j0 + 16; k += 16)  // T2 is upper triangular
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(Gl[b + i0 + lc][b + L + k + 4 * q + lk],
-                                                        Tl[b + L + k + 4 * q + lk][b + L + j0 + lc], acc[q], 0, 0, 0);
+          acc[q & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(Gl[b + i0 + lc][b + L + k + 4 * q + lk],
+                                                            Tl[b + L + k + 4 * q + lk][b + L + j0 + lc], acc[q & 1], 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        Tl[b + L + i0 + 4 * lk + r][b + j0 + lc] = (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]);
+      for (int r = 0; r < 4; ++r) Tl[b + L + i0 + lk + 4 * r][b + j0 + lc] = float(acc[0][r] + acc[1][r]);
     }
     __syncthreads();
     for (int tile = w; tile < tiles; tile += kQrTThreads / 64) {
       const int b = tile / per * 2 * L, i0 = tile % per / n * 16, j0 = tile % n * 16;
-      f32x4 acc[4] = {};
+      f64x4 acc[2] = {};
       for (int k = i0; k < L; k += 16)  // so is T1
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(Tl[b + i0 + lc][b + k + 4 * q + lk],
-                                                        Tl[b + L + k + 4 * q + lk][b + j0 + lc], acc[q], 0, 0, 0);
+          acc[q & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(Tl[b + i0 + lc][b + k + 4 * q + lk],
+                                                            Tl[b + L + k + 4 * q + lk][b + j0 + lc], acc[q & 1], 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        Tl[b + i0 + 4 * lk + r][b + L + j0 + lc] = -((acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]));
+      for (int r = 0; r < 4; ++r) Tl[b + i0 + lk + 4 * r][b + L + j0 + lc] = -float(acc[0][r] + acc[1][r]);
     }
     __syncthreads();
     // M's place is read as T's zeros by the next level

@@ -57,7 +57,8 @@ struct QrSide {
   size_t St = 0, Q = 0, V = 0, Vt[2] = {}, T = 0, G = 0, Wn = 0, U = 0, Ws = 0, Wq = 0;
 };
 
-constexpr int64_t kQrMaxGram = (kQrMaxDim + kQrGramChunk - 1) / kQrGramChunk;  // partials of V^T V and of W
+constexpr int64_t kQrMaxGram = (kQrMaxDim + kQrGramChunk - 1) / kQrGramChunk;  // partials of V^T V
+constexpr int64_t kQrMaxW = (kQrMaxDim + kQrWChunk - 1) / kQrWChunk;           // and of the next block's W
 
 void plan_qr_buffers(QrSide& s, Arena& a) {
   const size_t f = sizeof(float), col = size_t(s.dp) * kQrBlock * f, sq = size_t(kQrBlock) * kQrBlock * f;
@@ -68,7 +69,7 @@ void plan_qr_buffers(QrSide& s, Arena& a) {
   s.Wq = a.take(col);
   s.T = a.take(sq);
   s.G = a.take(size_t(kQrMaxGram) * sq);
-  s.Wn = a.take(size_t(kQrMaxGram) * sq);
+  s.Wn = a.take(size_t(kQrMaxW) * sq);
 }
 
 // A grouped product before its tile offset is known (so that a launch can be ordered by cost).
@@ -110,7 +111,7 @@ void add_gemm(Build& b, const std::vector<Prod>& all) {
 
 // The block update's products for each side, over X = the trailing columns of S (rows [j0 + 128,
 // dp) of St) and X = Q's columns [j0, dp): kWNext appends W = X V for St's next 128 rows (the next block's
-// columns) in partials of kQrGramChunk, kXNext X <- X - W U^T for them; kWRest and kXRest append the same
+// columns) in partials of kQrWChunk, kXNext X <- X - W U^T for them; kWRest and kXRest append the same
 // for the remaining St rows and for Q, W in one piece.
 enum WxPart { kWNext, kXNext, kWRest, kXRest };
 void add_wx(Build& b, const std::vector<QrSide*>& act, int64_t j0, WxPart part, std::vector<Prod>& ps) {
@@ -132,9 +133,9 @@ void add_wx(Build& b, const std::vector<QrSide*>& act, int64_t j0, WxPart part, 
     };
     if (part == kWNext) {
       float* wn = b.ptr<float>(s->Wn);
-      for (int64_t k0 = 0; has_trail && k0 < vrows; k0 += kQrGramChunk, wn += kQrBlock * kQrBlock)
+      for (int64_t k0 = 0; has_trail && k0 < vrows; k0 += kQrWChunk, wn += kQrBlock * kQrBlock)
         ps.push_back(Prod{XS + k0, Vt + k0, nullptr, wn, s->dp, s->dp, 0, kQrBlock, kQrBlock, kQrBlock,
-                          std::min<int64_t>(kQrGramChunk, vrows - k0), 0, 1.0f, 0.0f});
+                          std::min<int64_t>(kQrWChunk, vrows - k0), 0, 1.0f, 0.0f});
     } else if (part == kWRest) {
       if (has_trail && trail > kQrBlock) w(XS + kQrBlock * s->dp, WS + kQrBlock * kQrBlock, trail - kQrBlock);
       w(XQ, WQ, s->dp);
@@ -243,7 +244,8 @@ void add_qr_ops(Build& b, std::vector<QrSide*> sides) {
         }
         const bool next = vrows > kQrBlock && j0 + kQrBlock < s->d;
         td.push_back(QrTDesc{b.ptr<float>(s->T), b.ptr<float>(s->G), b.ptr<float>(s->Vt[odd]), b.ptr<float>(s->V),
-                             next ? b.ptr<float>(s->Wn) : nullptr, b.ptr<float>(s->Ws), s->dp, ng, tt});
+                             next ? b.ptr<float>(s->Wn) : nullptr, b.ptr<float>(s->Ws), s->dp, ng,
+                             int32_t((vrows + kQrWChunk - 1) / kQrWChunk), tt});
         tt += int(vrows / 64 * (kQrBlock / 64)) + (next ? kQrSumWgs : 0);
       }
       add_wx(b, act, j0, kWNext, gp);

@@ -24,10 +24,10 @@ constexpr int kQrColThreads = 256;    // in-block application: one workgroup per
 constexpr int kQrColGroups = kQrMaxDim / (4 * kQrColThreads);  // groups of four column entries per thread
 constexpr int kQrTThreads = 512;      // block factor: one workgroup per block
 constexpr int kQrSumWgs = 8;          // workgroups that sum one block's partials of W
-// K chunk of the split products V^T V and W = X V of the next block's rows: a tile's serial K loop takes
-// 0.46 us per 16 k, a partial more costs the block factor's one CU a round of loads (12 partials of
-// 256 made it 46 us long)
-constexpr int kQrGramChunk = 512;
+// K chunks of the split products V^T V and W = X V of the next block's rows: a tile's serial K loop takes
+// 0.46 us per 16 k. V^T V's is half as long: its error enters the basis's orthogonality, which chunks of 512 made
+// 1 to 2 % worse from d = 300 on.
+constexpr int kQrGramChunk = 256, kQrWChunk = 512;
 static_assert(kQrBlock == kShTile, "the block update runs on the Shampoo GEMM's tiles");
 
 // M <- beta1 M + (1 - beta1) G over the real m x n block, and the padded layouts the products read
@@ -123,7 +123,7 @@ struct QrTDesc {
   const float* W;  // partials (consecutive 128 x 128 row-major), or null
   float* Ws;
   int64_t ldvt;
-  int32_t nG;
+  int32_t nG, nW;
   int32_t tile_begin;  // first of this problem's other workgroups, counted after the launch's `count` blocks
 };
 

@@ -120,6 +120,27 @@ def test_orthonormal_factor_around_the_row_groups(native, d):
     np.testing.assert_allclose(qg.T @ qg, np.eye(d), atol=2e-5)
 
 
+@pytest.mark.parametrize("d,bar", [(128, 5.4e-7), (768, 1.03e-6)])
+def test_orthonormal_factor_orthogonality(native, d, bar):
+    """||Q^T Q - I||_F / sqrt(d), mean over eight Wishart inputs. It grows with the rounding of V^T V and of the block
+    factor formed from it: with fp32 sums in the factor and V^T V in pieces of 512 it was 6.0e-7 and 1.06e-6, with
+    both in fp32 panel by panel and in pieces of 256 5.8e-7 and 1.015e-6."""
+    import torch
+    _say(f"orthogonality of the factor d={d}")
+    rng = np.random.default_rng(2350 + d)
+    err = []
+    for _ in range(8):
+        A = rng.standard_normal((d, d + 8))
+        a = to_dev((A @ A.T @ _orth(rng, d) / d).astype(np.float32), synth.F32)
+        q = torch.empty((d, d), dtype=torch.float32, device="cuda")
+        native.orthonormal_factor_t(a, q)
+        _sync()
+        qg = from_dev(q).astype(np.float64)
+        err.append(np.linalg.norm(qg.T @ qg - np.eye(d)) / d ** 0.5)
+    _say(f"{np.mean(err):.4g}")
+    assert np.mean(err) <= bar, err
+
+
 def test_orthonormal_factor_rank_deficient_and_signs(native):
     """A rank-deficient input still gives an orthogonal factor with Q^T A upper triangular; on a
     full-rank input LAPACK's signs are reproduced (no column flips)."""
