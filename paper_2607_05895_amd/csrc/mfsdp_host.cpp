@@ -1109,7 +1109,8 @@ int staging_upload(int slot, void* dst, size_t bytes, hipStream_t st) {
 // One auxiliary stream per device (default priority, non-blocking) and a ring of events for the
 // fork / join dependencies between it and the caller's stream, created on first use and kept until
 // the process ends. An event may be recorded again while an earlier wait on it is still pending: a
-// wait takes the record that precedes it on the host.
+// wait takes the record that precedes it on the host. Record and wait are one step under the lock, so that
+// no other thread records the event between them.
 namespace {
 struct AuxState {
   hipStream_t stream = nullptr;
@@ -1120,7 +1121,7 @@ std::mutex g_aux_mu;
 std::vector<AuxState> g_aux;
 }  // namespace
 
-int aux_stream(hipStream_t* out, hipEvent_t* ev) {
+int aux_order(bool fork, hipStream_t main_st, hipStream_t* aux) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
@@ -1133,13 +1134,18 @@ int aux_stream(hipStream_t* out, hipEvent_t* ev) {
       a.stream = nullptr;
       return hip_fail(e, "hipStreamCreateWithFlags");
     }
-    for (hipEvent_t& x : a.events) {
-      e = hipEventCreateWithFlags(&x, hipEventDisableTiming);
-      if (e != hipSuccess) return hip_fail(e, "hipEventCreateWithFlags");
+  }
+  hipEvent_t& ev = a.events[a.next++ % 8];
+  if (!ev) {
+    e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    if (e != hipSuccess) {
+      ev = nullptr;
+      return hip_fail(e, "hipEventCreateWithFlags");
     }
   }
-  *out = a.stream;
-  if (ev) *ev = a.events[a.next++ % 8];
-  return MFSDP_OK;
+  *aux = a.stream;
+  e = hipEventRecord(ev, fork ? main_st : a.stream);
+  if (e == hipSuccess) e = hipStreamWaitEvent(fork ? a.stream : main_st, ev, 0);
+  return e == hipSuccess ? MFSDP_OK : hip_fail(e, "stream fork / join");
 }
 }  // namespace mfsdp

@@ -20,8 +20,9 @@ namespace mfsdp {
 int set_last_error(int status, const std::string& msg);
 int staging_acquire(size_t bytes, void** host);
 int staging_upload(int slot, void* dst, size_t bytes, hipStream_t st);
-// The device's auxiliary stream and (if ev is set) the next event of its ring.
-int aux_stream(hipStream_t* out, hipEvent_t* ev);
+// The device's auxiliary stream waits for everything enqueued so far on main_st (fork), or main_st for everything
+// on the auxiliary stream (join).
+int aux_order(bool fork, hipStream_t main_st, hipStream_t* aux);
 
 namespace shb {
 
@@ -153,12 +154,8 @@ inline int run(Build& b, char* ws, size_t desc_at, hipStream_t main_st, const Ru
   bool forked = false;
   for (const Op& o : b.ops) {
     if (o.kind == kOpFork || o.kind == kOpJoin) {
-      hipEvent_t ev = nullptr;
-      const int rc = aux_stream(&aux, &ev);
+      const int rc = aux_order(o.kind == kOpFork, main_st, &aux);
       if (rc != MFSDP_OK) return rc;
-      hipError_t e = hipEventRecord(ev, o.kind == kOpFork ? main_st : aux);
-      if (e == hipSuccess) e = hipStreamWaitEvent(o.kind == kOpFork ? aux : main_st, ev, 0);
-      if (e != hipSuccess) return hip_err(e, "stream fork / join");
       forked = o.kind == kOpFork;
       continue;
     }

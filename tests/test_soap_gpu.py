@@ -634,3 +634,42 @@ def test_soap_refresh_keeps_small_blocks_of_the_statistic(native, low):
         s = slice(k * h, (k + 1) * h)
         assert _sign_aligned_err(q[s, s], OS.orthonormal_factor(blocks[k])) <= Q_TOL
     np.testing.assert_allclose(q.T @ q, np.eye(m), atol=2e-5)
+
+
+def test_soap_refresh_steps_of_two_threads(native):
+    """Two threads, each on a stream of its own, refresh bases at the same time: both share the device's auxiliary
+    stream and its events, and each gets the bits that it gets alone."""
+    import threading
+    import torch
+    _say("soap refresh from two threads")
+    hpn = native.soap_hparams(refresh=True, step=2)
+
+    def build(k):
+        rng = np.random.default_rng(554 + k)
+        return [_Mat(rng, m, n, synth.BF16, synth.BF16).device() for m, n in ((300, 520), (640, 260 + 90 * k))]
+
+    def steps(mats, stream):
+        ents = [x.entry(native) for x in mats]
+        ws = native.soap_workspace_t(ents, hpn)
+        with torch.cuda.stream(stream):
+            for _ in range(6):
+                native.soap_step_t(ents, hpn, ws)
+        stream.synchronize()
+
+    def run(together):
+        mats = [build(k) for k in range(2)]
+        streams = [torch.cuda.Stream() for _ in mats]
+        _sync()
+        if together:
+            ts = [threading.Thread(target=steps, args=a) for a in zip(mats, streams)]
+            for t in ts:
+                t.start()
+            for t in ts:
+                t.join()
+        else:
+            for a in zip(mats, streams):
+                steps(*a)
+        return [y for g in mats for x in g for y in (x.dp, x.dM, x.dL, x.dR, x.dQL, x.dQR)]
+
+    for a, b in zip(run(False), run(True)):
+        assert torch.equal(a, b)
