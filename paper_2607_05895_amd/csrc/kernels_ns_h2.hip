@@ -356,7 +356,8 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
 
 // Sum of a split Gram product's partial tiles: one workgroup per 16-row slab of an upper tile. Thread t adds
 // the ranges' 8 consecutive columns 8 (t % (T / 8)) of row t / (T / 8) in order, and stores them and, through
-// LDS, the mirrored block rows.
+// LDS, the mirrored block rows. The block on the diagonal takes its lower triangle from its upper one, as in the
+// unsplit product: (i, j) and (j, i) add their mixed products in different orders.
 template <int T, bool DYN>
 __global__ __launch_bounds__(2 * T) void ns_h2_sum_kernel(const GemmDesc* __restrict__ descs, int count, int parity,
                                                           NsH2Exponents he) {
@@ -414,10 +415,18 @@ __global__ __launch_bounds__(2 * T) void ns_h2_sum_kernel(const GemmDesc* __rest
     *(h2_gu4*)o = h;
     *(h2_gu4*)(o + kH2Lo) = l;
   };
-  const int gc = bj * T + c8 * 8;
-  if ((gc >> 4) < np && (gc >> 4) >= rp) put(rp * 16 + row, gc);
   if constexpr (DYN) put_stats<T / 32>(stats, eo, &st->amax, &st->a2, red);  // (with a barrier of its own)
   else __syncthreads();
+  const int gc = bj * T + c8 * 8;
+  if ((gc >> 4) < np && (gc >> 4) >= rp) {
+    if ((gc >> 4) == rp) {  // (then bi == bj)
+      const int c0 = c8 * 8 - slab * 16;  // the thread's first column within the block
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (c0 + k < row) v[k] = tt[c0 + k][slab * 16 + row];
+    }
+    put(rp * 16 + row, gc);
+  }
   // mirror: row `c` of the tile's columns, its 8 values of slab rows 8 h .. 8 h + 7
   const int c = t >> 1, h = t & 1, gm = bj * T + c;
   if ((gm >> 4) >= np || (gm >> 4) <= rp) return;
