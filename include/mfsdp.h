@@ -265,7 +265,7 @@ typedef struct {
 } mfsdp_shampoo_hparams;
 
 /* Bytes of device workspace mfsdp_shampoo_step needs for these entries and hyperparameters:
- * per matrix, zero-padded copies of G and G^T (fp32, or bf16 for a bf16 gradient), P_L G and U
+ * per matrix, zero-padded copies of G and G^T (fp32, or bf16 for a bf16 gradient) and P_L G
  * (3 mp np floats in all) and five
  * padded matrices per side for the root iteration (5 (mp^2 + np^2) floats), mp, np = m, n rounded
  * up to 128; plus launch descriptors. Data pointers are not used. 0 on invalid arguments;

@@ -72,9 +72,9 @@ void plan_side(Side& s, int64_t d, Arena& a) {
   s.xsel = a.take(sizeof(int32_t));
 }
 
-// Gp, GpT: G and G^T zero-padded (fp32, or for a bf16 gradient bf16 G and G^T both in Gp, which
-// leaves GpT free); Y = P_L G (or Y^T = P_R G^T for a wide bf16 G); U goes to Gp for an fp32
-// gradient, GpT for a bf16 one.
+// Gp, GpT: G and G^T zero-padded (of a bf16 gradient both as bf16 in Gp); Y = P_L G (or Y^T = P_R G^T for a
+// wide bf16 G). U is applied as it is formed. (A bf16 gradient's GpT is counted in the workspace's documented
+// size, but not used.)
 struct EntryPlan {
   int64_t m, n, mp, np;
   bool grad_bf16;
@@ -84,7 +84,6 @@ struct EntryPlan {
   size_t gt() const {              // G^T (row stride mp)
     return grad_bf16 ? Gp + size_t(mp) * size_t(np) * 2 : GpT;
   }
-  size_t u() const { return grad_bf16 ? GpT : Gp; }
 };
 
 // The products of the Newton iteration (p = 1, 2); returns the index of the X buffer they end in.
@@ -507,13 +506,13 @@ size_t build_shampoo(const mfsdp_shampoo_entry* en, int64_t count, const mfsdp_s
       gy.push_back(gemm_desc(pr, b.ptr<float>(e.g()), nullptr, b.ptr<float>(e.Y), e.np, e.np, 0, e.mp, e.np,
                              e.mp, e.np, 0, 1.0f, 0.0f, 0.0f, ty));
       gy.back().q_bf16 = 1;
-      gu.push_back(gemm_desc(pl, b.ptr<float>(e.Y), nullptr, b.ptr<float>(e.u()), e.mp, e.mp, 0, e.np, e.mp,
+      gu.push_back(gemm_desc(pl, b.ptr<float>(e.Y), nullptr, nullptr, e.mp, e.mp, 0, e.np, e.mp,
                              e.np, e.mp, 0, 1.0f, 0.0f, 0.0f, tu));
     } else {
       gy.push_back(gemm_desc(pl, b.ptr<float>(e.gt()), nullptr, b.ptr<float>(e.Y), e.mp, e.mp, 0, e.np, e.mp,
                              e.np, e.mp, 0, 1.0f, 0.0f, 0.0f, ty));
       gy.back().q_bf16 = e.grad_bf16 ? 1 : 0;
-      gu.push_back(gemm_desc(b.ptr<float>(e.Y), pr, nullptr, b.ptr<float>(e.u()), e.np, e.np, 0, e.np, e.mp,
+      gu.push_back(gemm_desc(b.ptr<float>(e.Y), pr, nullptr, nullptr, e.np, e.np, 0, e.np, e.mp,
                              e.np, e.np, 0, 1.0f, 0.0f, 0.0f, tu));
     }
   }
