@@ -307,7 +307,9 @@ __global__ __launch_bounds__(256) void prep_kernel(const PrepDesc* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------------------------
-// norm: one workgroup per matrix; fixed-order sum of the tile partials in fp64.
+// norm: one workgroup per matrix; fixed-order sum of the tile partials in fp64. (The fp32 path's exponent of a
+// norm below eps counts what the partials, of at most 64 x 256 elements, can have lost to squares below fp32's
+// smallest denormal, 2^-149.)
 __global__ __launch_bounds__(256) void norm_kernel(const NormDesc* __restrict__ descs, float eps) {
   __shared__ double red[256];
   const NormDesc d = descs[blockIdx.x];
@@ -321,7 +323,15 @@ __global__ __launch_bounds__(256) void norm_kernel(const NormDesc* __restrict__ 
   }
   if (threadIdx.x == 0) {
     const double nrm = sqrt(red[0]);
-    d.scale[0] = float(1.0 / (nrm > double(eps) ? nrm : double(eps)));
+    const bool clamped = !(nrm > double(eps));
+    const double den = clamped ? double(eps) : nrm;
+    d.scale[0] = float(1.0 / den);
+    int small = 0;
+    if (clamped) {
+      const double bound = (nrm + 0x1p-74 * 128.0 * sqrt(double(d.count))) / den;
+      if (bound < 1.0) small = max(0, min(min(kNsH2MaxSmall, 110 + ilogb(den)), -ilogb(bound) - 1));
+    }
+    reinterpret_cast<int32_t*>(d.scale)[1] = small;
   }
 }
 

@@ -41,6 +41,7 @@ constexpr int kGram = 0, kSquare = 1, kUpdate = 2, kApply = 3;
 //             |A_ij| <= min(K max |X|^2, lambda_max(A))               (|A_ij| <= the row norms' squares)
 //             |B'_ij| <= |a| + |b| max |A| + |c| ||A||_F max |A|       (|(A A)_ij| <= lambda_max(A) max |A|)
 //             |X'_ij| <= max |sqrt(y) (a + b y + c y^2)|, 0 <= y <= sqrt(||A A||_F)    (>= lambda_max(A))
+//                                                         or 0 <= y <= lambda_max(A)'s bound from the last step
 //           The maxima and the norms (sums of squares, in integers, so that their order does not matter) are
 //           taken by the epilogues, which costs 1 us per launch and 7 % at 768 x 3072; the last bound squared
 //           is the next step's lambda_max(A). They exceed the largest element by up to about r^(1/4) in the
@@ -84,6 +85,9 @@ __device__ __forceinline__ void put_stats(TileStats s, int e, uint32_t* max_slot
 __device__ __forceinline__ NsH2State* ns_state(const float* scale) {
   return reinterpret_cast<NsH2State*>(reinterpret_cast<uintptr_t>(scale) + kNsH2StateOffset);
 }
+__device__ __forceinline__ const int32_t* ns_small(const float* scale) {
+  return reinterpret_cast<const int32_t*>(scale) + 1;
+}
 __device__ __forceinline__ int gram_exponent(float lam, float xmax, int K) {
   return ns_h2_exponent(fminf(lam, float(K) * xmax * xmax));
 }
@@ -126,9 +130,14 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
   const int mp = d.M >> 4, np = d.N >> 4;      // panels of C's rows and columns
   const int r0 = bi * PB, c0 = bj * PB;
 
-  // DYN: the matrix's state (loaded here, beside the operands' first loads, and used after the loop)
+  // the matrix's state (loaded here, beside the operands' first loads, and used after the loop)
   NsH2State* st = ns_state(d.scale);
-  int ex = he.ex, ea = he.ea, eb = he.eb, eq_in = 0;
+  // (small by a vector load, the oldest outstanding one during the loop: a scalar one was waited for before the
+  // operands' loads, 1.3 % of a step on seven 768/3072/1024x4096 matrices against 0.2 %)
+  int zero = 0;
+  asm volatile("" : "+v"(zero));
+  const int vsmall = DYN ? 0 : ns_small(d.scale)[zero];
+  int ex = 0, ea = he.ea, eb = he.eb, eq_in = 0;
   float lam = 0.0f, xmax = 0.0f, amax = 0.0f, a2 = 0.0f, q2 = 0.0f;
   if constexpr (DYN) {
     ex = st->ex[parity];
@@ -161,10 +170,13 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
     Core::loop(ps, qs, nk, smem, w, lane, acc);
   }
 
+  const int small = __builtin_amdgcn_readfirstlane(vsmall);
+  if constexpr (!DYN) ex = he.ex + max(0, small + he.gx);
+
   // the result's scale 2^eo, and 2^ep that of acc
   const bool first = bi == 0 && bj == 0 && ks == 0 && t == 0;
   const int ep = PK == kGram ? 2 * ex : PK == kSquare ? 2 * ea : eb + ex;
-  int eo = PK == kGram ? ea : PK == kSquare ? eb : he.exn, eq = 0;
+  int eo = PK == kGram ? ea : PK == kSquare ? eb : he.exn + max(0, small + he.gxn), eq = 0;
   if constexpr (DYN && PK == kGram) {
     eo = gram_exponent(lam, xmax, d.K);
     if (first) {
@@ -181,13 +193,14 @@ __global__ __launch_bounds__(256, 2) void ns_h2_kernel(const GemmDesc* __restric
       st->eq = eq;
     }
   } else if constexpr (DYN && PK == kUpdate) {
-    const float bound = ns_h2_next_bound(sqrtf(ldexpf(sqrtf(q2), -eq_in)), ca, cb, cc);
+    const float bound = fminf(ns_h2_next_bound(sqrtf(ldexpf(sqrtf(q2), -eq_in)), ca, cb, cc),
+                              ns_h2_next_bound(lam, ca, cb, cc));
     eo = ns_h2_exponent(bound);
     if (first) {
       st->amax = 0;
       st->a2 = 0;
       st->ex[parity ^ 1] = eo;
-      st->lam[parity ^ 1] = bound * bound;
+      st->lam[parity ^ 1] = fmaxf(bound * bound, 0x1p-120f);
     }
   }
 
@@ -386,7 +399,7 @@ __global__ __launch_bounds__(2 * T) void ns_h2_sum_kernel(const GemmDesc* __rest
     b += *(g_cf32x4*)(part + int64_t(k) * (T * T) + 4);
   }
   NsH2State* st = ns_state(d.scale);
-  const int ep = 2 * (DYN ? st->ex[parity] : he.ex);
+  const int ep = 2 * (DYN ? st->ex[parity] : he.ex + max(0, *ns_small(d.scale) + he.gx));
   const int eo = DYN ? gram_exponent(st->lam[parity], __uint_as_float(st->xmax[parity]), d.K) : he.ea;
   float v[8];
   TileStats stats;
@@ -449,12 +462,13 @@ __global__ __launch_bounds__(256) void ns_h2_split_kernel(const PrepDesc* __rest
   uint8_t* x_out = static_cast<uint8_t*>(d.d_out) - tiles * (64 * 64 * 4);
   const float* scale = reinterpret_cast<const float*>(reinterpret_cast<const uint8_t*>(d.partials) +
                                                       ((tiles * 4 + 255) & ~int64_t(255)));
-  const float s = ldexpf(*scale, kNsH2First);
+  const int small = *ns_small(scale);
+  const float s = ldexpf(*scale, kNsH2First + small);
   if (lt == 0 && threadIdx.x == 0) {
     NsH2State* st = ns_state(scale);
-    st->ex[0] = kNsH2First;
-    st->lam[0] = 1.0f;                       // ||X_0||_F <= 1
-    st->xmax[0] = __float_as_uint(1.0f);
+    st->ex[0] = kNsH2First + small;
+    st->lam[0] = ldexpf(1.0f, -2 * small);   // ||X_0||_F <= 2^-small
+    st->xmax[0] = __float_as_uint(ldexpf(1.0f, -small));
     st->amax = 0;
     st->a2 = 0;
   }

@@ -472,8 +472,8 @@ constexpr double kH2MaxSlack = 1024.0;
 std::vector<NsH2Exponents> h2_exponents(const double* coeffs, int steps) {
   auto exponent = [](double bound) { return int(std::min(100.0, std::max(-100.0, std::floor(14.0 - std::log2(bound))))); };
   std::vector<NsH2Exponents> s;
-  double sigma = 1.0, slack = 1.0;
-  int ex = kNsH2First;
+  double sigma = 1.0, slack = 1.0, growth = 1.0;  // growth: of a small X, whatever the bounds
+  int ex = kNsH2First, gx = 0;
   for (int k = 0; k < steps; ++k) {
     const double a = coeffs[3 * k], b = coeffs[3 * k + 1], c = coeffs[3 * k + 2];
     auto q = [&](double y) { return std::fabs(a + b * y + c * y * y); };
@@ -501,8 +501,11 @@ std::vector<NsH2Exponents> h2_exponents(const double* coeffs, int steps) {
     slack *= next / (sigma * low);
     if (!(slack <= kH2MaxSlack) || !(bb > 1e-18 && bb < 1e18) || !(next > 1e-18 && next < 1e18)) return {};
     sigma = next;
-    NsH2Exponents h{ex, exponent(y1), exponent(bb), exponent(sigma)};
+    growth *= 1.01 * bb;
+    NsH2Exponents h{ex, exponent(y1), exponent(bb), exponent(sigma), gx, 0};
+    h.gxn = int(std::max(-1000.0, std::floor(std::log2(sigma / growth))));
     ex = h.exn;
+    gx = h.gxn;
     s.push_back(h);
   }
   return s;

@@ -187,9 +187,14 @@ struct GemmDesc {
 // alternate with the iterate's buffers).
 struct NsH2Exponents {
   int32_t ex, ea, eb, exn;
+  // A matrix whose norm is below eps starts at ||X_0||_F <= 2^-small (an int beside its norm scale, else 0) and stays
+  // that far below the bounds but for the steps' growth: X and X' take 2^max(0, small + gx) and
+  // 2^max(0, small + gxn) more.
+  int32_t gx, gxn;
 };
 constexpr size_t kNsH2StateOffset = 64;
 constexpr int kNsH2First = 15;  // X_0's exponent: its elements are at most 1
+constexpr int kNsH2MaxSmall = 60;
 struct NsH2State {
   int32_t ex[2], ea, eb, eq;  // exponents of X, A, B' and of A A in q2
   float lam[2];               // bound on lambda_max(A) of the step that reads this X

@@ -553,6 +553,26 @@ def test_ns_f32_schedules_with_loose_bounds(native, shape, which):
     assert err <= 2e-5, err
 
 
+@pytest.mark.parametrize("norm", [1e-8, 1e-12, 1e-16, 1e-20, 1e-24])
+@pytest.mark.parametrize("shape", [(256, 512), (513, 257), (20, 3000), (1024, 1500)])
+@pytest.mark.parametrize("which", ["fixed", "minimax", "down_and_up", "quintic40"])
+def test_ns_f32_norm_below_eps(native, shape, which, norm):
+    """An input whose norm is below eps is not brought to norm 1: the iterate starts small (down to 1e-17), and every
+    step still holds it with 32 bits' accuracy (the same bar as above), also once many steps have grown it to size."""
+    import torch
+    m, n = shape
+    sched = {"fixed": [(A, B, C)] * 5, "quintic40": [(1.875, -1.25, 0.375)] * 40, **WIDE_SCHEDULES}[which]
+    _say(f"ns f32 norm {norm} {which} {m}x{n}")
+    x = np.random.default_rng(415 + m + n).standard_normal((m, n))
+    x = (x * (norm / np.linalg.norm(x))).astype(np.float32)
+    out = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    native.newton_schulz_schedule_t(to_dev(x, synth.F32), out, sched, 1e-7, "f32")
+    _sync()
+    ref = oracle.newton_schulz(x, A, B, C, len(sched), schedule=sched)
+    err = rel_fro(from_dev(out), ref)
+    assert err <= 2e-5, err
+
+
 def test_muon_f32_with_minimax_schedule_matches_oracle(native):
     _say("muon f32, minimax schedule")
     rng = np.random.default_rng(335)
