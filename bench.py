@@ -36,7 +36,8 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2516.6   # dense bf16 MFMA: 256 CU x 2.4 GHz x 4096 flop/clk/CU
 PEAK_HBM_GBS = 8000.0       # HBM3E
-PEAK_F32_TFLOPS = 157.3     # dense fp32 MFMA (the fp32 NS path runs v_mfma_f32_32x32x2f32)
+# the fp32 NS path: each fp32 product as three dense fp16 ones (same rate as bf16) of two-part operands
+PEAK_F32_TFLOPS = PEAK_BF16_TFLOPS / 3.0
 METRIC = "owner Muon-step latency (ms) and NS TFLOP/s (% MFMA bf16 peak) at 1 MI355X"
 GEMM_KERNEL = "gemm_bf16_kernel"
 GEMM_SOURCE = os.path.join(ROOT, "paper_2607_05895_amd", "csrc", "kernels_gemm.hip")
@@ -222,8 +223,7 @@ def time_reduction(args, native, wl, keep, ents, h, ws, stream, hev, plain_step_
     step_ms = hev.elapsed_ms(e0, e1) / args.steps
     prep_ms = plain_prep_ms + (step_ms - plain_step_ms)
     elts = wl.muon_elements()
-    es_ns = 2 if wl.hp.ns_dtype == synth.BF16 else 4
-    nbytes = elts * (W * es_g + 8 + 2 * es_ns)      # W parts, momentum in/out, u and u^T
+    nbytes = elts * (W * es_g + 8 + 4)      # W parts, momentum in/out, u and u^T in bf16 or u in fp32
     log(f"reduction W={W}: step {step_ms:.3f} ms, fused momentum+reduction pass ~{prep_ms:.3f} ms "
         f"({nbytes / (prep_ms * 1e-3) / 1e9:.0f} GB/s)")
     return {"grad_parts": W, "ms_per_step": round(step_ms, 4), "reduce_prep_ms": round(prep_ms, 4),
@@ -337,20 +337,38 @@ def planner_report(native, spans, gpu_span, ctx=None) -> dict:
 
 
 PEAK_F32_MFMA_TFLOPS = 157.3  # dense fp32 MFMA
-# Shampoo / SOAP products run on the bf16 MFMA with each fp32 operand split into three bf16 parts
-# (six bf16 products per fp32 product): their ceiling in fp32 flop is the bf16 peak / 6
-PEAK_SPLIT_TFLOPS = PEAK_BF16_TFLOPS / 6.0
 
 
-def shampoo_nominal_flop(shapes, iters: int, refresh: bool) -> float:
+def shampoo_nominal_flop(shapes, refresh: bool) -> float:
     """Nominal flop of one Shampoo step: statistics G G^T and G^T G, P_L G and (P_L G) P_R, and on
-    refresh 4 iters - 3 products of d x d per side (the last iteration forms X only)."""
+    refresh 10 d^3 per side, an eigendecomposition's order of work (the root's iteration ends by
+    itself on the device, so what it executes is not known here)."""
     tot = 0.0
     for m, n in shapes:
         tot += 2.0 * m * m * n + 2.0 * m * n * n          # statistics
         tot += 2.0 * m * m * n + 2.0 * m * n * n          # U = P_L G P_R
         if refresh:
-            tot += (4 * iters - 3) * 2.0 * (m ** 3 + n ** 3)
+            tot += 10.0 * (m ** 3 + n ** 3)
+    return tot
+
+
+def shampoo_mfma_flop(shapes) -> float:
+    """bf16 MFMA flop that a step with a bf16 gradient and stored preconditioners executes: statistics in one
+    product (upper tiles), the product with G, on the longer side, in three and the other in six."""
+    return sum(m * n * (1.0 * (m + n) + 2.0 * (3 * max(m, n) + 6 * min(m, n))) for m, n in shapes)
+
+
+def soap_mfma_flop(shapes, max_precond_dim: int = 4096) -> float:
+    """The same for a SOAP step without refresh: statistics in one product, the projection of G that comes first
+    in three, every other product (of M, of both halves, the two back) in six."""
+    tot = 0.0
+    for m, n in shapes:
+        sides = [d for d in (m, n) if d <= max_precond_dim]
+        tot += m * n * sum(1.0 * d + 6 * 2.0 * d for d in sides)           # statistics, projection back
+        first = max(m, n) if len(sides) == 2 and n > m else m if m <= max_precond_dim else None
+        for d in sides:
+            tot += m * n * 2.0 * d * (3 + 6 if d == first else 6 + 6)      # projections of G and M
+            first = None if d == first else first
     return tot
 
 
@@ -413,7 +431,7 @@ def share_record(native, torch, dev, hev, stream, index, steps, warmup) -> dict:
     peak = PEAK_BF16_TFLOPS if bf16_ns else PEAK_F32_TFLOPS
     flops = wl.ns_flops_nominal()
     es = {synth.BF16: 2, synth.F32: 4}
-    prep_bytes = sum(e.m * e.n * (es[e.grad_dtype] + 8 + 2 * es[hp.ns_dtype]) for e in wl.muon)
+    prep_bytes = sum(e.m * e.n * (es[e.grad_dtype] + 8 + 4) for e in wl.muon)
     rec = {"workload": wl.name, "description": wl.description, "muon_matrices": len(wl.muon),
            "muon_elements": wl.muon_elements(), "adamw_elements": wl.adamw_elements(),
            "ns_dtype": "bf16" if bf16_ns else "f32", "steps": steps, "warmup": warmup,
@@ -482,13 +500,15 @@ def time_shampoo(native, torch, dev, hev, stream, steps, warmup, iters=20) -> di
         hev.record(b, stream)
         torch.cuda.synchronize()
         ms = hev.elapsed_ms(a, b) / steps
-        fl = shampoo_nominal_flop(shapes, iters, refresh)
+        fl = shampoo_nominal_flop(shapes, refresh)
         key = "refresh" if refresh else "stale_preconditioners"
         out[key] = {"ms_per_step": round(ms, 4), "nominal_flop_per_step": fl,
                     "nominal_tflops": round(fl / (ms * 1e-3) / 1e12, 2),
                     "x_fp32_mfma_peak": round(fl / (ms * 1e-3) / 1e12 / PEAK_F32_MFMA_TFLOPS, 4),
-                    "frac_split_bf16_peak": round(fl / (ms * 1e-3) / 1e12 / PEAK_SPLIT_TFLOPS, 4),
                     "workspace_gib": round(ws.numel() / 2 ** 30, 3)}
+        if not refresh:
+            out[key]["executed_frac_bf16_peak"] = round(shampoo_mfma_flop(shapes) / (ms * 1e-3) / 1e12
+                                                        / PEAK_BF16_TFLOPS, 4)
         log(f"shampoo ({key}): {ms:.3f} ms per step, {fl / (ms * 1e-3) / 1e12:.1f} nominal TFLOP/s")
         del ws
     return out
@@ -561,8 +581,10 @@ def time_soap(native, torch, dev, hev, stream, steps, warmup, shapes=None, label
         out[key] = {"ms_per_step": round(ms, 4), "nominal_flop_per_step": fl,
                     "nominal_tflops": round(fl / (ms * 1e-3) / 1e12, 2),
                     "x_fp32_mfma_peak": round(fl / (ms * 1e-3) / 1e12 / PEAK_F32_MFMA_TFLOPS, 4),
-                    "frac_split_bf16_peak": round(fl / (ms * 1e-3) / 1e12 / PEAK_SPLIT_TFLOPS, 4),
                     "workspace_gib": round(ws.numel() / 2 ** 30, 3)}
+        if not refresh:
+            out[key]["executed_frac_bf16_peak"] = round(soap_mfma_flop(shapes, max_precond_dim) / (ms * 1e-3) / 1e12
+                                                        / PEAK_BF16_TFLOPS, 4)
         log(f"{tag} ({key}): {ms:.3f} ms per step, {fl / (ms * 1e-3) / 1e12:.1f} nominal TFLOP/s")
         del ws
     del keep, ents
@@ -684,7 +706,7 @@ def main() -> int:
     adamw_ms = (sum(hev.elapsed_ms(e[4], e[5]) for e in ev) / n_ev) if aents else 0.0
     log(f"step {ms_per_step:.3f} ms: prep+norm {prep_ms:.3f}, NS {ns_ms:.3f}, apply {apply_ms:.3f}, "
         f"AdamW {adamw_ms:.3f}")
-    if hp.ns_dtype == synth.BF16 and hp.ns_steps >= 1:
+    if hp.ns_steps >= 1:
         apply_ms = 0.0  # the events around the (absent) apply pass bracket no kernel
 
     flops = wl.ns_flops_nominal()
@@ -697,9 +719,9 @@ def main() -> int:
     es_g = 2 if all(e.grad_dtype == synth.BF16 for e in wl.muon) else 4
     es_p = 2 if all(e.param_dtype == synth.BF16 for e in wl.muon) else 4
     es_ns = 2 if hp.ns_dtype == synth.BF16 else 4
-    prep_bytes = elts * (es_g + 4 + 4 + 2 * es_ns)       # g, m in/out, u and u^T
-    # on the bf16 path the parameter update runs in the last NS update's epilogue (no apply pass)
-    apply_fused = hp.ns_dtype == synth.BF16 and hp.ns_steps >= 1
+    prep_bytes = elts * (es_g + 4 + 4 + 4)               # g, m in/out, u and u^T in bf16 or u in fp32
+    # the parameter update runs in the last NS update's epilogue (no apply pass)
+    apply_fused = hp.ns_steps >= 1
     apply_bytes = 0 if apply_fused else elts * (es_ns + 2 * es_p)   # O, p in/out
     alg_bytes = elts * (es_g + 8 + 2 * es_p)              # g, m in/out, p in/out
     adamw_bytes = sum(e.numel * ({"bf16": 2, "f32": 4}[e.param_dtype] * 2 +
