@@ -87,7 +87,9 @@ typedef struct {
  *   lr >= 0, weight_decay >= 0, 0 <= momentum < 1, nesterov 0/1,
  *   (a, b, c) NS coefficients, 0 <= ns_steps < 100, eps > 0 (norm clamp),
  *   lr_adjust an mfsdp_lr_adjust, ns_dtype: BF16 = NS products on bf16 MFMA with fp32
- *   accumulation and bf16 storage between products; F32 = fp32 throughout.
+ *   accumulation and bf16 storage between products; F32 = fp32 accuracy: each matrix between products in two
+ *   scaled fp16 parts (22 to 23 bits of every element down to 2^-28 of a bound on the largest, 2^-51 of it in
+ *   absolute terms below), products of them with fp32 accumulation, everything else in fp32.
  *   ns_schedule: NULL = the triple (a, b, c) on every NS step; otherwise a host array of ns_steps
  *   finite triples (a_k, b_k, c_k), k = 0 .. ns_steps - 1, step k computing
  *   X <- a_k X + (b_k A + c_k A A) X. It is read during the call and not kept. (The paper runs one
@@ -291,8 +293,10 @@ size_t mfsdp_inverse_root_workspace_size(int64_t d, int32_t p, int32_t iters);
 /* out = (a + rho I)^(-1/p), rho = eps + eps_rel ||a||_F, for a symmetric positive semidefinite
  * d x d fp32 matrix `a` (row-major, device; read only; not checked for symmetry), by at most `iters`
  * steps of a coupled iteration (p = 1, 2: Newton's, Guo and Higham 2006; p = 4: the same coupling with
- * a quadratic factor, the iteration the Shampoo step uses; products as there). p in {1, 2, 4}; 1 <= d <= 65536; eps > 0; eps_rel >= 0;
- * 1 <= iters <= 100.
+ * a quadratic factor, the iteration the Shampoo step uses). Products at fp32 accuracy: for p = 1, 2 as in the
+ * Shampoo step; for p = 4 of iterates held in two scaled fp16 parts (22 to 23 bits down to 2^-28 of a bound on
+ * the largest element, 2^-51 of it in absolute terms below). p in {1, 2, 4}; 1 <= d <= 65536; eps > 0;
+ * eps_rel >= 0; 1 <= iters <= 100.
  * `out` (d x d fp32, device) must not overlap `a`. In fp32 the iteration is stable while rho is
  * at least about 1e-6 ||a||_F; a smaller ridge can diverge. Same stream, workspace and error
  * rules as mfsdp_shampoo_step. */

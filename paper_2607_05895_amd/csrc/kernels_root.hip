@@ -30,8 +30,8 @@ __device__ __forceinline__ int find_desc(const D* d, int count, int b) {
 // One 128 x 128 upper tile of one product per workgroup (4 waves of 64 x 64, 80 KiB of LDS: two workgroups
 // per CU, so that one multiplies while the other is in its epilogue). Bound by the matrix pipe at the
 // power-limited clock, the operand loads and the LDS reads: a launch with one product of each of 24 sides
-// (4 of 3072, 20 of 768; 1.31e11 flop on the upper tiles) takes 0.39 to 0.42 ms, 1000 TFLOP/s of fp16 MFMA (the
-// six bf16 products per 16 k of the general kernel: 0.68 ms); the matrix pipe is busy 68 % of the cycles in
+// (4 of 3072, 20 of 768; 1.31e11 flop on the upper tiles) takes 0.38 to 0.47 ms, 1000 TFLOP/s of fp16 MFMA (the
+// six bf16 products per 16 k of the general kernel: 0.68 ms); the matrix pipe is busy 70 % of the cycles in
 // which its CU has work. 256 x 128 tiles (a quarter fewer operand bytes) took the same time, and so did
 // splitting the sides over two streams to fill the launches' tails.
 // Epilogue: the tile's image (64 blocks of 1 KiB) is formed in LDS. E, if any, is first copied there as it

@@ -289,7 +289,7 @@ hipError_t launch_adamw(const AdamWBatch& batch, int total_blocks, hipStream_t s
 // NS tile sizes (padding granularity of the workspace buffers).
 constexpr int kTileBF16 = 256;
 // The bf16 products of a launch with few 256 x 256 tiles run on 128 x 128 tiles, two workgroups per CU
-// (the padding stays 256).
+// (buffers stay padded to 256; where every product of a call runs on them, they cover the matrices padded to 128).
 constexpr int kTileBF16Small = 128;
 // The fp32 path pads to 64; its products run on 128 x 128 or 64 x 64 tiles, which may reach past the padding.
 constexpr int kTileF32 = 64;

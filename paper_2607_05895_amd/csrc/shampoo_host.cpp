@@ -16,7 +16,7 @@
 // 2.44-fold (root_rule.h has the rows of coefficients, the rules and their reasons). The iterates are
 // held as split fp16 and multiplied by h2_root_kernel. Two layers of width 768 / 3072 (24 sides, spectra
 // 1 / (1 + i)), the whole step: Newton on three-way bf16 splits 35.96 ms, the quadratic T on them 21.74 ms,
-// on split fp16 14.3 ms; one 768-wide root of a rank-deficient statistic 2.99, 1.84, 0.76 ms.
+// on split fp16 13.2 ms; one 768-wide root of a rank-deficient statistic 2.99, 1.84, 0.76 ms.
 // p = 1, 2: the coupled Newton iteration (Guo and Higham, SIAM J. Matrix Anal. Appl. 2006): with
 // z = (1 + p) / (2 ||A||_F),
 //   X_0 = z^(1/p) I,  M_0 = z A,  T_k = ((p + 1) I - M_k) / p,  X_{k+1} = X_k T_k,  M_{k+1} = T_k^p M_k,

@@ -311,7 +311,7 @@ UPDATE_EDGES = [(129, 513), (513, 129), (260, 772), (772, 260), (127, 255), (255
 def test_muon_parameter_update_tile_edges(native, dtype, full_size_tiles):
     """The last launch's parameter update at tile edges: alone (128 x 128 tiles, staged through LDS by
     four elements or one) and next to a 4096 x 4096 matrix that takes every launch to 256 x 256 tiles
-    (staged by eight or four, or straight from the accumulators). Matches the oracle; parameters do not
+    (staged by eight or by four, a row's last elements singly). Matches the oracle; parameters do not
     depend on whether the update is also written out."""
     import torch
     _say(f"muon update at tile edges: dtype={dtype} full_size_tiles={full_size_tiles} {UPDATE_EDGES}")
